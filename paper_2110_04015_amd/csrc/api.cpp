@@ -118,6 +118,15 @@ void free_multi(ba_system *s, DevMulti &m) {
     sfree(s, m.partial);
     sfree(s, m.group);
     sfree(s, m.chunk_seg);
+    sfree(s, m.blk_cam);
+    sfree(s, m.cam_blk);
+    sfree(s, m.tile_seg);
+    sfree(s, m.pair_obs);
+    sfree(s, m.pair_grp);
+    sfree(s, m.pair_f);
+    sfree(s, m.pair_h);
+    sfree(s, m.pair_partial);
+    for (uint32_t *&r : m.records) sfree(s, r);
     m = DevMulti();
 }
 
@@ -179,9 +188,13 @@ void free_all(ba_system *s) {
     s->prof_events.clear();
 }
 
+const void *tile_stream(const ba_system *s, int precision) {
+    return precision == 1 ? (const void *)s->J32 : precision == 2 ? (const void *)s->J16 : (const void *)s->J64;
+}
+
 SchurArgs schur_args(ba_system *s, int precision) {
     SchurArgs a{};
-    a.J = precision == 1 ? (const void *)s->J32 : precision == 2 ? (const void *)s->J16 : (const void *)s->J64;
+    a.J = tile_stream(s, precision);
     a.precision = precision;
     a.meta = s->meta;
     a.tile_lmk_base = s->tile_lmk_base;
@@ -285,14 +298,76 @@ ba_status ensure_precision(ba_system *s, int precision) {
     return BA_OK;
 }
 
+// Output rows per observation (the subsets among its landmark's observers, on average) from
+// which the multidirectional product takes its two-pass form.  The one-pass form adds that many
+// rows per observation in LDS and writes the chunk's rows out; the two-pass form reads the
+// records twice whatever their number.  Measured, one pass / two passes (us, FP64): walk of
+// 300 cameras, 1.8 rows 48 / 73, 3.5 rows 75 / 89; ring of 50 cameras, 4.2 rows 31 / 33, 10.5
+// rows 56 / 35; cap of 571 cameras, 2.0 rows 103 / 125, 3.7 rows 155 / 130, 5.8 rows 272 / 140,
+// 10.0 rows 1035 / 175; cap of 80, 6.2 rows 63 / 39.
+constexpr double kTwoPassRows = 5.0;
+
+// The two-pass product's camera-major records in a precision (the tile stream of that
+// precision must exist); fill_values renews those that were made.
+ba_status ensure_records(ba_system *s, int precision) {
+    DevMulti &m = s->multi;
+    if (!m.two_pass || m.records[precision]) return BA_OK;
+    ba_status st = salloc(s, &m.records[precision], (size_t)s->m * record_words(precision, s->dp) * 4);
+    if (st != BA_OK) return st;
+    if (!s->ws_counting)
+        launch_pair_records(s->m, precision, s->dp, s->cam_obs, s->obs_slot, tile_stream(s, precision),
+                            m.records[precision], s->stream);
+    HIPCHK(hipGetLastError());
+    return BA_OK;
+}
+
+// The two-pass product's work-groups, observation words and buffers.
+ba_status make_two_pass(ba_system *s, HostMultiPlan &mp) {
+    DevMulti &m = s->multi;
+    const HostPlan &P = s->plan;
+    std::vector<int32_t> cam_blk((size_t)s->np + 1, 0), blk_cam;
+    for (int c = 0; c < s->np; ++c) {
+        const int64_t k = P.cam_obs_ptr[(size_t)c + 1] - P.cam_obs_ptr[(size_t)c];
+        const int nb = (int)((k + kPairObs - 1) / kPairObs);
+        cam_blk[(size_t)c + 1] = cam_blk[(size_t)c] + nb;
+        blk_cam.insert(blk_cam.end(), (size_t)nb, c);
+    }
+    const size_t slots = (size_t)P.n_tiles * kTile;
+    ba_status st;
+    if ((st = supload(s, &m.mmeta, mp.mmeta)) != BA_OK) return st;
+    if ((st = supload(s, &m.slot_cam, mp.slot_cam)) != BA_OK) return st;
+    if ((st = supload(s, &m.pair_ll, mp.pair_ll)) != BA_OK) return st;
+    if ((st = supload(s, &m.cam_blk, cam_blk)) != BA_OK) return st;
+    if ((st = supload(s, &m.blk_cam, blk_cam)) != BA_OK) return st;
+    if (!P.cam_seg.empty() && (st = supload(s, &m.tile_seg, P.tile_seg)) != BA_OK) return st;
+    std::vector<uint8_t> grp8(slots, 0);
+    for (size_t i = 0; i < slots; ++i) grp8[i] = mp.pair_grp[i] < 0 ? 0 : (uint8_t)mp.pair_grp[i];
+    if ((st = supload(s, &m.pair_grp, grp8)) != BA_OK) return st;
+    if ((st = salloc(s, &m.pair_obs, (size_t)s->m)) != BA_OK) return st;
+    if ((st = salloc(s, &m.pair_f, slots * 2)) != BA_OK) return st;
+    if ((st = salloc(s, &m.pair_h, slots * 4)) != BA_OK) return st;
+    if ((st = salloc(s, &m.pair_partial, blk_cam.size() * (size_t)(s->dp * mp.N))) != BA_OK) return st;
+    if (!s->ws_counting)
+        launch_pair_obs(s->m, s->cam_obs, s->obs_slot, m.mmeta, m.pair_obs, s->stream);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(s->stream));   // the host vectors go out of scope
+    m.two_pass = true;
+    m.N = mp.N;
+    m.n_blocks = (int)blk_cam.size();
+    return BA_OK;
+}
+
 // The partition into N subsets and, with `plan`, the layout of the implicit
-// multidirectional product (the explicit S's grouped product needs the partition only).
-ba_status ensure_multi(ba_system *s, int N, bool plan = true) {
-    if (s->multi.N == N && s->multi.group && (!plan || s->multi.partial)) return BA_OK;
-    if (s->ws_base && s->multi.group)
-        return fail(BA_ERR_WORKSPACE, "the caller's workspace holds the layout of N = " + std::to_string(s->multi.N) +
+// multidirectional product in a precision (the explicit S's grouped product needs the
+// partition only).
+ba_status ensure_multi(ba_system *s, int N, int precision, bool plan = true) {
+    DevMulti &m = s->multi;
+    if (m.N == N && m.group && (!plan || m.partial || m.two_pass)) return plan ? ensure_records(s, precision) : BA_OK;
+    if (s->ws_base && m.group)
+        return fail(BA_ERR_WORKSPACE, "the caller's workspace holds the layout of N = " + std::to_string(m.N) +
                                           " subsets (ba_build_opts.ws_groups), not of N = " + std::to_string(N));
-    free_multi(s, s->multi);
+    free_multi(s, m);
+    ++s->multi_serial;
     HostMultiPlan mp;
     std::string err;
     // subsets: Sec. 3.2's partition of the poses; in a batch, of each problem's poses
@@ -311,26 +386,38 @@ ba_status ensure_multi(ba_system *s, int N, bool plan = true) {
     }
     ba_status st;
     if (!plan) {
-        if ((st = supload(s, &s->multi.group, grp)) != BA_OK) return st;
-        s->multi.N = N;
+        if ((st = supload(s, &m.group, grp)) != BA_OK) return st;
+        m.N = N;
         HIPCHK(hipStreamSynchronize(s->stream));   // grp goes out of scope
         return BA_OK;
     }
-    st = build_multi_plan(s->plan, N, 512, mp, err, grp.data());
-    if (st != BA_OK) return fail(st, err);
-    // LDS of the multidirectional kernel: max_out rows of 9 plus 2 x 64 x 3 values (FP64),
-    // up to the device's work-group limit (160 KiB on gfx950: 2,232 rows)
+    build_multi_pairs(s->plan, N, mp, grp.data());
+    // LDS of the one-pass kernel: max_out rows of 9 plus 2 x 64 x 3 values (FP64), up to the
+    // device's work-group limit (160 KiB on gfx950: 2,232 rows).  A problem with a wider tile
+    // is refused in either form, so that what is supported does not hang on the mean.
     int dev = 0, lds_max = 65536;
     HIPCHK(hipGetDevice(&dev));
     HIPCHK(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-    const size_t lds_need = (size_t)(mp.max_out * s->dp + 6 * kTile) * sizeof(double);
-    if (lds_need > (size_t)lds_max)
-        return fail(BA_ERR_UNSUPPORTED, "multidirectional product: a tile touches " + std::to_string(mp.max_out) +
-                                            " (camera, subset) pairs; at most " +
-                                            std::to_string(((size_t)lds_max / sizeof(double) - 6 * kTile) / s->dp) +
-                                            " fit in LDS");
-    DevMulti &m = s->multi;
+    const int lds_rows = (int)(((size_t)lds_max / sizeof(double) - 6 * kTile) / s->dp);
+    auto check_rows = [&](int rows) {
+        return rows <= lds_rows ? BA_OK
+                                : fail(BA_ERR_UNSUPPORTED, "multidirectional product: a tile touches " +
+                                                               std::to_string(rows) +
+                                                               " (camera, subset) pairs; at most " +
+                                                               std::to_string(lds_rows) + " fit in LDS");
+    };
     hipStream_t q = s->stream;
+    if (N <= kMaxBlock && s->plan.n_tiles * kTile <= (int64_t)UINT32_MAX && (double)mp.out_rows >= kTwoPassRows * (double)s->m) {
+        if (mp.tile_rows > lds_rows && (st = check_rows(multi_tile_outputs(s->plan, mp))) != BA_OK) return st;
+        if ((st = supload(s, &m.group, grp)) != BA_OK || (st = make_two_pass(s, mp)) != BA_OK) {
+            free_multi(s, m);
+            return st;
+        }
+        return ensure_records(s, precision);
+    }
+    st = build_multi_chunks(s->plan, 512, mp, err);
+    if (st != BA_OK) return fail(st, err);
+    if ((st = check_rows(mp.max_out)) != BA_OK) return st;
     if ((st = supload(s, &m.mmeta, mp.mmeta)) != BA_OK) return st;
     if ((st = supload(s, &m.slot_cam, mp.slot_cam)) != BA_OK) return st;
     if ((st = supload(s, &m.pair_ll, mp.pair_ll)) != BA_OK) return st;
@@ -355,7 +442,7 @@ ba_status ensure_multi(ba_system *s, int N, bool plan = true) {
 
 MultiArgs multi_args(ba_system *s, int precision) {
     MultiArgs a{};
-    a.J = precision == 1 ? (const void *)s->J32 : precision == 2 ? (const void *)s->J16 : (const void *)s->J64;
+    a.J = tile_stream(s, precision);
     a.precision = precision;
     a.meta = s->meta;
     a.mmeta = s->multi.mmeta;
@@ -378,6 +465,19 @@ MultiArgs multi_args(ba_system *s, int precision) {
     a.np = s->np;
     a.N = s->multi.N;
     a.dp = s->dp;
+    a.two_pass = s->multi.two_pass;
+    a.n_tiles = s->plan.n_tiles;
+    a.n_blocks = s->multi.n_blocks;
+    a.blk_cam = s->multi.blk_cam;
+    a.cam_blk = s->multi.cam_blk;
+    a.cam_obs_ptr = s->cam_obs_ptr;
+    a.tile_seg = s->multi.tile_seg;
+    a.records = s->multi.records[precision];
+    a.pair_obs = s->multi.pair_obs;
+    a.pair_grp = s->multi.pair_grp;
+    a.pair_f = s->multi.pair_f;
+    a.pair_h = s->multi.pair_h;
+    a.pair_partial = s->multi.pair_partial;
     return a;
 }
 
@@ -508,7 +608,7 @@ ba_status prepare_mcg(ba_system *s, int N, int precision) {
     if (st != BA_OK || N <= 1) return st;
     if (N > s->np) return fail(BA_ERR_INVALID_ARG, "N must be in [1, n_cams]");
     const bool bsr = s->bsr_val && precision == 0 && N <= kMaxBlock;
-    return ensure_multi(s, N, !bsr);
+    return ensure_multi(s, N, precision, !bsr);
 }
 }  // namespace ba
 
@@ -615,6 +715,9 @@ static ba_status fill_values(ba_system *s, const double *J_p, const double *J_l,
     HIPCHK(hipStreamSynchronize(q));
     if (hst & kStatusNonfinite) return fail(BA_ERR_NONFINITE, "NaN or Inf in J_p, J_l or r");
     launch_pack(s->slot_obs, nslots, J_p, J_l, s->J64, s->J32, s->J16, q, s->dp);
+    for (int p = 0; p < 3; ++p)
+        if (s->multi.records[p])
+            launch_pair_records(m, p, s->dp, s->cam_obs, s->obs_slot, tile_stream(s, p), s->multi.records[p], q);
     launch_landmarks_base(s->nl, s->lmk_first_slot, s->lmk_count, s->slot_obs, J_l, r, s->Vraw, s->bl, q);
     launch_cameras_base(s->np, s->cam_obs_ptr, s->cam_obs, J_p, r, s->Uraw, s->bp, q, s->dp);
     HIPCHK(hipGetLastError());
@@ -640,7 +743,9 @@ static ba_status reserve_solvers(ba_system *s, const ba_build_opts *o) {
             // the explicit S's grouped product needs the partition only, reduced-precision
             // products the implicit layout
             const bool bsr = s->bsr_val && N <= kMaxBlock;
-            if ((st = ensure_multi(s, N, !bsr || mixed)) != BA_OK) return st;
+            if ((st = ensure_multi(s, N, mixed && bsr ? (o->store_fp32 ? 1 : 2) : 0, !bsr || mixed)) != BA_OK) return st;
+            if (o->store_fp32 && (st = ensure_records(s, 1)) != BA_OK) return st;
+            if (o->store_bf16 && (st = ensure_records(s, 2)) != BA_OK) return st;
         }
         if ((st = mcg_buffers(s, N, 1 + (int64_t)it * N)) != BA_OK) return st;
     }
@@ -959,7 +1064,7 @@ ba_status ba_schur_matmat_grouped(ba_system *s, int32_t N, const double *z, doub
     ba_status st = ensure_precision(s, precision);
     if (st != BA_OK) return st;
     const bool bsr = s->bsr_val && precision == 0 && N <= kMaxBlock;   // the grouped kernel keeps N x 9 sums in LDS
-    if ((st = ensure_multi(s, N, !bsr)) != BA_OK) return st;
+    if ((st = ensure_multi(s, N, precision, !bsr)) != BA_OK) return st;
     if (bsr)
         launch_bsr_mm_grouped(s->np, N, s->bsr_ptr, s->bsr_col, s->bsr_val, s->multi.group, z, Y, s->stream);
     else
@@ -1210,7 +1315,7 @@ static ba_status mcg_core(ba_system *s, const double *bt, bool report_true, int 
     ba_status st = ensure_precision(s, prec);
     if (st != BA_OK) return st;
     const bool use_bsr_multi = N > 1 && s->bsr_val && prec == 0 && N <= kMaxBlock;
-    if (N > 1 && (st = ensure_multi(s, N, !use_bsr_multi)) != BA_OK) return st;
+    if (N > 1 && (st = ensure_multi(s, N, prec, !use_bsr_multi)) != BA_OK) return st;
     const int64_t n = (int64_t)s->np * s->dp;
     hipStream_t q = s->stream;
     const int64_t cap = opts.max_history_cols > 0 ? opts.max_history_cols : 1 + (int64_t)opts.max_iter * N;
@@ -1717,9 +1822,10 @@ struct ba_batch {
         int precision = -1, window = 0, N = 0;
         double tau = 0.0, eps = 0.0;
         int64_t cap = 0;
+        int64_t layout = -1;   // multi_serial of the multidirectional layout the graph reads
         bool operator==(const GraphKey &o) const {
             return x == o.x && precision == o.precision && window == o.window && N == o.N && tau == o.tau &&
-                   eps == o.eps && cap == o.cap;
+                   eps == o.eps && cap == o.cap && layout == o.layout;
         }
     } gkey;
     int32_t *host_i = nullptr;      // pinned
@@ -1926,6 +2032,7 @@ ba_status batch_window(ba_batch *b, const BatchRun &R, int precision, double tau
     key.tau = tau;
     key.eps = eps;
     key.cap = b->cap;
+    key.layout = b->sys->multi_serial;
     hipStream_t gs = b->gstream;
     if (!b->gexec || !(b->gkey == key)) {
         if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
@@ -2089,7 +2196,7 @@ ba_status ba_batch_mcg_solve(ba_batch *b, int32_t N, double tau, double *x, cons
     ba_system *s = b->sys;
     hipStream_t q = s->stream;
     if ((st = ensure_precision(s, opts.precision)) != BA_OK) return st;
-    if (N > 1 && (st = ensure_multi(s, N)) != BA_OK) return st;
+    if (N > 1 && (st = ensure_multi(s, N, opts.precision)) != BA_OK) return st;
     const int inner_max = opts.precision == 0 ? opts.max_iter : std::min(opts.max_inner, opts.max_iter);
     const int64_t cap = opts.max_history_cols > 0 ? opts.max_history_cols : 1 + (int64_t)inner_max * N;
     if ((st = ensure_batch_ws(b, N, cap)) != BA_OK) return st;

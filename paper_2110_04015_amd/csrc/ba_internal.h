@@ -67,6 +67,9 @@ struct HostMultiPlan {
     int n_chunks = 0;
     int64_t n_part = 0;
     int max_out = 0;                      // largest out-pair count of a chunk
+    int64_t out_rows = 0;                 // (observation, subset of its landmark) pairs in all
+    int tile_rows = 0;                    // most (observation, subset) pairs of one tile
+    std::vector<int32_t> pair_grp;        // tile * 64 + pair -> subset (-1 past the tile's pairs)
     std::vector<uint32_t> mmeta;          // tile slot -> own pair | first pair << 8 | pairs << 16
     std::vector<int32_t> slot_cam;        // tile slot -> camera (0 for padding)
     std::vector<uint8_t> pair_ll;         // tile * 64 + pair -> landmark index in tile
@@ -95,6 +98,14 @@ struct DevMulti {
     double *partial = nullptr;
     int32_t *group = nullptr;             // camera -> subset
     int32_t *chunk_seg = nullptr;         // batches: chunk -> problem
+    // the two-pass form (see MultiArgs)
+    bool two_pass = false;
+    int n_blocks = 0;
+    int32_t *blk_cam = nullptr, *cam_blk = nullptr, *tile_seg = nullptr;
+    uint2 *pair_obs = nullptr;
+    uint8_t *pair_grp = nullptr;
+    double *pair_f = nullptr, *pair_h = nullptr, *pair_partial = nullptr;
+    uint32_t *records[3] = {nullptr, nullptr, nullptr};   // by precision, made when first asked for
 };
 
 // Plan construction (host, plan.cpp).  Returns BA_OK or an error with message.
@@ -108,8 +119,14 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
                      const int32_t *cam_seg = nullptr, int target_chunks = 0, int max_tiles_multi = 0,
                      int target_multi = 0);
 // group (nullable, host, [np]): subset of every camera; default partition_groups(np, N)
+// build_multi_pairs: the (landmark, subset) pairs of every tile only; build_multi_chunks: the
+// one-pass product's chunks and output rows on top of them; build_multi_plan: both
+void build_multi_pairs(const HostPlan &plan, int N, HostMultiPlan &mp, const int32_t *group = nullptr);
+ba_status build_multi_chunks(const HostPlan &plan, int max_out, HostMultiPlan &mp, std::string &err);
 ba_status build_multi_plan(const HostPlan &plan, int N, int max_out, HostMultiPlan &mp,
                            std::string &err, const int32_t *group = nullptr);
+// Most distinct (camera, subset) pairs of one tile.
+int multi_tile_outputs(const HostPlan &plan, const HostMultiPlan &mp);
 void partition_groups(int np, int N, int32_t *group);
 void covisibility_degree(const HostPlan &plan, std::vector<int32_t> &deg);
 
@@ -199,6 +216,7 @@ struct ba_system {
     double *host_pinned_dev = nullptr;  // the same memory as kernels address it
     double sc_tag = 0.0;            // tag of the last scalars a kernel wrote to host_pinned[SC_COUNT]
     ba::DevMulti multi;
+    int64_t multi_serial = 0;       // layouts made so far
     // batches: problem of every camera and of every chunk of the S product (device)
     int32_t *seg_cam = nullptr, *seg_chunk = nullptr;
     // explicit S in block-sparse rows (optional)

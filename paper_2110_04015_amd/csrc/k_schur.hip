@@ -497,39 +497,51 @@ __device__ __forceinline__ void fetch_mtile(const MultiArgs &a, const double *__
     b.o1 = oi[cnt > 1 ? 1 : 0];
 }
 
-// One tile: e = J_p z_c; g per (landmark, subset) pair = sum over the pair's
-// observations of J_l^T e; h = V^-1 g; every observation of the landmark adds
-// J_p^T (e [own pair] - J_l h_pair) to its (camera, pair subset) row.  With SEG (the
-// reduced-precision products) g is a segmented sum across the pair's lanes in registers
-// and the pair's last lane publishes h; without, g goes through FP64 LDS atomics and lane
-// p forms h of pair p.
-template <typename T, int DP, bool SEG>
-__device__ __forceinline__ void multi_tile(const MultiArgs &a, const T (&J)[2 * DP + 6], const double (&zb)[DP],
-                                           const dbl2_t (&vi)[3], const MultiSlot &m, uint32_t obase, int o0, int o1,
-                                           int lane, double *yloc, double *gloc, double *hloc) {
+// First half of one tile: e = J_p z_c; g per (landmark, subset) pair = sum over the pair's
+// observations of J_l^T e; h = V^-1 g.  In the reduced-precision products g is a segmented
+// sum across the pair's lanes in registers and the pair's last lane holds h; in FP64 g goes
+// through LDS atomics and lane p forms h of pair p.
+template <typename T>
+struct PairVals {
+    T e0, e1;       // e of the lane's observation
+    T h0, h1, h2;   // h of pair `pair`
+    int pair;       // -1: the lane holds no pair's h
+};
+
+template <int PREC, typename T, int DP, bool TWO>
+__device__ __forceinline__ PairVals<T> pair_tile(const T (&J)[2 * DP + 6], const double (&zb)[DP],
+                                                 const dbl2_t (&vi)[3], const MultiSlot &m, int lane, double *gloc) {
     constexpr int L0 = 2 * DP, L1 = 2 * DP + 3;   // J_l rows 0 and 1
     const bool valid = m.mm != kPad;
+    PairVals<T> r;
     T e0 = 0, e1 = 0;
 #pragma unroll
     for (int k = 0; k < DP; ++k) {
         e0 += J[k] * (T)zb[k];
         e1 += J[DP + k] * (T)zb[k];
     }
+    r.e0 = e0;
+    r.e1 = e1;
     const int own = (int)(m.mm & 0xFFu);
     const T w0 = (T)vi[0].x, w1 = (T)vi[0].y, w2 = (T)vi[1].x;
     const T w3 = (T)vi[1].y, w4 = (T)vi[2].x, w5 = (T)vi[2].y;
-    if constexpr (SEG) {
+    T g0, g1, g2;
+    if constexpr (PREC != 0) {
         // segments: the pairs (own pair index), padding lanes one each
         const Segs sg = tile_segments(valid ? (uint32_t)own << 16 : kPad, lane);
         double gs[3];   // the pair's total, in its last lane (the only one that uses it)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) gs[k] = segment_scan(valid ? (double)(J[L0 + k] * e0 + J[L1 + k] * e1) : 0.0, sg);
-        if (valid && sg.end == lane) {
-            const T g0 = (T)gs[0], g1 = (T)gs[1], g2 = (T)gs[2];
-            hloc[own * 3 + 0] = (double)(w0 * g0 + w1 * g1 + w2 * g2);
-            hloc[own * 3 + 1] = (double)(w1 * g0 + w3 * g1 + w4 * g2);
-            hloc[own * 3 + 2] = (double)(w2 * g0 + w4 * g1 + w5 * g2);
+        for (int k = 0; k < 3; ++k) {
+            // TWO: contracted as the compiler contracts the one-pass kernel's short chunks (the
+            // dense problems the two-pass form takes), so that both give the same term
+            T t;
+            if constexpr (!TWO) t = J[L0 + k] * e0 + J[L1 + k] * e1;
+            else if constexpr (PREC == 2 && DP == 6) t = fmaf(J[L0 + k], e0, J[L1 + k] * e1);
+            else t = fmaf(J[L1 + k], e1, J[L0 + k] * e0);
+            gs[k] = segment_scan(valid ? (double)t : 0.0, sg);
         }
+        r.pair = valid && sg.end == lane ? own : -1;
+        g0 = (T)gs[0], g1 = (T)gs[1], g2 = (T)gs[2];
     } else {
         gloc[lane * 3 + 0] = 0;
         gloc[lane * 3 + 1] = 0;
@@ -540,12 +552,30 @@ __device__ __forceinline__ void multi_tile(const MultiArgs &a, const T (&J)[2 * 
             for (int k = 0; k < 3; ++k) atomicAdd(&gloc[own * 3 + k], (double)(J[L0 + k] * e0 + J[L1 + k] * e1));
         }
         wave_sync();
-        if (m.pll != 0xFFu) {
-            const T g0 = (T)gloc[lane * 3], g1 = (T)gloc[lane * 3 + 1], g2 = (T)gloc[lane * 3 + 2];
-            hloc[lane * 3 + 0] = (double)(w0 * g0 + w1 * g1 + w2 * g2);
-            hloc[lane * 3 + 1] = (double)(w1 * g0 + w3 * g1 + w4 * g2);
-            hloc[lane * 3 + 2] = (double)(w2 * g0 + w4 * g1 + w5 * g2);
-        }
+        r.pair = m.pll != 0xFFu ? lane : -1;
+        g0 = (T)gloc[lane * 3], g1 = (T)gloc[lane * 3 + 1], g2 = (T)gloc[lane * 3 + 2];
+    }
+    r.h0 = w0 * g0 + w1 * g1 + w2 * g2;
+    r.h1 = w1 * g0 + w3 * g1 + w4 * g2;
+    r.h2 = w2 * g0 + w4 * g1 + w5 * g2;
+    return r;
+}
+
+// One tile: h per pair (pair_tile), then every observation of the landmark adds
+// J_p^T (e [own pair] - J_l h_pair) to its (camera, pair subset) row.
+template <int PREC, typename T, int DP>
+__device__ __forceinline__ void multi_tile(const MultiArgs &a, const T (&J)[2 * DP + 6], const double (&zb)[DP],
+                                           const dbl2_t (&vi)[3], const MultiSlot &m, uint32_t obase, int o0, int o1,
+                                           int lane, double *yloc, double *gloc, double *hloc) {
+    constexpr int L0 = 2 * DP, L1 = 2 * DP + 3;   // J_l rows 0 and 1
+    const bool valid = m.mm != kPad;
+    const PairVals<T> pv = pair_tile<PREC, T, DP, false>(J, zb, vi, m, lane, gloc);
+    const T e0 = pv.e0, e1 = pv.e1;
+    const int own = (int)(m.mm & 0xFFu);
+    if (pv.pair >= 0) {
+        hloc[pv.pair * 3 + 0] = (double)pv.h0;
+        hloc[pv.pair * 3 + 1] = (double)pv.h1;
+        hloc[pv.pair * 3 + 2] = (double)pv.h2;
     }
     wave_sync();
     if (valid) {
@@ -576,9 +606,9 @@ __device__ __forceinline__ void process_mtile(const MultiArgs &a, const MultiBuf
     if constexpr (PREC == 2) {
         T J[2 * DP + 6];
         Stream<2, DP>::template unpack<T>(b.r.w, J);
-        multi_tile<T, DP, true>(a, J, b.z, b.vi, b.m, b.obase, b.o0, b.o1, lane, yloc, gloc, hloc);
+        multi_tile<PREC, T, DP>(a, J, b.z, b.vi, b.m, b.obase, b.o0, b.o1, lane, yloc, gloc, hloc);
     } else {
-        multi_tile<T, DP, PREC != 0>(a, b.r.v, b.z, b.vi, b.m, b.obase, b.o0, b.o1, lane, yloc, gloc, hloc);
+        multi_tile<PREC, T, DP>(a, b.r.v, b.z, b.vi, b.m, b.obase, b.o0, b.o1, lane, yloc, gloc, hloc);
     }
 }
 
@@ -654,7 +684,458 @@ __global__ __launch_bounds__(256) void k_reduce_multi(int np, int N, const int32
     }
 }
 
+// ---------------------------------------------------------------- N columns in two passes
+//
+// Where a landmark's observers fall in many subsets the one-pass form pays for every
+// (observation, subset) pair an LDS row of its own: a tile of the 571-camera dense problem
+// with 47 subsets touches up to 1,600 of them, one wavefront fills a CU's LDS, and its rows
+// go to memory as partials (369 MB).  Here the landmark side and the camera side are split:
+//   k_pair_h (landmark-major tiles): h = V^-1 g per (landmark, subset) and
+//     f = e - J_l h_own per observation, the own subset's term;
+//   k_pair_out (camera-major records): a work-group sums the columns of up to kPairObs
+//     observations of one camera, sum_o J_p^T ([p = own] f_o - [p != own] J_l h_{l,p});
+//   k_pair_reduce: the work-groups of a camera, in order.
+// Every term is formed as the one-pass form forms it.
+// The 571-camera dense problem (897k observations, N = 47), one-pass form -> this one: FP64
+// 845 + 100 us (product, reduction) -> 38 + 98 + 12 us, FP32 888 + 101 us -> 24 + 82 + 13 us.
+// k_pair_h streams the records (5 TB/s); the camera side is bound by the issue of its vector
+// instructions (95 per four observations in FP64, beside 35 us of the matrix cores).
+
+// h of a (landmark, subset) pair and the subset
+template <typename T>
+struct alignas(4 * sizeof(T)) PairH;
+template <>
+struct alignas(32) PairH<double> {
+    double h[3];
+    int64_t grp;
+};
+template <>
+struct alignas(16) PairH<float> {
+    float h[3];
+    int32_t grp;
+};
+
+// a . b, in the order in which the one-pass form rounds it
+template <typename T>
+__device__ __forceinline__ T dot3(const T *a, const T *b) {
+    return __builtin_elementwise_fma(a[2], b[2], __builtin_elementwise_fma(a[0], b[0], a[1] * b[1]));
+}
+
+// a - b, never contracted with the operations that formed a
+template <typename T>
+__device__ __forceinline__ T sub_plain(T a, T b) {
+#pragma clang fp contract(off)
+    return a - b;
+}
+
+// -f of every slot's own subset (F, two values) and the entry of every pair (H, at
+// 64 tile + pair).  One wavefront per tile.
+template <int PREC, typename T, int DP>
+__global__ __launch_bounds__(256) void k_pair_h(MultiArgs a, const double *__restrict__ z) {
+    if (a.skip && *a.skip != 0.0) return;
+    constexpr int L0 = 2 * DP, L1 = 2 * DP + 3;   // J_l rows 0 and 1
+    __shared__ double gsh[PREC == 0 ? 4 * 3 * kTile : 1];
+    __shared__ T hsh[4][3 * kTile];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t t = (int64_t)blockIdx.x * 4 + w;
+    if (t >= a.n_tiles) return;   // uniform per wavefront
+    if (a.seg_skip && a.seg_skip[a.tile_seg[t]]) return;
+    const int64_t si = t * kTile + lane;
+    MultiSlot m;
+    m.mm = a.mmeta[si];
+    m.cam = a.slot_cam[si];
+    m.pll = a.pair_ll[si];
+    m.ooff = 0;
+    TileBuf<PREC, T, DP> b;
+    fetch_record<PREC, T, DP>(a.J, (int)t, lane, b);
+    const bool valid = m.mm != kPad;
+    const double *zc = z + (int64_t)(valid ? m.cam : 0) * DP;
+    double zb[DP];
+#pragma unroll
+    for (int k = 0; k < DP; ++k) zb[k] = zc[k];
+    int ll;
+    if constexpr (PREC != 0) {
+        const uint32_t mt = a.meta[si];
+        ll = mt != kPad ? (int)((mt >> 16) & 63u) : 0;
+    } else {
+        ll = m.pll != 0xFFu ? (int)m.pll : 0;
+    }
+    const dbl2_t *vp = reinterpret_cast<const dbl2_t *>(a.vinv + (int64_t)(a.tile_lmk_base[t] + ll) * 6);
+    dbl2_t vi[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) vi[q] = vp[q];
+    T J[2 * DP + 6];
+    if constexpr (PREC == 2) {
+        Stream<2, DP>::template unpack<T>(b.w, J);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 2 * DP + 6; ++k) J[k] = b.v[k];
+    }
+    const PairVals<T> r = pair_tile<PREC, T, DP, true>(J, zb, vi, m, lane, gsh + (PREC == 0 ? w * 3 * kTile : 0));
+    T *hl = hsh[w];
+    if (r.pair >= 0) {
+        hl[r.pair * 3 + 0] = r.h0;
+        hl[r.pair * 3 + 1] = r.h1;
+        hl[r.pair * 3 + 2] = r.h2;
+        PairH<T> e;
+        e.h[0] = r.h0;
+        e.h[1] = r.h1;
+        e.h[2] = r.h2;
+        e.grp = a.pair_grp[t * kTile + r.pair];
+        reinterpret_cast<PairH<T> *>(a.pair_h)[t * kTile + r.pair] = e;
+    }
+    wave_sync();
+    if (valid) {
+        const int own = (int)(m.mm & 0xFFu);
+        T *F = reinterpret_cast<T *>(a.pair_f) + si * 2;
+        F[0] = sub_plain(dot3(J + L0, hl + own * 3), r.e0);
+        F[1] = sub_plain(dot3(J + L1, hl + own * 3), r.e1);
+    }
+}
+
+// The share of wavefront w of work-group `block`: observations [lo, hi) of those at b0.
+struct PairShare {
+    int64_t b0;
+    int c, lo, hi;
+};
+__device__ __forceinline__ PairShare pair_share(const MultiArgs &a, int block, int w) {
+    PairShare s;
+    s.c = a.blk_cam[block];
+    s.b0 = a.cam_obs_ptr[s.c] + (int64_t)(block - a.cam_blk[s.c]) * kPairObs;
+    const int cnt = (int)min((int64_t)kPairObs, a.cam_obs_ptr[s.c + 1] - s.b0);
+    const int per = (cnt + 3) / 4;
+    s.lo = min(cnt, w * per);
+    s.hi = min(cnt, s.lo + per);
+    return s;
+}
+
+// The four wavefronts' column sums (negated terms), [component][column], to the block's partials.
+template <int DP>
+__device__ __forceinline__ void pair_store(const double (&sh)[4][DP][64], int N, double *__restrict__ partial) {
+    __syncthreads();
+    double *out = partial + (int64_t)blockIdx.x * DP * N;
+    for (int i = threadIdx.x; i < DP * 64; i += 256) {
+        const int k = i >> 6, p = i & 63;
+        if (p < N) out[k * N + p] = -((sh[0][k][p] + sh[1][k][p]) + (sh[2][k][p] + sh[3][k][p]));
+    }
+}
+
+// In both forms of the camera side a wavefront takes four observations at a time: lane
+// (o, i) = (lane / 16, lane mod 16) works for observation j + o on pair i of its landmark
+// (a landmark with more than 16 pairs takes further rounds), so the work follows the pairs
+// there are and not the number of subsets.  pair_obs: the observation's first pair entry and,
+// in y, its slot in that tile (bits 0..5) and its landmark's pairs (bits 8..14).
+
+// FP32 and BF16: the lane forms its pair's column terms and adds them in the wavefront's
+// column sums in LDS.  (With a column per lane and the records in scalar registers the kernel
+// took 111 us instead of 82: the terms of the subsets that do not see a landmark are work too.)
+template <int PREC, typename T, int DP>
+__global__ __launch_bounds__(256) void k_pair_out(MultiArgs a, const void *__restrict__ records,
+                                                  const uint2 *__restrict__ obs, const T *__restrict__ F,
+                                                  const PairH<T> *__restrict__ H, double *__restrict__ partial) {
+    if (a.skip && *a.skip != 0.0) return;
+    typedef Stream<PREC, DP> St;
+    typedef typename St::word_t W;
+    constexpr int L0 = 2 * DP, L1 = 2 * DP + 3;   // J_l rows 0 and 1
+    __shared__ double sh[4][DP][64];
+    const int lane = threadIdx.x & 63, i = lane & 15, o = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const PairShare me = pair_share(a, blockIdx.x, w);
+    if (a.seg_skip && a.seg_skip[a.cam_seg[me.c]]) return;
+    const int lo = me.lo, hi = me.hi;
+    const int own = a.group[me.c];
+    const W *rec = reinterpret_cast<const W *>(records) + me.b0 * St::kWords;
+    obs += me.b0;
+#pragma unroll
+    for (int k = 0; k < DP; ++k) sh[w][k][lane] = 0.0;
+    wave_sync();
+    struct Group {
+        W rw[St::kWords];
+        T f0, f1;
+        PairH<T> h;
+        int cnt;
+        uint32_t first;
+    };
+    auto words = [&](int j) { return obs[min(j + o, hi - 1)]; };
+    auto load = [&](int j, const uint2 &d, Group &g) {
+        const int at = min(j + o, hi - 1);
+#pragma unroll
+        for (int q = 0; q < St::kWords; ++q) g.rw[q] = rec[(int64_t)at * St::kWords + q];
+        const uint32_t slot = (d.x & ~63u) | (d.y & 63u);
+        g.f0 = F[(int64_t)slot * 2];
+        g.f1 = F[(int64_t)slot * 2 + 1];
+        g.cnt = j + o < hi ? (int)(d.y >> 8) : 0;
+        g.first = d.x;
+        g.h = H[d.x + (i < g.cnt ? i : 0)];
+    };
+    auto add = [&](Group &g) {
+        T J[2 * DP + 6];
+        St::template unpack<T>(g.rw, J);
+        for (int p = i;;) {
+            if (p < g.cnt) {
+                T f0 = dot3(J + L0, g.h.h), f1 = dot3(J + L1, g.h.h);
+                if (g.h.grp == own) {
+                    f0 = g.f0;
+                    f1 = g.f1;
+                }
+#pragma unroll
+                for (int k = 0; k < DP; ++k) atomicAdd(&sh[w][k][g.h.grp], (double)fmaf(J[k], f0, J[DP + k] * f1));
+            }
+            p += 16;
+            if (!__any(p < g.cnt)) break;
+            g.h = H[g.first + (p < g.cnt ? p : 0)];
+        }
+    };
+    if (lo < hi) {
+        Group A, B;
+        load(lo, words(lo), A);
+        uint2 d = words(lo + 4);
+        int j = lo;
+        for (; j + 4 < hi; j += 8) {
+            load(j + 4, d, B);
+            d = words(j + 8);
+            add(A);
+            load(j + 8, d, A);
+            d = words(j + 12);
+            add(B);
+        }
+        if (j < hi) add(A);
+    }
+    pair_store<DP>(sh, a.N, partial);
+}
+
+typedef double dbl4_t __attribute__((ext_vector_type(4)));
+
+// x of lane `AT` of the lane's row of 16, in every lane of the row
+template <int AT>
+__device__ __forceinline__ double row_bcast(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x150 + AT, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x150 + AT, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// FP64, on the matrix cores: lane (o, i) of v_mfma_f64_16x16x4f64 supplies
+// A[i][o] = J_p,o[row][i] and B[o][i] = f_{o, column}[row], NT tiles of 16 columns, one
+// product per row and tile.  J_l rides in the lanes past DP of the first row's load, F in lane
+// 15, and DPP hands them to the row; the pairs' f go to their columns through LDS (98 us on
+// the problem above; with f formed per column from gathered h 112 us, a column per lane with
+// FMAs and scalar loads 141 us).
+template <int DP, int NT>
+__global__ __launch_bounds__(256) void k_pair_out_mfma(MultiArgs a, const double *__restrict__ records,
+                                                       const uint2 *__restrict__ obs,
+                                                       const double *__restrict__ F,
+                                                       const PairH<double> *__restrict__ H,
+                                                       double *__restrict__ partial) {
+    if (a.skip && *a.skip != 0.0) return;
+    constexpr int NV = 2 * DP + 6;
+    __shared__ double sh[4][DP][64];
+    __shared__ double fsh[4][4][2][16 * NT];
+    const int lane = threadIdx.x & 63, i = lane & 15, o = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const PairShare me = pair_share(a, blockIdx.x, w);
+    if (a.seg_skip && a.seg_skip[a.cam_seg[me.c]]) return;
+    const int lo = me.lo, hi = me.hi;
+    const int own = a.group[me.c];
+    // record values of the lane: J_p row 0 (i < DP), then J_l; J_p row 1; lane 15: F
+    const double *rec0 = records + me.b0 * NV + (i < DP ? i : i < DP + 6 ? DP + i : 0);
+    const double *rec1 = records + me.b0 * NV + DP + (i < DP ? i : 0);
+    obs += me.b0;
+    double (*fc)[2][16 * NT] = fsh[w];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) fc[o][0][16 * q + i] = fc[o][1][16 * q + i] = 0.0;
+    wave_sync();
+    dbl4_t acc[NT];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) acc[q] = dbl4_t{0.0, 0.0, 0.0, 0.0};
+    struct Group {
+        double x0, x1;
+        PairH<double> h;
+        int cnt;
+        uint32_t first;
+    };
+    auto words = [&](int j) { return obs[min(j + o, hi - 1)]; };
+    auto load = [&](int j, const uint2 &d, Group &g) {
+        const int64_t at = (int64_t)min(j + o, hi - 1) * NV;
+        const double *fp = F + (int64_t)((d.x & ~63u) | (d.y & 63u)) * 2;
+        g.x0 = *(i == 15 ? fp : rec0 + at);
+        g.x1 = *(i == 15 ? fp + 1 : rec1 + at);
+        g.cnt = j + o < hi ? (int)(d.y >> 8) : 0;   // past the share: no pair, so f = 0
+        g.first = d.x;
+        g.h = H[d.x + (i < g.cnt ? i : 0)];
+    };
+    auto add = [&](Group &g) {
+        const double l0 = row_bcast<DP + 0>(g.x0), l1 = row_bcast<DP + 1>(g.x0), l2 = row_bcast<DP + 2>(g.x0);
+        const double l3 = row_bcast<DP + 3>(g.x0), l4 = row_bcast<DP + 4>(g.x0), l5 = row_bcast<DP + 5>(g.x0);
+        const double own0 = row_bcast<15>(g.x0), own1 = row_bcast<15>(g.x1);
+        auto put = [&](int p, double f0, double f1) {
+            if (p < g.cnt) {
+                fc[o][0][g.h.grp] = f0;
+                fc[o][1][g.h.grp] = f1;
+            }
+        };
+        auto pair = [&](int p) {
+            const double f0 = l0 * g.h.h[0] + l1 * g.h.h[1] + l2 * g.h.h[2];
+            const double f1 = l3 * g.h.h[0] + l4 * g.h.h[1] + l5 * g.h.h[2];
+            const bool mine = g.h.grp == own;
+            put(p, mine ? own0 : f0, mine ? own1 : f1);
+        };
+        const int64_t grp = g.h.grp;
+        pair(i);
+        bool more = false;
+        for (int p = i + 16; __any(p < g.cnt); p += 16) {
+            more = true;
+            g.h = H[g.first + (p < g.cnt ? p : 0)];
+            pair(p);
+        }
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(g.x0, fc[o][0][16 * q + i], acc[q], 0, 0, 0);
+            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(g.x1, fc[o][1][16 * q + i], acc[q], 0, 0, 0);
+        }
+        wave_sync();
+        // the columns are zero again before the next four observations
+        if (more) {
+#pragma unroll
+            for (int q = 0; q < NT; ++q) fc[o][0][16 * q + i] = fc[o][1][16 * q + i] = 0.0;
+        } else if (i < g.cnt) {
+            fc[o][0][grp] = 0.0;
+            fc[o][1][grp] = 0.0;
+        }
+        wave_sync();
+    };
+    if (lo < hi) {   // four observations in flight while four are added, their words earlier still
+        Group A, B;
+        load(lo, words(lo), A);
+        uint2 d = words(lo + 4);
+        int j = lo;
+        for (; j + 4 < hi; j += 8) {
+            load(j + 4, d, B);
+            d = words(j + 8);
+            add(A);
+            load(j + 8, d, A);
+            d = words(j + 12);
+            add(B);
+        }
+        if (j < hi) add(A);
+    }
+#pragma unroll
+    for (int q = 0; q < NT; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (o + 4 * e < DP) sh[w][o + 4 * e][16 * q + i] = acc[q][e];
+    pair_store<DP>(sh, a.N, partial);
+}
+
+template <int DP>
+static void launch_pair_out_mfma(const MultiArgs &a, hipStream_t s) {
+    const dim3 g((unsigned)a.n_blocks), b(256);
+    const double *rec = reinterpret_cast<const double *>(a.records);
+    const double *F = reinterpret_cast<const double *>(a.pair_f);
+    const PairH<double> *H = reinterpret_cast<const PairH<double> *>(a.pair_h);
+    switch ((a.N + 15) / 16) {
+    case 1: hipLaunchKernelGGL((k_pair_out_mfma<DP, 1>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial); break;
+    case 2: hipLaunchKernelGGL((k_pair_out_mfma<DP, 2>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial); break;
+    case 3: hipLaunchKernelGGL((k_pair_out_mfma<DP, 3>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial); break;
+    default: hipLaunchKernelGGL((k_pair_out_mfma<DP, 4>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial);
+    }
+}
+
+// Y[p][c] = [group(c) == p] lambda diag(U_c) z_c + sum of camera c's blocks, in order:
+// wavefront w of the work-group of (c, component) adds blocks w, w + 4, ..., lane p column p.
+template <int DP>
+__global__ __launch_bounds__(256) void k_pair_reduce(MultiArgs a, const double *__restrict__ partial,
+                                                     const double *__restrict__ z, double *__restrict__ Y) {
+    if (a.skip && *a.skip != 0.0) return;
+    const int c = blockIdx.x / DP, k = blockIdx.x - c * DP;
+    if (a.seg_skip && a.seg_skip[a.cam_seg[c]]) return;
+    __shared__ double sh[4][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int b1 = a.cam_blk[c + 1], N = a.N;
+    const double *p0 = partial + (int64_t)k * N + (lane < N ? lane : 0);
+    double s = 0.0;
+    for (int b = a.cam_blk[c] + w; b < b1; b += 32) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p0[(int64_t)(b + 4 * u < b1 ? b + 4 * u : b) * DP * N];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (b + 4 * u < b1) s += v[u];
+    }
+    sh[w][lane] = s;
+    __syncthreads();
+    if (w == 0 && lane < N) {
+        const int64_t row = (int64_t)c * DP + k;
+        const double t = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
+        Y[(int64_t)lane * a.np * DP + row] = (a.group[c] == lane ? a.dU[row] * z[row] : 0.0) + t;
+    }
+}
+
+// Camera-major copy of the tile stream: 16-byte word q of the i-th observation of the
+// camera order goes to word i kw + q (consecutive threads take consecutive words).
+__global__ __launch_bounds__(256) void k_pair_records(int64_t m, int kw, const int64_t *__restrict__ cam_obs,
+                                                      const int64_t *__restrict__ obs_slot,
+                                                      const u32x4_t *__restrict__ J, u32x4_t *__restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= m * kw) return;
+    const int64_t o = i / kw;
+    const int q = (int)(i - o * kw);
+    const int64_t s = obs_slot[cam_obs[o]];
+    out[i] = J[(s / kTile * kw + q) * kTile + s % kTile];
+}
+
+void launch_pair_records(int64_t m, int precision, int dp, const int64_t *cam_obs, const int64_t *obs_slot,
+                         const void *J, void *out, hipStream_t s) {
+    const int kw = record_words(precision, dp);
+    hipLaunchKernelGGL(k_pair_records, dim3((unsigned)((m * kw + 255) / 256)), dim3(256), 0, s, m, kw, cam_obs,
+                       obs_slot, reinterpret_cast<const u32x4_t *>(J), reinterpret_cast<u32x4_t *>(out));
+}
+
+// pair_obs of every observation, in camera order (see k_pair_out).
+__global__ __launch_bounds__(256) void k_pair_obs(int64_t m, const int64_t *__restrict__ cam_obs,
+                                                  const int64_t *__restrict__ obs_slot,
+                                                  const uint32_t *__restrict__ mmeta, uint2 *__restrict__ obs) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= m) return;
+    const int64_t s = obs_slot[cam_obs[i]];
+    const uint32_t mm = mmeta[s];
+    obs[i] = make_uint2((uint32_t)(s & ~(int64_t)63) + ((mm >> 8) & 0xFFu), (uint32_t)(s & 63) | ((mm >> 16) & 0xFFu) << 8);
+}
+
+void launch_pair_obs(int64_t m, const int64_t *cam_obs, const int64_t *obs_slot, const uint32_t *mmeta, uint2 *obs,
+                     hipStream_t s) {
+    hipLaunchKernelGGL(k_pair_obs, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, m, cam_obs, obs_slot, mmeta, obs);
+}
+
+template <int PREC, typename T, int DP>
+static void launch_two_pass(const MultiArgs &a, const double *z, double *Y, hipStream_t s) {
+    hipLaunchKernelGGL((k_pair_h<PREC, T, DP>), dim3((unsigned)((a.n_tiles + 3) / 4)), dim3(256), 0, s, a, z);
+    if constexpr (PREC == 0)
+        launch_pair_out_mfma<DP>(a, s);
+    else
+        hipLaunchKernelGGL((k_pair_out<PREC, T, DP>), dim3((unsigned)a.n_blocks), dim3(256), 0, s, a, a.records,
+                           a.pair_obs, reinterpret_cast<const T *>(a.pair_f),
+                           reinterpret_cast<const PairH<T> *>(a.pair_h), a.pair_partial);
+    hipLaunchKernelGGL(k_pair_reduce<DP>, dim3((unsigned)(a.np * DP)), dim3(256), 0, s, a, a.pair_partial, z, Y);
+}
+
 void launch_schur_multi(const MultiArgs &a, const double *z, double *Y, hipStream_t s) {
+    if (a.two_pass) {
+        if (a.dp == 6) {
+            switch (a.precision) {
+                case 0: launch_two_pass<0, double, 6>(a, z, Y, s); break;
+                case 1: launch_two_pass<1, float, 6>(a, z, Y, s); break;
+                default: launch_two_pass<2, float, 6>(a, z, Y, s); break;
+            }
+        } else {
+            switch (a.precision) {
+                case 0: launch_two_pass<0, double, 9>(a, z, Y, s); break;
+                case 1: launch_two_pass<1, float, 9>(a, z, Y, s); break;
+                default: launch_two_pass<2, float, 9>(a, z, Y, s); break;
+            }
+        }
+        return;
+    }
     if (a.n_chunks > 0) {
         const size_t lds = (size_t)(a.max_out * a.dp + 6 * kTile) * sizeof(double);
         const dim3 g(a.n_chunks), b(kTile);

@@ -140,7 +140,34 @@ struct MultiArgs {
     const int32_t *chunk_seg = nullptr, *cam_seg = nullptr, *seg_skip = nullptr;
     const double *skip = nullptr;             // nullable: when *skip != 0 the launch does nothing
     int dp = 9;                               // pose dimension: 9, or 6 for extrinsics only
+    // the two-pass form (launch_schur_multi takes it when set)
+    bool two_pass = false;
+    int64_t n_tiles = 0;
+    int n_blocks = 0;                         // work-groups of the camera side
+    const int32_t *blk_cam = nullptr;         // work-group -> camera
+    const int32_t *cam_blk = nullptr;         // [np + 1] camera -> its first work-group
+    const int64_t *cam_obs_ptr = nullptr;     // [np + 1] camera -> range of the camera order
+    const int32_t *tile_seg = nullptr;        // batches: tile -> problem
+    const void *records = nullptr;            // camera-major records in the product's precision
+    const uint2 *pair_obs = nullptr;          // camera-major observation words
+    const uint8_t *pair_grp = nullptr;        // 64 tile + pair -> subset
+    void *pair_f = nullptr, *pair_h = nullptr;  // own terms per slot, h and subset per pair
+    double *pair_partial = nullptr;           // n_blocks * dp * N
 };
+// Observations of one work-group of the camera side: 64 per wavefront.  512 and 1024 leave
+// small problems with too few work-groups (80 cameras, 108k observations: FP64 38.8, 43.3 and
+// 54.9 us) and gain nothing on the 571-camera one (174.6, 172.2, 198.2 us).
+constexpr int kPairObs = 256;
+// 16-byte words of a record
+inline int record_words(int precision, int dp) {
+    return dp == 6 ? (precision == 0 ? RecordShape<6>::kW64 : precision == 1 ? RecordShape<6>::kW32 : RecordShape<6>::kW16)
+                   : (precision == 0 ? RecordShape<9>::kW64 : precision == 1 ? RecordShape<9>::kW32 : RecordShape<9>::kW16);
+}
+// camera-major copy of a tile stream, and the observation words of the camera side
+void launch_pair_records(int64_t m, int precision, int dp, const int64_t *cam_obs, const int64_t *obs_slot,
+                         const void *J, void *out, hipStream_t s);
+void launch_pair_obs(int64_t m, const int64_t *cam_obs, const int64_t *obs_slot, const uint32_t *mmeta, uint2 *obs,
+                     hipStream_t s);
 // Y[p] = S (z restricted to subset p), Y column-major [N][n]
 void launch_schur_multi(const MultiArgs &a, const double *z, double *Y, hipStream_t s);
 

@@ -265,8 +265,7 @@ void covisibility_degree(const HostPlan &P, std::vector<int32_t> &deg) {
     }
 }
 
-ba_status build_multi_plan(const HostPlan &P, int N, int max_out, HostMultiPlan &M,
-                           std::string &err, const int32_t *group_in) {
+void build_multi_pairs(const HostPlan &P, int N, HostMultiPlan &M, const int32_t *group_in) {
     M = HostMultiPlan();
     M.N = N;
     const int np = P.np;
@@ -280,9 +279,10 @@ ba_status build_multi_plan(const HostPlan &P, int N, int max_out, HostMultiPlan 
     M.slot_ooff.assign((size_t)T * kTile, 0);
     M.tile_oidx.assign((size_t)T + 1, 0);
     // per tile: landmark pairs (landmark, subset) in order of first appearance
-    std::vector<int32_t> pair_grp((size_t)T * kTile, -1);
+    std::vector<int32_t> &pair_grp = M.pair_grp;
+    pair_grp.assign((size_t)T * kTile, -1);
     for (int64_t t = 0; t < T; ++t) {
-        int npairs = 0;
+        int npairs = 0, rows = 0;
         int q = 0;
         while (q < kTile) {
             size_t s0 = (size_t)(t * kTile + q);
@@ -309,27 +309,57 @@ ba_status build_multi_plan(const HostPlan &P, int N, int max_out, HostMultiPlan 
             }
             int cnt = npairs - base;
             for (int a = q; a < q1; ++a) M.mmeta[(size_t)(t * kTile + a)] |= (uint32_t)cnt << 16;
+            rows += cnt * (q1 - q);
             q = q1;
         }
+        M.out_rows += rows;
+        M.tile_rows = std::max(M.tile_rows, rows);
     }
+}
+
+// distinct out-pairs (camera * N + subset) of tile t, ascending
+static void tile_outputs(const HostPlan &P, const HostMultiPlan &M, int64_t t, std::vector<int64_t> &need) {
+    need.clear();
+    for (int q = 0; q < kTile; ++q) {
+        size_t s = (size_t)(t * kTile + q);
+        if (P.slot_obs[s] < 0) continue;
+        uint32_t mm = M.mmeta[s];
+        int base = (mm >> 8) & 0xFF, cnt = (mm >> 16) & 0xFF;
+        int c = M.slot_cam[s];
+        for (int j = 0; j < cnt; ++j) need.push_back((int64_t)c * M.N + M.pair_grp[(size_t)(t * kTile + base + j)]);
+    }
+    std::sort(need.begin(), need.end());
+    need.erase(std::unique(need.begin(), need.end()), need.end());
+}
+
+int multi_tile_outputs(const HostPlan &P, const HostMultiPlan &M) {
+    int most = 0;
+    std::vector<int64_t> need;
+    for (int64_t t = 0; t < P.n_tiles; ++t) {
+        tile_outputs(P, M, t, need);
+        most = std::max(most, (int)need.size());
+    }
+    return most;
+}
+
+ba_status build_multi_plan(const HostPlan &P, int N, int max_out, HostMultiPlan &M, std::string &err,
+                           const int32_t *group_in) {
+    build_multi_pairs(P, N, M, group_in);
+    return build_multi_chunks(P, max_out, M, err);
+}
+
+ba_status build_multi_chunks(const HostPlan &P, int max_out, HostMultiPlan &M, std::string &err) {
+    const int np = P.np, N = M.N;
+    const int64_t T = P.n_tiles;
+    const std::vector<int32_t> &pair_grp = M.pair_grp;
+    std::vector<int64_t> need;
     // chunks over out-pairs (camera, subset)
     std::vector<int32_t> stamp((size_t)np * N, -1), local((size_t)np * N, 0);
     std::vector<int64_t> part_key;                    // partial row -> camera * N + subset
     int chunk = -1, outs = 0, ntiles_in = 0;
     M.max_out = 0;
     for (int64_t t = 0; t < T; ++t) {
-        // distinct out-pairs needed by this tile alone
-        std::vector<int64_t> need;
-        for (int q = 0; q < kTile; ++q) {
-            size_t s = (size_t)(t * kTile + q);
-            if (P.slot_obs[s] < 0) continue;
-            uint32_t mm = M.mmeta[s];
-            int base = (mm >> 8) & 0xFF, cnt = (mm >> 16) & 0xFF;
-            int c = M.slot_cam[s];
-            for (int j = 0; j < cnt; ++j) need.push_back((int64_t)c * N + pair_grp[(size_t)(t * kTile + base + j)]);
-        }
-        std::sort(need.begin(), need.end());
-        need.erase(std::unique(need.begin(), need.end()), need.end());
+        tile_outputs(P, M, t, need);   // out-pairs needed by this tile alone
         int fresh = 0;
         if (chunk >= 0)
             for (int64_t k : need) fresh += stamp[(size_t)k] != chunk;
