@@ -118,8 +118,6 @@ void free_multi(ba_system *s, DevMulti &m) {
     sfree(s, m.partial);
     sfree(s, m.group);
     sfree(s, m.chunk_seg);
-    sfree(s, m.blk_cam);
-    sfree(s, m.cam_blk);
     sfree(s, m.tile_seg);
     sfree(s, m.pair_obs);
     sfree(s, m.pair_grp);
@@ -137,6 +135,12 @@ void free_all(ba_system *s) {
     sfree(s, s->slot_obs);
     sfree(s, s->cam_obs_ptr);
     sfree(s, s->cam_obs);
+    sfree(s, s->cam_slot);
+    sfree(s, s->cam_lmk);
+    sfree(s, s->blk_cam);
+    sfree(s, s->cam_blk);
+    sfree(s, s->blk_order);
+    sfree(s, s->cam_part);
     sfree(s, s->lmk_store);
     sfree(s, s->obs_lm);
     sfree(s, s->h0);
@@ -315,8 +319,8 @@ ba_status ensure_records(ba_system *s, int precision) {
     ba_status st = salloc(s, &m.records[precision], (size_t)s->m * record_words(precision, s->dp) * 4);
     if (st != BA_OK) return st;
     if (!s->ws_counting)
-        launch_pair_records(s->m, precision, s->dp, s->cam_obs, s->obs_slot, tile_stream(s, precision),
-                            m.records[precision], s->stream);
+        launch_pair_records(s->m, precision, s->dp, s->cam_slot, tile_stream(s, precision), m.records[precision],
+                            s->stream);
     HIPCHK(hipGetLastError());
     return BA_OK;
 }
@@ -325,20 +329,11 @@ ba_status ensure_records(ba_system *s, int precision) {
 ba_status make_two_pass(ba_system *s, HostMultiPlan &mp) {
     DevMulti &m = s->multi;
     const HostPlan &P = s->plan;
-    std::vector<int32_t> cam_blk((size_t)s->np + 1, 0), blk_cam;
-    for (int c = 0; c < s->np; ++c) {
-        const int64_t k = P.cam_obs_ptr[(size_t)c + 1] - P.cam_obs_ptr[(size_t)c];
-        const int nb = (int)((k + kPairObs - 1) / kPairObs);
-        cam_blk[(size_t)c + 1] = cam_blk[(size_t)c] + nb;
-        blk_cam.insert(blk_cam.end(), (size_t)nb, c);
-    }
     const size_t slots = (size_t)P.n_tiles * kTile;
     ba_status st;
     if ((st = supload(s, &m.mmeta, mp.mmeta)) != BA_OK) return st;
     if ((st = supload(s, &m.slot_cam, mp.slot_cam)) != BA_OK) return st;
     if ((st = supload(s, &m.pair_ll, mp.pair_ll)) != BA_OK) return st;
-    if ((st = supload(s, &m.cam_blk, cam_blk)) != BA_OK) return st;
-    if ((st = supload(s, &m.blk_cam, blk_cam)) != BA_OK) return st;
     if (!P.cam_seg.empty() && (st = supload(s, &m.tile_seg, P.tile_seg)) != BA_OK) return st;
     std::vector<uint8_t> grp8(slots, 0);
     for (size_t i = 0; i < slots; ++i) grp8[i] = mp.pair_grp[i] < 0 ? 0 : (uint8_t)mp.pair_grp[i];
@@ -346,14 +341,13 @@ ba_status make_two_pass(ba_system *s, HostMultiPlan &mp) {
     if ((st = salloc(s, &m.pair_obs, (size_t)s->m)) != BA_OK) return st;
     if ((st = salloc(s, &m.pair_f, slots * 2)) != BA_OK) return st;
     if ((st = salloc(s, &m.pair_h, slots * 4)) != BA_OK) return st;
-    if ((st = salloc(s, &m.pair_partial, blk_cam.size() * (size_t)(s->dp * mp.N))) != BA_OK) return st;
+    if ((st = salloc(s, &m.pair_partial, P.blk_cam.size() * (size_t)(s->dp * mp.N))) != BA_OK) return st;
     if (!s->ws_counting)
-        launch_pair_obs(s->m, s->cam_obs, s->obs_slot, m.mmeta, m.pair_obs, s->stream);
+        launch_pair_obs(s->m, s->cam_slot, m.mmeta, m.pair_obs, s->stream);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(s->stream));   // the host vectors go out of scope
     m.two_pass = true;
     m.N = mp.N;
-    m.n_blocks = (int)blk_cam.size();
     return BA_OK;
 }
 
@@ -467,9 +461,9 @@ MultiArgs multi_args(ba_system *s, int precision) {
     a.dp = s->dp;
     a.two_pass = s->multi.two_pass;
     a.n_tiles = s->plan.n_tiles;
-    a.n_blocks = s->multi.n_blocks;
-    a.blk_cam = s->multi.blk_cam;
-    a.cam_blk = s->multi.cam_blk;
+    a.n_blocks = (int)s->plan.blk_cam.size();
+    a.blk_cam = s->blk_cam;
+    a.cam_blk = s->cam_blk;
     a.cam_obs_ptr = s->cam_obs_ptr;
     a.tile_seg = s->multi.tile_seg;
     a.records = s->multi.records[precision];
@@ -666,12 +660,36 @@ static BsrGather bsr_gather(const ba_system *s) {
 // and the packed Jacobian stream: V_lambda^-1 and h0 = V_lambda^-1 b_l per landmark,
 // D(S), its factor, the damping of the S product and b~ per camera (eq. (9)-(15)), and
 // the explicit S when the system keeps one.  Waits for the stream.
-static ba_status apply_lambda(ba_system *s) {
+// (r: the caller's residuals, when the lambda-free camera sums are to be formed as well.)
+static ba_status apply_lambda(ba_system *s, const double *r) {
     hipStream_t q = s->stream;
     HIPCHK(hipMemsetAsync(s->status, 0, sizeof(int32_t), q));
     launch_landmarks_lambda(s->nl, s->Vraw, s->bl, s->lambda, s->vinv, s->h0, s->status, q);
-    launch_cameras_lambda(s->np, s->cam_obs_ptr, s->cam_obs, s->obs_lm, s->lmk_store, s->obs_slot, s->J64, s->Uraw,
-                          s->bp, s->vinv, s->h0, s->lambda, s->dU, s->Dblk, s->Dchol, s->bt, s->status, q, s->dp);
+    CameraArgs ca;
+    ca.np = s->np;
+    ca.n_blocks = (int)s->plan.blk_cam.size();
+    ca.blk_cam = s->blk_cam;
+    ca.cam_blk = s->cam_blk;
+    ca.blk_order = s->blk_order;
+    ca.cam_obs_ptr = s->cam_obs_ptr;
+    ca.cam_obs = s->cam_obs;
+    ca.cam_slot = s->cam_slot;
+    ca.cam_lmk = s->cam_lmk;
+    ca.J64 = s->J64;
+    ca.r = r;
+    ca.vinv = s->vinv;
+    ca.h0 = s->h0;
+    ca.lambda = s->lambda;
+    ca.partial = s->cam_part;
+    ca.Uraw = s->Uraw;
+    ca.bp = s->bp;
+    ca.dU = s->dU;
+    ca.Dblk = s->Dblk;
+    ca.Dchol = s->Dchol;
+    ca.bt = s->bt;
+    ca.status = s->status;
+    ca.dp = s->dp;
+    launch_cameras(ca, q);
     if (s->bsr_val) {
         hipEvent_t e0 = nullptr, e1 = nullptr;
         (void)hipEventCreate(&e0);
@@ -717,11 +735,10 @@ static ba_status fill_values(ba_system *s, const double *J_p, const double *J_l,
     launch_pack(s->slot_obs, nslots, J_p, J_l, s->J64, s->J32, s->J16, q, s->dp);
     for (int p = 0; p < 3; ++p)
         if (s->multi.records[p])
-            launch_pair_records(m, p, s->dp, s->cam_obs, s->obs_slot, tile_stream(s, p), s->multi.records[p], q);
+            launch_pair_records(m, p, s->dp, s->cam_slot, tile_stream(s, p), s->multi.records[p], q);
     launch_landmarks_base(s->nl, s->lmk_first_slot, s->lmk_count, s->slot_obs, J_l, r, s->Vraw, s->bl, q);
-    launch_cameras_base(s->np, s->cam_obs_ptr, s->cam_obs, J_p, r, s->Uraw, s->bp, q, s->dp);
     HIPCHK(hipGetLastError());
-    return apply_lambda(s);
+    return apply_lambda(s, r);
 }
 
 static ba_status pcg_buffers(ba_system *s, int max_iter, bool trace);
@@ -830,6 +847,12 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
     if ((st = supload(s, &s->slot_obs, P.slot_obs)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->cam_obs_ptr, P.cam_obs_ptr)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->cam_obs, P.cam_obs)) != BA_OK) return bail(st);
+    if ((st = salloc(s, &s->cam_slot, (size_t)m)) != BA_OK) return bail(st);
+    if ((st = salloc(s, &s->cam_lmk, (size_t)m)) != BA_OK) return bail(st);
+    if ((st = supload(s, &s->blk_cam, P.blk_cam)) != BA_OK) return bail(st);
+    if ((st = supload(s, &s->cam_blk, P.cam_blk)) != BA_OK) return bail(st);
+    if ((st = supload(s, &s->blk_order, P.blk_order)) != BA_OK) return bail(st);
+    if ((st = salloc(s, &s->cam_part, P.blk_cam.size() * (size_t)camera_part(d->d_p))) != BA_OK) return bail(st);
     if ((st = supload(s, &s->lmk_store, P.lmk_store)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->obs_lm, hlm)) != BA_OK) return bail(st);
     if ((st = salloc(s, &s->h0, (size_t)s->nl * 3)) != BA_OK) return bail(st);
@@ -926,6 +949,7 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(q) != hipSuccess)   // host vectors go out of scope
             return bail(fail(BA_ERR_HIP, "explicit S: pattern failed"));
     }
+    if (!counting) launch_cam_slots(m, s->cam_obs, s->obs_slot, s->obs_lm, s->lmk_store, s->cam_slot, s->cam_lmk, q);
     if (!counting && (st = fill_values(s, d->J_p, d->J_l, d->r)) != BA_OK) return bail(st);
     if ((st = ensure_pinned(s)) != BA_OK) return bail(st);
     if ((ws || counting) && (st = reserve_solvers(s, opts)) != BA_OK) return bail(st);
@@ -981,7 +1005,7 @@ ba_status ba_set_lambda(ba_system *s, double lambda) {
     if (!std::isfinite(lambda)) return fail(BA_ERR_NONFINITE, "lambda is not finite");
     if (lambda < 0.0) return fail(BA_ERR_INVALID_ARG, "lambda must be >= 0");
     s->lambda = lambda;
-    return apply_lambda(s);
+    return apply_lambda(s, nullptr);
 }
 
 ba_status ba_profile_enable(ba_system *s, int32_t on) {

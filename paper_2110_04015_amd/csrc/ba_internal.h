@@ -26,6 +26,11 @@ namespace ba {
 constexpr int kTile = 64;          // observation slots per tile (= wavefront width)
 constexpr int kPairs = 12;         // 16-byte component pairs per observation
 constexpr uint32_t kPad = 0xFFFFFFFFu;
+// Observations of one work-group of the camera-major kernels, 64 per wavefront.  In the
+// two-pass multidirectional product 512 and 1024 leave small problems with too few work-groups
+// (80 cameras, 108k observations: FP64 38.8, 43.3 and 54.9 us) and gain nothing on the
+// 571-camera one (174.6, 172.2, 198.2 us).
+constexpr int kCamObs = 256;
 
 // Per-slot metadata word: bits 0..15 chunk-local camera slot, bits 16..21 the
 // landmark's index inside its tile.  Padding slots hold kPad.
@@ -54,7 +59,11 @@ struct HostPlan {
     std::vector<int32_t> cam_part_idx;    // partial rows, camera-major, ascending
     std::vector<int32_t> part_dst;        // partial row -> its position in camera-major order
     std::vector<int64_t> cam_obs_ptr;     // [np + 1]
-    std::vector<int64_t> cam_obs;         // observation indices, camera-major
+    std::vector<int64_t> cam_obs;         // observation indices, camera-major, in slot order
+    // work-groups of the camera-major kernels: up to kCamObs observations of one camera
+    std::vector<int32_t> blk_cam;         // work-group -> camera
+    std::vector<int32_t> cam_blk;         // [np + 1] camera -> its first work-group
+    std::vector<int32_t> blk_order;       // work-groups by their first slot
     std::vector<int32_t> obs_cam;         // host copy of the camera of each observation
     // batches: problem of every camera (nondecreasing), of every tile and of every chunk;
     // tiles and chunks never mix problems.  Empty for a single problem.
@@ -100,8 +109,7 @@ struct DevMulti {
     int32_t *chunk_seg = nullptr;         // batches: chunk -> problem
     // the two-pass form (see MultiArgs)
     bool two_pass = false;
-    int n_blocks = 0;
-    int32_t *blk_cam = nullptr, *cam_blk = nullptr, *tile_seg = nullptr;
+    int32_t *tile_seg = nullptr;
     uint2 *pair_obs = nullptr;
     uint8_t *pair_grp = nullptr;
     double *pair_f = nullptr, *pair_h = nullptr, *pair_partial = nullptr;
@@ -176,6 +184,10 @@ struct ba_system {
     int64_t *slot_obs = nullptr;    // tile slot -> observation (or -1)
     int64_t *cam_obs_ptr = nullptr; // camera -> range of cam_obs
     int64_t *cam_obs = nullptr;     // observations camera by camera
+    uint32_t *cam_slot = nullptr;   // their tile slots
+    int32_t *cam_lmk = nullptr;     // the storage indices of their landmarks
+    int32_t *blk_cam = nullptr, *cam_blk = nullptr, *blk_order = nullptr;   // see HostPlan
+    double *cam_part = nullptr;     // camera sums of the work-groups
     int32_t *lmk_store = nullptr;   // observation -> storage index of its landmark
     int32_t *obs_lm = nullptr;      // copy of the observations' landmarks
     double *h0 = nullptr;           // nl * 3: V^-1 b_l (storage order)

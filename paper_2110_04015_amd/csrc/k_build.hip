@@ -177,150 +177,222 @@ __global__ void k_landmarks_lambda(int nl, const double *__restrict__ Vraw, cons
 
 // ---------------------------------------------------------------- cameras
 
-__device__ __forceinline__ double wave_sum(double v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+__global__ __launch_bounds__(256) void k_cam_slots(int64_t m, const int64_t *__restrict__ cam_obs,
+                                                   const int64_t *__restrict__ obs_slot,
+                                                   const int32_t *__restrict__ obs_lm,
+                                                   const int32_t *__restrict__ lmk_store,
+                                                   uint32_t *__restrict__ cam_slot, int32_t *__restrict__ cam_lmk) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= m) return;
+    const int64_t o = cam_obs[i];
+    cam_slot[i] = (uint32_t)obs_slot[o];
+    cam_lmk[i] = lmk_store[obs_lm[o]];
 }
 
-// One wavefront per camera: the undamped block U = J_p^T J_p (eq. (9), packed upper
-// triangle) and b_p = J_p^T r0 (eq. (11)) over the camera's observations.  Neither
-// depends on lambda.  DP x DP blocks (DP = 9, or 6 for extrinsics only).
+void launch_cam_slots(int64_t m, const int64_t *cam_obs, const int64_t *obs_slot, const int32_t *obs_lm,
+                      const int32_t *lmk_store, uint32_t *cam_slot, int32_t *cam_lmk, hipStream_t s) {
+    hipLaunchKernelGGL(k_cam_slots, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, m, cam_obs, obs_slot, obs_lm,
+                       lmk_store, cam_slot, cam_lmk);
+}
+
+// Sums over a camera's observations, on the FP64 matrix cores:
+//   U = sum J_p^T J_p, b_p = sum J_p^T r0            (eq. (9), (11); independent of lambda)
+//   E = sum W V_lambda^-1 W^T, w = sum W h0, W = J_p^T J_l
+// With the 2 x 2 block B = J_l V_lambda^-1 J_l^T and q = J_l h0 of an observation,
+// E = sum J_p^T B J_p and w = sum J_p^T q, so all four are products of J_p^T with a few
+// columns.  One work-group takes up to kCamObs observations of a camera, 64 per wavefront:
+//   1. lane l loads observation l's record (12 scattered 16-byte words of the tile stream),
+//      V_lambda^-1 and h0, forms B and q and leaves them and J_p in LDS;
+//   2. four observations at a time, v_mfma_f64_16x16x4f64 once per Jacobian row adds
+//      A^T C with A = [J_p | first 16 - DP columns of B J_p] and
+//      C = [J_p | r0 | q | remaining columns of B J_p]: U, b_p, w and E (by its symmetry)
+//      all lie in the one 16 x 16 result.
+// The work-groups run in the order of their first slot, consecutive ones on one XCD, so that
+// the cameras that share tiles read them from its L2 at about the same time.  r0 = 0 when
+// only the lambda-dependent sums are asked for: the others' accumulators do not see it.
+// Lane layouts as in the Gram kernel of the solvers.  Bound by the scattered 16-byte loads
+// (twenty per observation keep the address units busy for three quarters of the time; of the
+// lines read, 1.9 GB come from HBM for 1.0 GB of records).  5.08M observations of 1,936
+// cameras: 506 us, against 354 (U, b_p) + 1,389 us (E, w) with a wavefront per camera and the
+// sums on the vector units; ba_set_lambda 1,420 -> 500 us.  571 cameras of very uneven
+// popularity, 897k observations: an update 6.1 -> 0.45 ms.
+typedef double dbl2_t __attribute__((ext_vector_type(2)));
+typedef double dbl4_t __attribute__((ext_vector_type(4)));
+
 template <int DP>
-__global__ __launch_bounds__(64) void k_cameras_base(int np, const int64_t *__restrict__ cam_ptr,
-                                                     const int64_t *__restrict__ cam_obs,
-                                                     const double *__restrict__ Jp, const double *__restrict__ r,
-                                                     double *__restrict__ Uraw, double *__restrict__ bp) {
-    constexpr int T = DP * (DP + 1) / 2;   // packed upper triangle
-    constexpr int NA = T + DP;
-    int c = blockIdx.x;
-    int lane = threadIdx.x;
-    if (c >= np) return;
-    int64_t a = cam_ptr[c], b = cam_ptr[c + 1];
-    double acc[NA];
-    for (int k = 0; k < NA; ++k) acc[k] = 0.0;
-    for (int64_t q = a + lane; q < b; q += 64) {
-        int64_t o = cam_obs[q];
-        const double *j = Jp + o * 2 * DP;
-        double r0 = r[o * 2], r1 = r[o * 2 + 1];
-        int t = 0;
-        for (int i = 0; i < DP; ++i)
-            for (int k = i; k < DP; ++k) acc[t++] += j[i] * j[k] + j[DP + i] * j[DP + k];
-        for (int i = 0; i < DP; ++i) acc[T + i] += j[i] * r0 + j[DP + i] * r1;
-    }
-    for (int k = 0; k < NA; ++k) {
-        double v = wave_sum(acc[k]);
-        if (lane == 0) {
-            if (k < T) Uraw[(int64_t)c * T + k] = v;
-            else bp[(int64_t)c * DP + (k - T)] = v;
+__global__ __launch_bounds__(256) void k_cameras(CameraArgs a) {
+    typedef RecordShape<DP> R;
+    constexpr int T = DP * (DP + 1) / 2, NA = T + DP;
+    constexpr int RB = 16 - DP < DP ? 16 - DP : DP;   // columns of B J_p that A takes
+    __shared__ __align__(16) double sJ[4][64][2 * DP];
+    __shared__ __align__(16) double sB[4][64][8];     // B00, B01, B11, q0, q1, r0, r1
+    const int lane = threadIdx.x & 63, i = lane & 15, o = lane >> 4;
+    const int w = threadIdx.x >> 6;
+    const int per = (a.n_blocks + 7) / 8;
+    const int at = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+    if (at >= a.n_blocks) return;   // uniform (the grid is a multiple of eight)
+    const int blk = a.blk_order[at];
+    const int c = a.blk_cam[blk];
+    const int64_t b0 = a.cam_obs_ptr[c] + (int64_t)(blk - a.cam_blk[c]) * kCamObs + w * 64;
+    const int cnt = (int)min((int64_t)64, a.cam_obs_ptr[c + 1] - b0);   // may be <= 0
+    if (lane < cnt) {
+        const uint32_t sl = a.cam_slot[b0 + lane];
+        const int64_t l = a.cam_lmk[b0 + lane];
+        const dbl2_t *rec = reinterpret_cast<const dbl2_t *>(a.J64) + (int64_t)(sl / kTile) * R::kW64 * kTile + sl % kTile;
+        dbl2_t x[R::kW64];
+#pragma unroll
+        for (int q = 0; q < R::kW64; ++q) x[q] = rec[q * kTile];
+        const dbl2_t *vp = reinterpret_cast<const dbl2_t *>(a.vinv + l * 6);
+        const dbl2_t v01 = vp[0], v23 = vp[1], v45 = vp[2];
+        const double g0 = a.h0[l * 3], g1 = a.h0[l * 3 + 1], g2 = a.h0[l * 3 + 2];
+        double r0 = 0.0, r1 = 0.0;
+        if (a.r) {
+            struct alignas(8) Pair {
+                double x, y;
+            };
+            const Pair rr = reinterpret_cast<const Pair *>(a.r)[a.cam_obs[b0 + lane]];
+            r0 = rr.x;
+            r1 = rr.y;
         }
+        dbl2_t *dj = reinterpret_cast<dbl2_t *>(sJ[w][lane]);
+#pragma unroll
+        for (int q = 0; q < DP; ++q) dj[q] = x[q];
+        // J_l rows m (x[DP].x, x[DP].y, x[DP+1].x) and k (x[DP+1].y, x[DP+2].x, x[DP+2].y)
+        const double m0 = x[DP].x, m1 = x[DP].y, m2 = x[DP + 1].x;
+        const double k0 = x[DP + 1].y, k1 = x[DP + 2].x, k2 = x[DP + 2].y;
+        const double t0 = v01.x * m0 + v01.y * m1 + v23.x * m2;
+        const double t1 = v01.y * m0 + v23.y * m1 + v45.x * m2;
+        const double t2 = v23.x * m0 + v45.x * m1 + v45.y * m2;
+        const double u0 = v01.x * k0 + v01.y * k1 + v23.x * k2;
+        const double u1 = v01.y * k0 + v23.y * k1 + v45.x * k2;
+        const double u2 = v23.x * k0 + v45.x * k1 + v45.y * k2;
+        double *db = sB[w][lane];
+        db[0] = m0 * t0 + m1 * t1 + m2 * t2;
+        db[1] = k0 * t0 + k1 * t1 + k2 * t2;
+        db[2] = k0 * u0 + k1 * u1 + k2 * u2;
+        db[3] = m0 * g0 + m1 * g1 + m2 * g2;
+        db[4] = k0 * g0 + k1 * g1 + k2 * g2;
+        db[5] = r0;
+        db[6] = r1;
+    } else {   // no observation: zeros
+        for (int k = 0; k < 2 * DP; ++k) sJ[w][lane][k] = 0.0;
+        for (int k = 0; k < 8; ++k) sB[w][lane][k] = 0.0;
+    }
+    __syncthreads();
+    // A: column i of J_p, or column i - DP of B J_p; C: column i of J_p, r0, q, then B J_p
+    const int ka = i < DP ? i : min(i - DP, DP - 1);
+    const int kc = i < DP + 2 ? 0 : min(RB + i - (DP + 2), DP - 1);
+    // (two accumulators, so that the products of a step do not wait for each other)
+    dbl4_t acc = dbl4_t{0.0, 0.0, 0.0, 0.0}, acc1 = acc;
+    for (int j = 0; j < cnt; j += 4) {
+        const double *J = sJ[w][j + o];
+        const double *B = sB[w][j + o];
+        const double b00 = B[0], b01 = B[1], b11 = B[2], q0 = B[3], q1 = B[4], r0 = B[5], r1 = B[6];
+        const double x0 = J[ka], x1 = J[DP + ka], y0 = J[kc], y1 = J[DP + kc];
+        const double A0 = i < DP ? x0 : b00 * x0 + b01 * x1;
+        const double A1 = i < DP ? x1 : b01 * x0 + b11 * x1;
+        const double C0 = i < DP ? x0 : i == DP ? r0 : i == DP + 1 ? q0 : b00 * y0 + b01 * y1;
+        const double C1 = i < DP ? x1 : i == DP ? r1 : i == DP + 1 ? q1 : b01 * y0 + b11 * y1;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A0, C0, acc, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(A1, C1, acc1, 0, 0, 0);
+    }
+    __syncthreads();
+    double (*sh)[16][16] = reinterpret_cast<double (*)[16][16]>(&sJ[0][0][0]);
+    static_assert(sizeof(sJ) >= sizeof(double) * 4 * 256, "room for the wavefronts' results");
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sh[w][o + 4 * e][i] = acc[e] + acc1[e];
+    __syncthreads();
+    // E and w, then U and b_p, each as packed upper triangle and vector
+    const int n = a.r ? 2 * NA : NA;
+    for (int t = threadIdx.x; t < n; t += 256) {
+        int k = t < NA ? t : t - NA, row, col;
+        if (k >= T) {
+            row = k - T;
+            col = t < NA ? DP + 1 : DP;
+        } else {
+            int p = 0;
+            while (k >= DP - p) k -= DP - p++;
+            const int q = p + k;   // entry (p, q), p <= q
+            if (t >= NA) row = p, col = q;
+            else if (p < RB) row = DP + p, col = q;
+            else row = q, col = DP + 2 + (p - RB);
+        }
+        a.partial[(int64_t)blk * (2 * NA) + t] = (sh[0][row][col] + sh[1][row][col]) + (sh[2][row][col] + sh[3][row][col]);
     }
 }
 
-// One wavefront per camera, for the current lambda: E = sum_o W_o V_lambda^-1 W_o^T and
-// w = sum_o W_o h0 with W_o = J_p,o^T J_l,o read back from the packed tile stream (the
-// observation's slot from obs_slot), then
+// One wavefront per camera: adds its work-groups' sums in order (U and b_p are kept), then
 //   D(S)_c = U + lambda diag(U) - E   (diagonal block of eq. (14))
 //   b~_c   = b_p - w                  (eq. (15))
 // the damping lambda diag(U) of the S product, and the Cholesky factor of D(S)_c.
 template <int DP>
-__global__ __launch_bounds__(64) void k_cameras_lambda(int np, const int64_t *__restrict__ cam_ptr,
-                                                       const int64_t *__restrict__ cam_obs,
-                                                       const int32_t *__restrict__ obs_lm,
-                                                       const int32_t *__restrict__ lmk_store,
-                                                       const int64_t *__restrict__ obs_slot,
-                                                       const double *__restrict__ J64,
-                                                       const double *__restrict__ Uraw, const double *__restrict__ bpv,
-                                                       const double *__restrict__ vinv,
-                                                       const double *__restrict__ h0, double lambda,
-                                                       double *__restrict__ dU, double *__restrict__ Dblk,
-                                                       double *__restrict__ Dchol, double *__restrict__ bt,
-                                                       int32_t *status) {
-    typedef RecordShape<DP> R;
-    constexpr int T = DP * (DP + 1) / 2;
-    constexpr int NA = T + DP;
-    int c = blockIdx.x;
-    int lane = threadIdx.x;
-    if (c >= np) return;
-    __shared__ double red[NA];
-    int64_t a = cam_ptr[c], b = cam_ptr[c + 1];
-    const double2 *d2 = reinterpret_cast<const double2 *>(J64);
-    double acc[NA];
-    for (int k = 0; k < NA; ++k) acc[k] = 0.0;
-    for (int64_t q = a + lane; q < b; q += 64) {
-        int64_t o = cam_obs[q];
-        const int64_t sl = obs_slot[o];
-        const int64_t tile = sl / kTile;
-        const int sl_lane = (int)(sl % kTile);
-        double v[2 * R::kW64];
-        for (int w = 0; w < R::kW64; ++w) {
-            const double2 d = d2[(tile * R::kW64 + w) * kTile + sl_lane];
-            v[2 * w] = d.x;
-            v[2 * w + 1] = d.y;
+__global__ __launch_bounds__(64) void k_cameras_finish(CameraArgs a) {
+    constexpr int T = DP * (DP + 1) / 2, NA = T + DP;
+    __shared__ double sE[NA], sU[NA], D[DP][DP], L[DP][DP];
+    const int c = blockIdx.x, lane = threadIdx.x;
+    const int b0 = a.cam_blk[c], b1 = a.cam_blk[c + 1];
+    for (int t = lane; t < (a.r ? 2 * NA : NA); t += 64) {
+        const double *p = a.partial + t;
+        double s = 0.0;
+        for (int b = b0; b < b1; b += 16) {   // sixteen loads in flight, added in order
+            double v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = p[(int64_t)(b + u < b1 ? b + u : b) * (2 * NA)];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                if (b + u < b1) s += v[u];
         }
-        const double *jp = v, *jl = v + 2 * DP;
-        int64_t ls = lmk_store[obs_lm[o]];
-        const double *vi = vinv + ls * 6;
-        const double *hh = h0 + ls * 3;
-        double W[DP * 3];
-        for (int i = 0; i < DP; ++i)
-            for (int k = 0; k < 3; ++k) W[i * 3 + k] = jp[i] * jl[k] + jp[DP + i] * jl[3 + k];
-        double VW[DP * 3];   // (V^-1 W^T)^T = W V^-1, rows i
-        for (int i = 0; i < DP; ++i) {
-            double w0 = W[i * 3], w1 = W[i * 3 + 1], w2 = W[i * 3 + 2];
-            VW[i * 3 + 0] = w0 * vi[0] + w1 * vi[1] + w2 * vi[2];
-            VW[i * 3 + 1] = w0 * vi[1] + w1 * vi[3] + w2 * vi[4];
-            VW[i * 3 + 2] = w0 * vi[2] + w1 * vi[4] + w2 * vi[5];
+        if (t < NA) {
+            sE[t] = s;
+        } else {
+            sU[t - NA] = s;
+            if (t - NA < T) a.Uraw[(int64_t)c * T + t - NA] = s;
+            else a.bp[(int64_t)c * DP + t - NA - T] = s;
         }
-        int t = 0;
-        for (int i = 0; i < DP; ++i)
-            for (int k = i; k < DP; ++k)
-                acc[t++] += VW[i * 3] * W[k * 3] + VW[i * 3 + 1] * W[k * 3 + 1] + VW[i * 3 + 2] * W[k * 3 + 2];
-        for (int i = 0; i < DP; ++i) acc[T + i] += W[i * 3] * hh[0] + W[i * 3 + 1] * hh[1] + W[i * 3 + 2] * hh[2];
     }
-    for (int k = 0; k < NA; ++k) {
-        double v = wave_sum(acc[k]);
-        if (lane == 0) red[k] = v;
+    if (!a.r) {
+        if (lane < T) sU[lane] = a.Uraw[(int64_t)c * T + lane];
+        if (lane < DP) sU[T + lane] = a.bp[(int64_t)c * DP + lane];
     }
     __syncthreads();
-    if (lane != 0) return;
-    const double *U = Uraw + (int64_t)c * T;
-    double D[DP * DP];
-    int t = 0;
-    for (int i = 0; i < DP; ++i) {
-        for (int k = i; k < DP; ++k, ++t) {
-            double u = U[t];
-            if (k == i) u += lambda * U[t];
-            double d = u - red[t];
-            D[i * DP + k] = d;
-            D[k * DP + i] = d;
-        }
+    const auto packed = [](int p, int q) { return p * DP - p * (p - 1) / 2 + q - p; };   // (p, q), p <= q
+    for (int t = lane; t < DP * DP; t += 64) {
+        const int p = t / DP, q = t - p * DP;
+        const int e = p <= q ? packed(p, q) : packed(q, p);
+        double u = sU[e];
+        if (p == q) u += a.lambda * sU[e];
+        D[p][q] = u - sE[e];
+        a.Dblk[(int64_t)c * DP * DP + t] = D[p][q];
     }
-    for (int i = 0; i < DP; ++i) {
-        int diag = i * DP - (i * (i - 1)) / 2;   // index of (i, i) in the packed upper triangle
-        dU[(int64_t)c * DP + i] = lambda * U[diag];
-        bt[(int64_t)c * DP + i] = bpv[(int64_t)c * DP + i] - red[T + i];
+    if (lane < DP) {
+        a.dU[(int64_t)c * DP + lane] = a.lambda * sU[packed(lane, lane)];
+        a.bt[(int64_t)c * DP + lane] = sU[T + lane] - sE[T + lane];
     }
-    for (int k = 0; k < DP * DP; ++k) Dblk[(int64_t)c * DP * DP + k] = D[k];
-    // packed lower Cholesky factor, row i holds L[i][0..i]
-    double L[T];
+    __syncthreads();
+    // Cholesky factor, column by column: lane i > j takes row i
     bool ok = true;
     for (int j = 0; j < DP; ++j) {
-        double d = D[j * DP + j];
-        for (int p = 0; p < j; ++p) d -= L[j * (j + 1) / 2 + p] * L[j * (j + 1) / 2 + p];
+        double d = D[j][j];
+        for (int p = 0; p < j; ++p) d -= L[j][p] * L[j][p];
         if (!(d > 0.0)) {
             ok = false;
             d = 1.0;
         }
         d = sqrt(d);
-        L[j * (j + 1) / 2 + j] = d;
-        for (int i = j + 1; i < DP; ++i) {
-            double s = D[i * DP + j];
-            for (int p = 0; p < j; ++p) s -= L[i * (i + 1) / 2 + p] * L[j * (j + 1) / 2 + p];
-            L[i * (i + 1) / 2 + j] = s / d;
+        if (lane == j) L[j][j] = d;
+        if (lane > j && lane < DP) {
+            double s = D[lane][j];
+            for (int p = 0; p < j; ++p) s -= L[lane][p] * L[j][p];
+            L[lane][j] = s / d;
         }
+        __syncthreads();
     }
-    if (!ok) atomicOr(status, kStatusNotSpdCamera);
-    for (int k = 0; k < T; ++k) Dchol[(int64_t)c * T + k] = L[k];
+    if (!ok && lane == 0) atomicOr(a.status, kStatusNotSpdCamera);
+    if (lane < T) {   // packed lower factor, row p holds L[p][0..p]
+        int p = 0, k = lane;
+        while (k > p) k -= ++p;
+        a.Dchol[(int64_t)c * T + lane] = L[p][k];
+    }
 }
 
 // ---------------------------------------------------------------- launchers
@@ -350,24 +422,15 @@ void launch_landmarks_lambda(int nl, const double *Vraw, const double *bl, doubl
                        status);
 }
 
-void launch_cameras_base(int np, const int64_t *cam_ptr, const int64_t *cam_obs, const double *Jp, const double *r,
-                         double *Uraw, double *bp, hipStream_t s, int dp) {
-    if (dp == 6)
-        hipLaunchKernelGGL(k_cameras_base<6>, dim3(np), dim3(64), 0, s, np, cam_ptr, cam_obs, Jp, r, Uraw, bp);
-    else
-        hipLaunchKernelGGL(k_cameras_base<9>, dim3(np), dim3(64), 0, s, np, cam_ptr, cam_obs, Jp, r, Uraw, bp);
-}
-
-void launch_cameras_lambda(int np, const int64_t *cam_ptr, const int64_t *cam_obs, const int32_t *obs_lm,
-                           const int32_t *lmk_store, const int64_t *obs_slot, const double *J64, const double *Uraw,
-                           const double *bp, const double *vinv, const double *h0, double lambda, double *dU,
-                           double *Dblk, double *Dchol, double *bt, int32_t *status, hipStream_t s, int dp) {
-    if (dp == 6)
-        hipLaunchKernelGGL(k_cameras_lambda<6>, dim3(np), dim3(64), 0, s, np, cam_ptr, cam_obs, obs_lm, lmk_store,
-                           obs_slot, J64, Uraw, bp, vinv, h0, lambda, dU, Dblk, Dchol, bt, status);
-    else
-        hipLaunchKernelGGL(k_cameras_lambda<9>, dim3(np), dim3(64), 0, s, np, cam_ptr, cam_obs, obs_lm, lmk_store,
-                           obs_slot, J64, Uraw, bp, vinv, h0, lambda, dU, Dblk, Dchol, bt, status);
+void launch_cameras(const CameraArgs &a, hipStream_t s) {
+    const dim3 g((unsigned)((a.n_blocks + 7) / 8 * 8));
+    if (a.dp == 6) {
+        hipLaunchKernelGGL(k_cameras<6>, g, dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_cameras_finish<6>, dim3(a.np), dim3(64), 0, s, a);
+    } else {
+        hipLaunchKernelGGL(k_cameras<9>, g, dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_cameras_finish<9>, dim3(a.np), dim3(64), 0, s, a);
+    }
 }
 
 }  // namespace ba

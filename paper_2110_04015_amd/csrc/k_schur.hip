@@ -692,7 +692,7 @@ __global__ __launch_bounds__(256) void k_reduce_multi(int np, int N, const int32
 // go to memory as partials (369 MB).  Here the landmark side and the camera side are split:
 //   k_pair_h (landmark-major tiles): h = V^-1 g per (landmark, subset) and
 //     f = e - J_l h_own per observation, the own subset's term;
-//   k_pair_out (camera-major records): a work-group sums the columns of up to kPairObs
+//   k_pair_out (camera-major records): a work-group sums the columns of up to kCamObs
 //     observations of one camera, sum_o J_p^T ([p = own] f_o - [p != own] J_l h_{l,p});
 //   k_pair_reduce: the work-groups of a camera, in order.
 // Every term is formed as the one-pass form forms it.
@@ -801,8 +801,8 @@ struct PairShare {
 __device__ __forceinline__ PairShare pair_share(const MultiArgs &a, int block, int w) {
     PairShare s;
     s.c = a.blk_cam[block];
-    s.b0 = a.cam_obs_ptr[s.c] + (int64_t)(block - a.cam_blk[s.c]) * kPairObs;
-    const int cnt = (int)min((int64_t)kPairObs, a.cam_obs_ptr[s.c + 1] - s.b0);
+    s.b0 = a.cam_obs_ptr[s.c] + (int64_t)(block - a.cam_blk[s.c]) * kCamObs;
+    const int cnt = (int)min((int64_t)kCamObs, a.cam_obs_ptr[s.c + 1] - s.b0);
     const int per = (cnt + 3) / 4;
     s.lo = min(cnt, w * per);
     s.hi = min(cnt, s.lo + per);
@@ -1073,38 +1073,34 @@ __global__ __launch_bounds__(256) void k_pair_reduce(MultiArgs a, const double *
 
 // Camera-major copy of the tile stream: 16-byte word q of the i-th observation of the
 // camera order goes to word i kw + q (consecutive threads take consecutive words).
-__global__ __launch_bounds__(256) void k_pair_records(int64_t m, int kw, const int64_t *__restrict__ cam_obs,
-                                                      const int64_t *__restrict__ obs_slot,
+__global__ __launch_bounds__(256) void k_pair_records(int64_t m, int kw, const uint32_t *__restrict__ cam_slot,
                                                       const u32x4_t *__restrict__ J, u32x4_t *__restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= m * kw) return;
     const int64_t o = i / kw;
     const int q = (int)(i - o * kw);
-    const int64_t s = obs_slot[cam_obs[o]];
+    const int64_t s = cam_slot[o];
     out[i] = J[(s / kTile * kw + q) * kTile + s % kTile];
 }
 
-void launch_pair_records(int64_t m, int precision, int dp, const int64_t *cam_obs, const int64_t *obs_slot,
-                         const void *J, void *out, hipStream_t s) {
+void launch_pair_records(int64_t m, int precision, int dp, const uint32_t *cam_slot, const void *J, void *out,
+                         hipStream_t s) {
     const int kw = record_words(precision, dp);
-    hipLaunchKernelGGL(k_pair_records, dim3((unsigned)((m * kw + 255) / 256)), dim3(256), 0, s, m, kw, cam_obs,
-                       obs_slot, reinterpret_cast<const u32x4_t *>(J), reinterpret_cast<u32x4_t *>(out));
+    hipLaunchKernelGGL(k_pair_records, dim3((unsigned)((m * kw + 255) / 256)), dim3(256), 0, s, m, kw, cam_slot,
+                       reinterpret_cast<const u32x4_t *>(J), reinterpret_cast<u32x4_t *>(out));
 }
 
 // pair_obs of every observation, in camera order (see k_pair_out).
-__global__ __launch_bounds__(256) void k_pair_obs(int64_t m, const int64_t *__restrict__ cam_obs,
-                                                  const int64_t *__restrict__ obs_slot,
+__global__ __launch_bounds__(256) void k_pair_obs(int64_t m, const uint32_t *__restrict__ cam_slot,
                                                   const uint32_t *__restrict__ mmeta, uint2 *__restrict__ obs) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= m) return;
-    const int64_t s = obs_slot[cam_obs[i]];
-    const uint32_t mm = mmeta[s];
-    obs[i] = make_uint2((uint32_t)(s & ~(int64_t)63) + ((mm >> 8) & 0xFFu), (uint32_t)(s & 63) | ((mm >> 16) & 0xFFu) << 8);
+    const uint32_t s = cam_slot[i], mm = mmeta[s];
+    obs[i] = make_uint2((s & ~63u) + ((mm >> 8) & 0xFFu), (s & 63u) | ((mm >> 16) & 0xFFu) << 8);
 }
 
-void launch_pair_obs(int64_t m, const int64_t *cam_obs, const int64_t *obs_slot, const uint32_t *mmeta, uint2 *obs,
-                     hipStream_t s) {
-    hipLaunchKernelGGL(k_pair_obs, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, m, cam_obs, obs_slot, mmeta, obs);
+void launch_pair_obs(int64_t m, const uint32_t *cam_slot, const uint32_t *mmeta, uint2 *obs, hipStream_t s) {
+    hipLaunchKernelGGL(k_pair_obs, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, m, cam_slot, mmeta, obs);
 }
 
 template <int PREC, typename T, int DP>

@@ -66,19 +66,34 @@ void launch_check_finite(const double *a, int64_t count, int32_t *status, hipStr
 void launch_pack(const int64_t *slot_obs, int64_t nslots, const double *Jp, const double *Jl, double *J64,
                  float *J32, uint16_t *J16, hipStream_t s, int dp = 9);
 void launch_convert(const double *J64, int64_t nslots, float *J32, uint16_t *J16, hipStream_t s, int dp = 9);
-// lambda-independent sums (read the caller's J and r): J_l^T J_l and b_l per landmark,
-// J_p^T J_p (packed upper triangle) and b_p per camera
+// lambda-independent sums per landmark (read the caller's J_l and r): J_l^T J_l and b_l
 void launch_landmarks_base(int nl, const int64_t *first_slot, const int32_t *count, const int64_t *slot_obs,
                            const double *Jl, const double *r, double *Vraw, double *bl, hipStream_t s);
-void launch_cameras_base(int np, const int64_t *cam_ptr, const int64_t *cam_obs, const double *Jp, const double *r,
-                         double *Uraw, double *bp, hipStream_t s, int dp = 9);
 // the values that depend on lambda, from those sums and the packed tile stream
 void launch_landmarks_lambda(int nl, const double *Vraw, const double *bl, double lambda, double *vinv, double *h0,
                              int32_t *status, hipStream_t s);
-void launch_cameras_lambda(int np, const int64_t *cam_ptr, const int64_t *cam_obs, const int32_t *obs_lm,
-                           const int32_t *lmk_store, const int64_t *obs_slot, const double *J64, const double *Uraw,
-                           const double *bp, const double *vinv, const double *h0, double lambda, double *dU,
-                           double *Dblk, double *Dchol, double *bt, int32_t *status, hipStream_t s, int dp = 9);
+// tile slot and landmark storage index of every observation of the camera order
+void launch_cam_slots(int64_t m, const int64_t *cam_obs, const int64_t *obs_slot, const int32_t *obs_lm,
+                      const int32_t *lmk_store, uint32_t *cam_slot, int32_t *cam_lmk, hipStream_t s);
+struct CameraArgs {
+    int np = 0, n_blocks = 0;
+    const int32_t *blk_cam = nullptr, *cam_blk = nullptr, *blk_order = nullptr;   // work-groups (see HostPlan)
+    const int64_t *cam_obs_ptr = nullptr, *cam_obs = nullptr;
+    const uint32_t *cam_slot = nullptr;
+    const int32_t *cam_lmk = nullptr;
+    const double *J64 = nullptr;
+    const double *r = nullptr;        // nullable: the caller's residuals, when J_p^T J_p and b_p are to be formed
+    const double *vinv = nullptr, *h0 = nullptr;
+    double lambda = 0.0;
+    double *partial = nullptr;        // n_blocks * camera_part(dp)
+    double *Uraw = nullptr, *bp = nullptr;   // written when r is given, else read
+    double *dU = nullptr, *Dblk = nullptr, *Dchol = nullptr, *bt = nullptr;
+    int32_t *status = nullptr;
+    int dp = 9;
+};
+// doubles of one work-group's camera sums
+constexpr int camera_part(int dp) { return dp * (dp + 1) + 2 * dp; }
+void launch_cameras(const CameraArgs &a, hipStream_t s);
 
 // ---- Schur products (k_schur.hip)
 struct SchurArgs {
@@ -154,20 +169,15 @@ struct MultiArgs {
     void *pair_f = nullptr, *pair_h = nullptr;  // own terms per slot, h and subset per pair
     double *pair_partial = nullptr;           // n_blocks * dp * N
 };
-// Observations of one work-group of the camera side: 64 per wavefront.  512 and 1024 leave
-// small problems with too few work-groups (80 cameras, 108k observations: FP64 38.8, 43.3 and
-// 54.9 us) and gain nothing on the 571-camera one (174.6, 172.2, 198.2 us).
-constexpr int kPairObs = 256;
 // 16-byte words of a record
 inline int record_words(int precision, int dp) {
     return dp == 6 ? (precision == 0 ? RecordShape<6>::kW64 : precision == 1 ? RecordShape<6>::kW32 : RecordShape<6>::kW16)
                    : (precision == 0 ? RecordShape<9>::kW64 : precision == 1 ? RecordShape<9>::kW32 : RecordShape<9>::kW16);
 }
 // camera-major copy of a tile stream, and the observation words of the camera side
-void launch_pair_records(int64_t m, int precision, int dp, const int64_t *cam_obs, const int64_t *obs_slot,
-                         const void *J, void *out, hipStream_t s);
-void launch_pair_obs(int64_t m, const int64_t *cam_obs, const int64_t *obs_slot, const uint32_t *mmeta, uint2 *obs,
-                     hipStream_t s);
+void launch_pair_records(int64_t m, int precision, int dp, const uint32_t *cam_slot, const void *J, void *out,
+                         hipStream_t s);
+void launch_pair_obs(int64_t m, const uint32_t *cam_slot, const uint32_t *mmeta, uint2 *obs, hipStream_t s);
 // Y[p] = S (z restricted to subset p), Y column-major [N][n]
 void launch_schur_multi(const MultiArgs &a, const double *z, double *Y, hipStream_t s);
 

@@ -226,7 +226,41 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
         P.part_dst.resize((size_t)P.n_part);
         for (int64_t j = 0; j < P.n_part; ++j) P.part_dst[(size_t)P.cam_part_idx[(size_t)j]] = (int32_t)j;
     }
-    counting_csr(cam, m, np, P.cam_obs_ptr, P.cam_obs);
+    // camera-major observations, each camera's in slot order: the work-groups of the cameras
+    // that share a stretch of tiles read it at about the same time
+    P.cam_obs_ptr.assign((size_t)np + 1, 0);
+    for (int64_t o = 0; o < m; ++o) P.cam_obs_ptr[(size_t)cam[o] + 1]++;
+    for (int k = 0; k < np; ++k) P.cam_obs_ptr[(size_t)k + 1] += P.cam_obs_ptr[(size_t)k];
+    P.cam_blk.assign((size_t)np + 1, 0);
+    for (int c = 0; c < np; ++c) {
+        const int64_t k = P.cam_obs_ptr[(size_t)c + 1] - P.cam_obs_ptr[(size_t)c];
+        const int nb = (int)((k + kCamObs - 1) / kCamObs);
+        P.cam_blk[(size_t)c + 1] = P.cam_blk[(size_t)c] + nb;
+        P.blk_cam.insert(P.blk_cam.end(), (size_t)nb, c);
+    }
+    P.cam_obs.resize((size_t)m);
+    std::vector<int64_t> first_slot(P.blk_cam.size());
+    {
+        std::vector<int64_t> fill(P.cam_obs_ptr.begin(), P.cam_obs_ptr.end() - 1);
+        for (int ch = 0; ch < P.n_chunks; ++ch) {
+            const int32_t *cams = P.part_cam.data() + P.chunk_part[(size_t)ch];   // by chunk slot
+            for (int64_t sl = (int64_t)P.chunk_tile[(size_t)ch] * kTile; sl < (int64_t)P.chunk_tile[(size_t)ch + 1] * kTile; ++sl) {
+                const int64_t o = P.slot_obs[(size_t)sl];
+                if (o < 0) continue;
+                const int c = cams[P.meta[(size_t)sl] & 0xFFFFu];
+                const int64_t at = fill[(size_t)c]++;
+                P.cam_obs[(size_t)at] = o;
+                const int64_t k = at - P.cam_obs_ptr[(size_t)c];
+                if (k % kCamObs == 0) first_slot[(size_t)(P.cam_blk[(size_t)c] + k / kCamObs)] = sl;
+            }
+        }
+    }
+    P.blk_order.resize(P.blk_cam.size());
+    for (size_t b = 0; b < P.blk_order.size(); ++b) P.blk_order[b] = (int32_t)b;
+    std::sort(P.blk_order.begin(), P.blk_order.end(), [&](int32_t x, int32_t y) {
+        const int64_t fx = first_slot[(size_t)x], fy = first_slot[(size_t)y];
+        return fx < fy || (fx == fy && x < y);
+    });
     return BA_OK;
 }
 
