@@ -722,21 +722,31 @@ static ba_status apply_lambda(ba_system *s, const double *r) {
 static ba_status fill_values(ba_system *s, const double *J_p, const double *J_l, const double *r) {
     hipStream_t q = s->stream;
     const int64_t m = s->m;
-    const int64_t nslots = s->plan.n_tiles * kTile;
     HIPCHK(hipMemsetAsync(s->status, 0, sizeof(int32_t), q));
-    launch_check_finite(J_p, m * 2 * s->dp, s->status, q);
-    launch_check_finite(J_l, m * 6, s->status, q);
-    launch_check_finite(r, m * 2, s->status, q);
+    launch_check_finite(J_p, J_l, r, m, s->dp, s->status, q);
     int32_t hst = 0;
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(&hst, s->status, 4, hipMemcpyDeviceToHost, q));
     HIPCHK(hipStreamSynchronize(q));
     if (hst & kStatusNonfinite) return fail(BA_ERR_NONFINITE, "NaN or Inf in J_p, J_l or r");
-    launch_pack(s->slot_obs, nslots, J_p, J_l, s->J64, s->J32, s->J16, q, s->dp);
+    PackArgs pa;
+    pa.slot_obs = s->slot_obs;
+    pa.meta = s->meta;
+    pa.tile_lmk_base = s->tile_lmk_base;
+    pa.nslots = s->plan.n_tiles * kTile;
+    pa.Jp = J_p;
+    pa.Jl = J_l;
+    pa.r = r;
+    pa.J64 = s->J64;
+    pa.J32 = s->J32;
+    pa.J16 = s->J16;
+    pa.Vraw = s->Vraw;
+    pa.bl = s->bl;
+    pa.dp = s->dp;
+    launch_pack(pa, q);
     for (int p = 0; p < 3; ++p)
         if (s->multi.records[p])
             launch_pair_records(m, p, s->dp, s->cam_slot, tile_stream(s, p), s->multi.records[p], q);
-    launch_landmarks_base(s->nl, s->lmk_first_slot, s->lmk_count, s->slot_obs, J_l, r, s->Vraw, s->bl, q);
     HIPCHK(hipGetLastError());
     return apply_lambda(s, r);
 }

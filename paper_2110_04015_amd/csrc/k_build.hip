@@ -3,16 +3,37 @@
 // D(S) of Sec. 3.2 (before Algorithm 1), all in FP64.
 #include "ba_internal.h"
 #include "kernels.h"
+#include "dev_la.h"
 
 namespace ba {
 
 // ---------------------------------------------------------------- validation
 
-__global__ void k_check_finite(const double *__restrict__ a, int64_t count, int32_t *status) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    bool bad = false;
-    for (; i < count; i += stride) bad |= !isfinite(a[i]);
+// Two doubles, eight-byte aligned (the caller's arrays need no more)
+struct alignas(8) Dbl2 {
+    double x, y;
+};
+
+// Sets the flag when a value of a (count0), b (count1) or c (count2, all even) is not finite:
+// its exponent bits are all set.  Sixteen-byte loads, eight of a contiguous 32 KiB in flight
+// (1.06 GB just written by k_project: 221 us; with the eight a grid's width apart 251).
+__device__ __forceinline__ bool not_finite(const Dbl2 *__restrict__ a, int64_t n) {
+    uint32_t top = 0;   // the exponent bits of a value that is not finite are the largest
+    for (int64_t i = (int64_t)blockIdx.x * 2048 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 2048) {
+        Dbl2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = a[i + u * 256 < n ? i + u * 256 : i];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            top = max(top, max((uint32_t)__double2hiint(v[u].x) & 0x7FF00000u, (uint32_t)__double2hiint(v[u].y) & 0x7FF00000u));
+    }
+    return top == 0x7FF00000u;
+}
+
+__global__ __launch_bounds__(256) void k_check_finite(const Dbl2 *__restrict__ a, int64_t na, const Dbl2 *__restrict__ b,
+                                                      int64_t nb, const Dbl2 *__restrict__ c, int64_t nc,
+                                                      int32_t *status) {
+    const bool bad = not_finite(a, na) | not_finite(b, nb) | not_finite(c, nc);
     if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(status, kStatusNonfinite);
 }
 
@@ -53,23 +74,64 @@ __device__ __forceinline__ void write_record(const double *v, int64_t tile, int 
 }
 
 // One thread per tile slot: gathers the observation's 2 x DP and 2 x 3 blocks and
-// writes them in the component-pair-major tile layout (plus FP32 / BF16 copies).
+// writes them in the tile layout (plus FP32 / BF16 copies).  A wavefront is a tile, so it
+// also leaves its landmarks' sums that do not depend on lambda, as segmented sums across
+// their lanes: J_l^T J_l (eq. (10), six entries: 00 01 02 11 12 22) and b_l = J_l^T r0
+// (eq. (12)).  5.08M observations, 2.1 GB read and written: 437 us (4.9 TB/s, above a device
+// copy's 4.4), against 390 us for the packing alone and 294 us for a kernel of a thread per
+// landmark that read J_l and r once more.
 template <int DP>
-__global__ void k_pack(const int64_t *__restrict__ slot_obs, int64_t nslots, const double *__restrict__ Jp,
-                       const double *__restrict__ Jl, double *__restrict__ J64, float *__restrict__ J32,
-                       uint16_t *__restrict__ J16) {
+__global__ __launch_bounds__(256) void k_pack(const int64_t *__restrict__ slot_obs, const uint32_t *__restrict__ meta,
+                                              const int32_t *__restrict__ tile_lmk_base, int64_t nslots,
+                                              const double *__restrict__ Jp, const double *__restrict__ Jl,
+                                              const double *__restrict__ r, double *__restrict__ J64,
+                                              float *__restrict__ J32, uint16_t *__restrict__ J16,
+                                              double *__restrict__ Vraw, double *__restrict__ bl) {
     constexpr int NV = RecordShape<DP>::kVals;
-    int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= nslots) return;
-    int64_t o = slot_obs[s];
-    double v[NV];
+    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (s >= nslots) return;   // whole wavefronts
+    const int lane = threadIdx.x & 63;
+    const int64_t o = slot_obs[s], tile = s / kTile;
+    const uint32_t mt = meta[s];
+    double v[NV], r0 = 0.0, r1 = 0.0;
     if (o >= 0) {
-        for (int k = 0; k < 2 * DP; ++k) v[k] = Jp[o * 2 * DP + k];
-        for (int k = 0; k < 6; ++k) v[2 * DP + k] = Jl[o * 6 + k];
+        const Dbl2 *p = reinterpret_cast<const Dbl2 *>(Jp + o * 2 * DP), *l = reinterpret_cast<const Dbl2 *>(Jl + o * 6);
+#pragma unroll
+        for (int k = 0; k < DP; ++k) {
+            const Dbl2 d = p[k];
+            v[2 * k] = d.x;
+            v[2 * k + 1] = d.y;
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const Dbl2 d = l[k];
+            v[2 * DP + 2 * k] = d.x;
+            v[2 * DP + 2 * k + 1] = d.y;
+        }
+        const Dbl2 d = reinterpret_cast<const Dbl2 *>(r)[o];
+        r0 = d.x;
+        r1 = d.y;
     } else {
+#pragma unroll
         for (int k = 0; k < NV; ++k) v[k] = 0.0;
     }
-    write_record<DP>(v, s / kTile, (int)(s % kTile), J64, J32, J16);
+    write_record<DP>(v, tile, lane, J64, J32, J16);
+    const int ll = (int)((mt >> 16) & 63u);
+    const Segs sg = key_segments(mt != kPad ? ll : 64 + lane, lane);
+    const double *a = v + 2 * DP, *b = a + 3;   // J_l rows 0 and 1
+    const double x[9] = {a[0] * a[0] + b[0] * b[0], a[0] * a[1] + b[0] * b[1], a[0] * a[2] + b[0] * b[2],
+                         a[1] * a[1] + b[1] * b[1], a[1] * a[2] + b[1] * b[2], a[2] * a[2] + b[2] * b[2],
+                         a[0] * r0 + b[0] * r1,     a[1] * r0 + b[1] * r1,     a[2] * r0 + b[2] * r1};
+    double t[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) t[k] = segment_scan(x[k], sg);
+    if (mt != kPad && sg.end == lane) {
+        const int64_t l = tile_lmk_base[tile] + ll;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) Vraw[l * 6 + k] = t[k];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) bl[l * 3 + k] = t[6 + k];
+    }
 }
 
 // Lower-precision copies of an existing FP64 tile stream (one thread per slot).
@@ -99,36 +161,6 @@ void launch_convert(const double *J64, int64_t nslots, float *J32, uint16_t *J16
 }
 
 // ---------------------------------------------------------------- landmarks
-
-// One thread per landmark (storage order): the undamped block J_l^T J_l of eq. (10)
-// (symmetric, 6 entries: 00 01 02 11 12 22) and b_l = J_l^T r0 (eq. (12)).  Neither
-// depends on lambda, so a new lambda re-uses them.
-__global__ void k_landmarks_base(int nl, const int64_t *__restrict__ first_slot, const int32_t *__restrict__ count,
-                                 const int64_t *__restrict__ slot_obs, const double *__restrict__ Jl,
-                                 const double *__restrict__ r, double *__restrict__ Vraw, double *__restrict__ bl) {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= nl) return;
-    double V[6] = {0, 0, 0, 0, 0, 0};
-    double b[3] = {0, 0, 0};
-    int64_t f = first_slot[s];
-    int c = count[s];
-    for (int q = 0; q < c; ++q) {
-        int64_t o = slot_obs[f + q];
-        const double *j = Jl + o * 6;
-        double r0 = r[o * 2], r1 = r[o * 2 + 1];
-        V[0] += j[0] * j[0] + j[3] * j[3];
-        V[1] += j[0] * j[1] + j[3] * j[4];
-        V[2] += j[0] * j[2] + j[3] * j[5];
-        V[3] += j[1] * j[1] + j[4] * j[4];
-        V[4] += j[1] * j[2] + j[4] * j[5];
-        V[5] += j[2] * j[2] + j[5] * j[5];
-        b[0] += j[0] * r0 + j[3] * r1;
-        b[1] += j[1] * r0 + j[4] * r1;
-        b[2] += j[2] * r0 + j[5] * r1;
-    }
-    for (int k = 0; k < 6; ++k) Vraw[(int64_t)s * 6 + k] = V[k];
-    for (int k = 0; k < 3; ++k) bl[(int64_t)s * 3 + k] = b[k];
-}
 
 // One thread per landmark: V_lambda = V + lambda diag(V) (eq. (10) with Marquardt
 // damping), V_lambda^-1 (symmetric, 6 entries) by its 3x3 Cholesky factor, and
@@ -247,10 +279,7 @@ __global__ __launch_bounds__(256) void k_cameras(CameraArgs a) {
         const double g0 = a.h0[l * 3], g1 = a.h0[l * 3 + 1], g2 = a.h0[l * 3 + 2];
         double r0 = 0.0, r1 = 0.0;
         if (a.r) {
-            struct alignas(8) Pair {
-                double x, y;
-            };
-            const Pair rr = reinterpret_cast<const Pair *>(a.r)[a.cam_obs[b0 + lane]];
+            const Dbl2 rr = reinterpret_cast<const Dbl2 *>(a.r)[a.cam_obs[b0 + lane]];
             r0 = rr.x;
             r1 = rr.y;
         }
@@ -397,23 +426,22 @@ __global__ __launch_bounds__(64) void k_cameras_finish(CameraArgs a) {
 
 // ---------------------------------------------------------------- launchers
 
-void launch_check_finite(const double *a, int64_t count, int32_t *status, hipStream_t s) {
-    if (count <= 0) return;
-    int blocks = (int)std::min<int64_t>((count + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_check_finite, dim3(blocks), dim3(256), 0, s, a, count, status);
+void launch_check_finite(const double *Jp, const double *Jl, const double *r, int64_t m, int dp, int32_t *status,
+                         hipStream_t s) {
+    const int64_t na = m * dp;
+    const int blocks = (int)std::min<int64_t>((na + 2047) / 2048, 2048);
+    hipLaunchKernelGGL(k_check_finite, dim3(blocks), dim3(256), 0, s, reinterpret_cast<const Dbl2 *>(Jp), na,
+                       reinterpret_cast<const Dbl2 *>(Jl), m * 3, reinterpret_cast<const Dbl2 *>(r), m, status);
 }
 
-void launch_pack(const int64_t *slot_obs, int64_t nslots, const double *Jp, const double *Jl, double *J64,
-                 float *J32, uint16_t *J16, hipStream_t s, int dp) {
-    const dim3 g((unsigned)((nslots + 255) / 256));
-    if (dp == 6) hipLaunchKernelGGL(k_pack<6>, g, dim3(256), 0, s, slot_obs, nslots, Jp, Jl, J64, J32, J16);
-    else hipLaunchKernelGGL(k_pack<9>, g, dim3(256), 0, s, slot_obs, nslots, Jp, Jl, J64, J32, J16);
-}
-
-void launch_landmarks_base(int nl, const int64_t *first_slot, const int32_t *count, const int64_t *slot_obs,
-                           const double *Jl, const double *r, double *Vraw, double *bl, hipStream_t s) {
-    hipLaunchKernelGGL(k_landmarks_base, dim3((nl + 255) / 256), dim3(256), 0, s, nl, first_slot, count, slot_obs, Jl,
-                       r, Vraw, bl);
+void launch_pack(const PackArgs &a, hipStream_t s) {
+    const dim3 g((unsigned)((a.nslots + 255) / 256));
+    if (a.dp == 6)
+        hipLaunchKernelGGL(k_pack<6>, g, dim3(256), 0, s, a.slot_obs, a.meta, a.tile_lmk_base, a.nslots, a.Jp, a.Jl, a.r,
+                           a.J64, a.J32, a.J16, a.Vraw, a.bl);
+    else
+        hipLaunchKernelGGL(k_pack<9>, g, dim3(256), 0, s, a.slot_obs, a.meta, a.tile_lmk_base, a.nslots, a.Jp, a.Jl, a.r,
+                           a.J64, a.J32, a.J16, a.Vraw, a.bl);
 }
 
 void launch_landmarks_lambda(int nl, const double *Vraw, const double *bl, double lambda, double *vinv, double *h0,

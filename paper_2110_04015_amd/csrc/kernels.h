@@ -62,13 +62,25 @@ struct RecordShape {
 };
 
 // ---- build (k_build.hip); dp = pose dimension (9 or 6)
-void launch_check_finite(const double *a, int64_t count, int32_t *status, hipStream_t s);
-void launch_pack(const int64_t *slot_obs, int64_t nslots, const double *Jp, const double *Jl, double *J64,
-                 float *J32, uint16_t *J16, hipStream_t s, int dp = 9);
+// flags a NaN or Inf in the m observations' J_p, J_l and r
+void launch_check_finite(const double *Jp, const double *Jl, const double *r, int64_t m, int dp, int32_t *status,
+                         hipStream_t s);
+// the tile stream (and its lower-precision copies, when set) and the landmarks'
+// lambda-independent sums J_l^T J_l and b_l, from the caller's J and r
+struct PackArgs {
+    const int64_t *slot_obs = nullptr;
+    const uint32_t *meta = nullptr;
+    const int32_t *tile_lmk_base = nullptr;
+    int64_t nslots = 0;
+    const double *Jp = nullptr, *Jl = nullptr, *r = nullptr;
+    double *J64 = nullptr;
+    float *J32 = nullptr;
+    uint16_t *J16 = nullptr;
+    double *Vraw = nullptr, *bl = nullptr;
+    int dp = 9;
+};
+void launch_pack(const PackArgs &a, hipStream_t s);
 void launch_convert(const double *J64, int64_t nslots, float *J32, uint16_t *J16, hipStream_t s, int dp = 9);
-// lambda-independent sums per landmark (read the caller's J_l and r): J_l^T J_l and b_l
-void launch_landmarks_base(int nl, const int64_t *first_slot, const int32_t *count, const int64_t *slot_obs,
-                           const double *Jl, const double *r, double *Vraw, double *bl, hipStream_t s);
 // the values that depend on lambda, from those sums and the packed tile stream
 void launch_landmarks_lambda(int nl, const double *Vraw, const double *bl, double lambda, double *vinv, double *h0,
                              int32_t *status, hipStream_t s);
