@@ -1261,10 +1261,19 @@ static ba_status pcg_core(ba_system *s, const double *bt, bool report_true, cons
         // only once per batch.
         double *trace_dev = want_trace ? s->trace_buf : nullptr;
         const bool lowrank = opts.precond == 1;
-        launch_precond(s->np, s->Dchol, r, P, q, s->dp);
-        if (lowrank) launch_lowrank_apply(n, s->Ulr, r, P, nullptr, s->lr_proj, nullptr, nullptr, q);
         SchurArgs sa = schur_args(s, prec);
         sa.done = sc + SC_DONE;
+        // With the block-Jacobi preconditioner the implicit product forms P_{i+1} = Z - beta P_i
+        // itself (P_0 = Z: beta is 0 at first); the explicit product and the learned term take it
+        // from launch_pcg_update_p.
+        const bool forms_p = !lowrank && !use_bsr(s, sa);
+        if (forms_p) {
+            HIPCHK(hipMemsetAsync(P, 0, (size_t)n * sizeof(double), q));
+            sa.z = z;
+            sa.beta = sc + SC_BETA;
+        }
+        launch_precond(s->np, s->Dchol, r, forms_p ? z : P, q, s->dp);
+        if (lowrank) launch_lowrank_apply(n, s->Ulr, r, P, nullptr, s->lr_proj, nullptr, nullptr, q);
         // Delta_i and gamma_i from the camera reduction of Q_i = S P_i (or from the
         // explicit-S product, which leaves the same partials)
         sa.gram = pg;
@@ -1283,7 +1292,7 @@ static ba_status pcg_core(ba_system *s, const double *bt, bool report_true, cons
                     // alpha_i, x_{i+1}, r_{i+1}, the stop test, Z_{i+1}, Phi_i and beta_i
                     launch_pcg_xrz(s->np, dq, ndq, sc, x, r, P, Q, s->Dchol, z, pxz, s->tickets, opts.eps,
                                    opts.max_iter, trace_dev, q, s->dp);
-                    launch_pcg_update_p(n, nullptr, sc, z, P, q);            // P_{i+1}
+                    if (!forms_p) launch_pcg_update_p(n, nullptr, sc, z, P, q);   // P_{i+1}
                 } else {                                                     // M^-1 = D^-1 + U U^T
                     launch_pcg_update_xr(n, dq, ndq, sc, x, r, P, Q, prr, q);
                     launch_pcg_step_end(prr, sc, opts.eps, opts.max_iter, trace_dev, q);

@@ -23,6 +23,23 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
     return r;
 }
 
+// block_sum of two values with one barrier: the sums are added in block_sum's order (halves of
+// the block, then of the wavefront) by the first wavefront, whose lanes alone hold them.
+__device__ __forceinline__ void block_sum_first(double &u, double &v, double (*sh)[kNT]) {
+    const int t = threadIdx.x;
+    sh[0][t] = u;
+    sh[1][t] = v;
+    __syncthreads();
+    if (t >= 64) return;
+    u = (sh[0][t] + sh[0][t + 128]) + (sh[0][t + 64] + sh[0][t + 192]);
+    v = (sh[1][t] + sh[1][t + 128]) + (sh[1][t + 64] + sh[1][t + 192]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        u += __shfl_xor(u, o, 64);
+        v += __shfl_xor(v, o, 64);
+    }
+}
+
 // Sum over the lanes of a wavefront by a fixed butterfly.  Partners add the same two
 // values (in swapped order, which is exact), so every lane ends with the same sum,
 // independent of scheduling.
@@ -98,6 +115,37 @@ __device__ __forceinline__ void chol_solve_packed(const double *__restrict__ L, 
 #pragma unroll
         for (int p = i + 1; p < DP; ++p) s -= L[p * (p + 1) / 2 + i] * x[p];
         x[i] = s / L[i * (i + 1) / 2 + i];
+    }
+#pragma unroll
+    for (int i = 0; i < DP; ++i) z[i] = x[i];
+}
+
+// s / d from y = 1 / d (correctly rounded): the quotient's remainder is exact in an FMA, so one
+// correction rounds it as the division does, in three dependent operations instead of a
+// division's ten or so.
+__device__ __forceinline__ double div_with(double s, double d, double y) {
+    const double q = s * y;
+    return fma(fma(-q, d, s), y, q);
+}
+
+// chol_solve_packed with the reciprocals y of the factor's diagonal at hand (formed while
+// something else is waited for): the 2 DP quotients are the solve's serial chain.
+template <int DP>
+__device__ __forceinline__ void chol_solve_recip(const double *L, const double *y, const double *r, double *z) {
+    double x[DP];
+#pragma unroll
+    for (int i = 0; i < DP; ++i) {
+        double s = r[i];
+#pragma unroll
+        for (int p = 0; p < i; ++p) s -= L[i * (i + 1) / 2 + p] * x[p];
+        x[i] = div_with(s, L[i * (i + 1) / 2 + i], y[i]);
+    }
+#pragma unroll
+    for (int i = DP - 1; i >= 0; --i) {
+        double s = x[i];
+#pragma unroll
+        for (int p = i + 1; p < DP; ++p) s -= L[p * (p + 1) / 2 + i] * x[p];
+        x[i] = div_with(s, L[i * (i + 1) / 2 + i], y[i]);
     }
 #pragma unroll
     for (int i = 0; i < DP; ++i) z[i] = x[i];

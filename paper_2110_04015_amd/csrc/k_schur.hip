@@ -246,14 +246,18 @@ __device__ __forceinline__ void process_tile(const TileBuf<PREC, T, DP> &b, int 
     }
 }
 
+// P_{i+1} = Z - beta P_i (Alg. 1), rounded alike wherever it is formed
+__device__ __forceinline__ double next_direction(double z, double beta, double p) { return fma(-beta, p, z); }
+
 // Software pipeline over the tiles of the chunk with two buffers: the record and
 // V^-1 of tile t + 1 and the slot word of tile t + 2 are requested before tile t
 // is processed, so a wavefront keeps up to two tiles of the stream in flight.
 template <int PREC, typename T, int DP>
 __global__ __launch_bounds__(64) void k_schur1(SchurArgs a, const double *__restrict__ v) {
-    if (a.done && *a.done != 0.0) return;
     if (a.seg_skip && a.seg_skip[a.chunk_seg[blockIdx.x]]) return;
     extern __shared__ __align__(16) unsigned char smem[];
+    // (the flag and beta are requested with the chunk's bounds)
+    const double done = a.done ? *a.done : 0.0, beta = a.z ? *a.beta : 0.0;
     double *yloc = reinterpret_cast<double *>(smem);
     double *gloc = yloc + a.max_slots * DP;                                   // FP64: landmark rows
     T *vloc = reinterpret_cast<T *>(gloc + (PREC == 0 ? 3 * kTile : 0));
@@ -264,6 +268,7 @@ __global__ __launch_bounds__(64) void k_schur1(SchurArgs a, const double *__rest
     const int t0 = a.chunk_tile[chunk], t1 = a.chunk_tile[chunk + 1];
     const uint32_t *meta = a.meta + lane;
     const int tl = t1 - 1;   // slot words past the chunk's end are read from its last tile
+    if (done != 0.0) return;
     TileBuf<PREC, T, DP> A, B;
     uint32_t mA, mB = 0;
     if (t0 < t1) {
@@ -271,7 +276,8 @@ __global__ __launch_bounds__(64) void k_schur1(SchurArgs a, const double *__rest
         mB = meta[(int64_t)min(t0 + 1, tl) * kTile];
     }
     for (int i = lane; i < ns * DP; i += kTile) {
-        vloc[i] = (T)v[(int64_t)a.part_cam[pb + i / DP] * DP + i % DP];
+        const int64_t k = (int64_t)a.part_cam[pb + i / DP] * DP + i % DP;
+        vloc[i] = (T)(a.z ? next_direction(a.z[k], beta, v[k]) : v[k]);
         yloc[i] = 0.0;
     }
     wave_sync();
@@ -342,11 +348,14 @@ __device__ __forceinline__ double wave_rows(const double *__restrict__ rows, int
 // four cameras (the Gram products Q^T P and P^T r of a one-column block, Q = S P).
 // The skip flag, the camera's row range and its entries of v, diag(U) and gr are
 // requested together, before anything waits on one of them (a wavefront past the last
-// camera reads the last camera's and drops them).
+// camera reads the last camera's and drops them).  With z (PCG) the product's vector is
+// z - beta v, which every chunk formed for its cameras and this kernel, after all of them,
+// stores in v: a launch less per iteration (571 cameras and fewer: 2 us and the gap of one).
 template <int DP>
 __global__ __launch_bounds__(256) void k_reduce1(int np, const int32_t *__restrict__ ptr,
                                                  const double *__restrict__ partial,
-                                                 const double *__restrict__ dU, const double *__restrict__ v,
+                                                 const double *__restrict__ dU, double *__restrict__ v,
+                                                 const double *__restrict__ z, const double *__restrict__ beta,
                                                  double *__restrict__ y, const double *__restrict__ done,
                                                  const int32_t *__restrict__ cam_seg,
                                                  const int32_t *__restrict__ seg_skip, double *__restrict__ gram,
@@ -359,15 +368,18 @@ __global__ __launch_bounds__(256) void k_reduce1(int np, const int32_t *__restri
     const int64_t i = (int64_t)cl * DP + (lane < DP ? lane : 0);
     const double dn = done ? *done : 0.0;
     const int32_t ra = ptr[cl], rb = ptr[cl + 1];
-    const double vi = v[i], du = dU[i];
+    double vi = v[i];
+    const double du = dU[i], zi = z ? z[i] : 0.0, be = z ? *beta : 0.0;
     const double gi = gram ? gr[i] : 0.0;
     if (dn != 0.0) return;
+    if (z) vi = next_direction(zi, be, vi);
     double qp = 0.0, pr = 0.0;
     if (c < np && !(seg_skip && seg_skip[cam_seg[c]])) {   // uniform per wavefront
         const double t = wave_rows<DP>(partial, ra, rb, sh[w]);
         if (lane < DP) {
             const double yi = du * vi + t;
             y[i] = yi;
+            if (z) v[i] = vi;
             if (y32) y32[i] = (float)yi;
             if (gram) {
                 qp = yi * vi;
@@ -416,12 +428,13 @@ int schur_gram_blocks(int np) { return (np + 3) / 4; }
 
 void launch_schur_reduce(const SchurArgs &a, const double *v, double *y, hipStream_t s) {
     const dim3 g((unsigned)schur_gram_blocks(a.np)), b(256);
+    double *vw = const_cast<double *>(v);   // written with a.z only (then the caller's own vector)
     if (a.dp == 6)
-        hipLaunchKernelGGL(k_reduce1<6>, g, b, 0, s, a.np, a.cam_part_ptr, a.partial, a.dU, v, y, a.done, a.cam_seg,
-                           a.seg_skip, a.gram, a.gram_r, a.y32);
+        hipLaunchKernelGGL(k_reduce1<6>, g, b, 0, s, a.np, a.cam_part_ptr, a.partial, a.dU, vw, a.z, a.beta, y, a.done,
+                           a.cam_seg, a.seg_skip, a.gram, a.gram_r, a.y32);
     else
-        hipLaunchKernelGGL(k_reduce1<9>, g, b, 0, s, a.np, a.cam_part_ptr, a.partial, a.dU, v, y, a.done, a.cam_seg,
-                           a.seg_skip, a.gram, a.gram_r, a.y32);
+        hipLaunchKernelGGL(k_reduce1<9>, g, b, 0, s, a.np, a.cam_part_ptr, a.partial, a.dU, vw, a.z, a.beta, y, a.done,
+                           a.cam_seg, a.seg_skip, a.gram, a.gram_r, a.y32);
 }
 
 void launch_schur_matvec(const SchurArgs &a, const double *v, double *y, hipStream_t s) {

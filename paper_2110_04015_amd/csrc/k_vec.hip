@@ -237,11 +237,10 @@ __global__ __launch_bounds__(kNT) void k_pcg_xrz(int np, const double *__restric
                                                  double *__restrict__ z, double *__restrict__ partials,
                                                  uint32_t *__restrict__ ticket, double eps, int max_iter,
                                                  double *__restrict__ trace) {
-    if (sc[SC_DONE] != 0.0) return;
     constexpr int CB = kNT / DP;
     constexpr int NL = DP * (DP + 1) / 2;
     __shared__ double sr[CB * DP], sq[CB * DP];
-    __shared__ double sh[kNT];
+    __shared__ double sh[2][kNT];
     __shared__ double s_alpha;
     __shared__ int last;
     const int c0 = blockIdx.x * CB;
@@ -250,14 +249,17 @@ __global__ __launch_bounds__(kNT) void k_pcg_xrz(int np, const double *__restric
     const bool row = t < cams * DP;
     const int64_t i = (int64_t)c0 * DP + (row ? t : 0);
     const double xi = x[i], ri = r[i], pi = P[i], qi = Q[i];
+    const double done = sc[SC_DONE], iter = sc[SC_ITER], rr0 = sc[SC_RR0];
     double Lc[NL];
     {
         const double *Lp = Dchol + (int64_t)(c0 + (t < cams ? t : 0)) * NL;
 #pragma unroll
         for (int e = 0; e < NL; ++e) Lc[e] = Lp[e];
     }
+    double D = 0.0;
+    if (done != 0.0) return;   // uniform
     if (t < 64) {
-        double D, g;
+        double g;
         wave_pair_sums(pdq, npdq, D, g);
         const double al = D > 0.0 ? g / D : 0.0;
         if (t == 0) {
@@ -270,6 +272,9 @@ __global__ __launch_bounds__(kNT) void k_pcg_xrz(int np, const double *__restric
             }
         }
     }
+    double yd[DP];   // reciprocals of the factor's diagonal, while the sums are waited for
+#pragma unroll
+    for (int e = 0; e < DP; ++e) yd[e] = 1.0 / Lc[e * (e + 1) / 2 + e];
     __syncthreads();
     const double al = s_alpha;
     double rr = 0.0;
@@ -287,15 +292,14 @@ __global__ __launch_bounds__(kNT) void k_pcg_xrz(int np, const double *__restric
         double rc[DP], zc[DP];
 #pragma unroll
         for (int e = 0; e < DP; ++e) rc[e] = sr[t * DP + e];
-        chol_solve_packed<DP>(Lc, rc, zc);
+        chol_solve_recip<DP>(Lc, yd, rc, zc);
 #pragma unroll
         for (int e = 0; e < DP; ++e) {
             z[(int64_t)(c0 + t) * DP + e] = zc[e];
             phi += sq[t * DP + e] * zc[e];
         }
     }
-    rr = block_sum(rr, sh);
-    phi = block_sum(phi, sh);
+    block_sum_first(rr, phi, sh);
     if (t == 0) {
         partials[2 * blockIdx.x] = rr;
         partials[2 * blockIdx.x + 1] = phi;
@@ -309,15 +313,14 @@ __global__ __launch_bounds__(kNT) void k_pcg_xrz(int np, const double *__restric
     wave_pair_sums(partials, gridDim.x, srr, sphi);
     if (t != 0) return;
     __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (sc[SC_BREAK] != 0.0) {
+    if (!(D > 0.0)) {   // every block formed the same Delta
         sc[SC_DONE] = 1.0;
         sc[SC_STATUS] = (double)BA_ERR_BREAKDOWN;
         return;
     }
-    const double it = sc[SC_ITER] + 1.0;
+    const double it = iter + 1.0;
     sc[SC_ITER] = it;
     sc[SC_RR] = srr;
-    const double rr0 = sc[SC_RR0];
     if (trace) trace[(int)it - 1] = sqrt(srr / rr0);
     if (sqrt(srr) < eps * sqrt(rr0)) {
         sc[SC_DONE] = 1.0;
@@ -327,7 +330,7 @@ __global__ __launch_bounds__(kNT) void k_pcg_xrz(int np, const double *__restric
         sc[SC_STATUS] = (double)BA_MAXITER;
     } else {
         sc[SC_PHI] = sphi;
-        sc[SC_BETA] = sphi / sc[SC_DELTA];
+        sc[SC_BETA] = sphi / D;
     }
 }
 
@@ -684,7 +687,7 @@ __global__ __launch_bounds__(kNT) void k_mcg_xrz(int np, int k, const double *__
     constexpr int CB = kNT / DP;
     constexpr int NL = DP * (DP + 1) / 2;
     __shared__ double sr[CB * DP];
-    __shared__ double sh[kNT];
+    __shared__ double sh[2][kNT];
     __shared__ double al[kMaxK], ga_sh[kMaxK];
     __shared__ double rank_sh;
     __shared__ double ush[4 * kLowRank];
@@ -742,6 +745,9 @@ __global__ __launch_bounds__(kNT) void k_mcg_xrz(int np, int k, const double *__
         }
         if (t == SC_RANK) rank_sh = scv;
     }
+    double yd[DP];   // reciprocals of the factor's diagonal, while the sums are waited for
+#pragma unroll
+    for (int e = 0; e < DP; ++e) yd[e] = 1.0 / Lc[e * (e + 1) / 2 + e];
     __syncthreads();
     double rr = 0.0, rv = 0.0;
     if (row) {
@@ -786,15 +792,14 @@ __global__ __launch_bounds__(kNT) void k_mcg_xrz(int np, int k, const double *__
         double rc[DP], zc[DP];
 #pragma unroll
         for (int e = 0; e < DP; ++e) rc[e] = sr[t * DP + e];
-        chol_solve_packed<DP>(Lc, rc, zc);
+        chol_solve_recip<DP>(Lc, yd, rc, zc);
 #pragma unroll
         for (int e = 0; e < DP; ++e) {
             z[(int64_t)(c0 + t) * DP + e] = zc[e];
             rho += rc[e] * zc[e];
         }
     }
-    rr = block_sum(rr, sh);
-    rho = block_sum(rho, sh);
+    block_sum_first(rr, rho, sh);
     if (t == 0) {
         partials[2 * blockIdx.x] = rr;
         partials[2 * blockIdx.x + 1] = rho;

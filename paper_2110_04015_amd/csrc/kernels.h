@@ -129,6 +129,8 @@ struct SchurArgs {
     // y^T v and v^T gram_r, gram[2 b], gram[2 b + 1] for b < schur_gram_blocks(np)
     double *gram = nullptr;
     const double *gram_r = nullptr;
+    // nullable, single systems only: the product's vector is z - *beta v, and v becomes it
+    const double *z = nullptr, *beta = nullptr;
     // nullable: the camera reduction also writes y rounded to FP32 here (the FP32 history
     // copy of mixed-precision MCG)
     float *y32 = nullptr;
