@@ -869,16 +869,9 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
     if ((st = salloc(s, &s->Vraw, (size_t)s->nl * 6)) != BA_OK) return bail(st);
     if ((st = salloc(s, &s->Uraw, (size_t)s->np * (d->d_p * (d->d_p + 1) / 2))) != BA_OK) return bail(st);
     if ((st = salloc(s, &s->bp, (size_t)s->np * d->d_p)) != BA_OK) return bail(st);
-    {
-        // tile slot of every observation (the lambda kernels read the packed stream by it)
-        std::vector<int64_t> oslot((size_t)m, 0);
-        for (int64_t sl = 0; sl < P.n_tiles * kTile; ++sl) {
-            const int64_t o = P.slot_obs[(size_t)sl];
-            if (o >= 0) oslot[(size_t)o] = sl;
-        }
-        if ((st = supload(s, &s->obs_slot, oslot)) != BA_OK) return bail(st);
-        if (hipStreamSynchronize(q) != hipSuccess) return bail(fail(BA_ERR_HIP, "uploading the slot map failed"));
-    }
+    // tile slot of every observation (the lambda kernels read the packed stream by it)
+    if ((st = salloc(s, &s->obs_slot, (size_t)m)) != BA_OK) return bail(st);
+    if (!counting) launch_obs_slots(nslots, s->slot_obs, s->obs_slot, q);
     if ((st = supload(s, &s->meta, P.meta)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->tile_lmk_base, P.tile_lmk_base)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->chunk_tile, P.chunk_tile)) != BA_OK) return bail(st);

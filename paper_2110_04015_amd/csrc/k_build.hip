@@ -209,6 +209,19 @@ __global__ void k_landmarks_lambda(int nl, const double *__restrict__ Vraw, cons
 
 // ---------------------------------------------------------------- cameras
 
+// The observations' tile slots, from the slots' observations (-1: padding).
+__global__ __launch_bounds__(256) void k_obs_slots(int64_t slots, const int64_t *__restrict__ slot_obs,
+                                                   int64_t *__restrict__ obs_slot) {
+    const int64_t sl = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (sl >= slots) return;
+    const int64_t o = slot_obs[sl];
+    if (o >= 0) obs_slot[o] = sl;
+}
+
+void launch_obs_slots(int64_t slots, const int64_t *slot_obs, int64_t *obs_slot, hipStream_t s) {
+    hipLaunchKernelGGL(k_obs_slots, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, s, slots, slot_obs, obs_slot);
+}
+
 __global__ __launch_bounds__(256) void k_cam_slots(int64_t m, const int64_t *__restrict__ cam_obs,
                                                    const int64_t *__restrict__ obs_slot,
                                                    const int32_t *__restrict__ obs_lm,

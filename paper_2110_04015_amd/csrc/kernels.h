@@ -84,6 +84,8 @@ void launch_convert(const double *J64, int64_t nslots, float *J32, uint16_t *J16
 // the values that depend on lambda, from those sums and the packed tile stream
 void launch_landmarks_lambda(int nl, const double *Vraw, const double *bl, double lambda, double *vinv, double *h0,
                              int32_t *status, hipStream_t s);
+// tile slot of every observation
+void launch_obs_slots(int64_t slots, const int64_t *slot_obs, int64_t *obs_slot, hipStream_t s);
 // tile slot and landmark storage index of every observation of the camera order
 void launch_cam_slots(int64_t m, const int64_t *cam_obs, const int64_t *obs_slot, const int32_t *obs_lm,
                       const int32_t *lmk_store, uint32_t *cam_slot, int32_t *cam_lmk, hipStream_t s);

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
+#include <utility>
 
 #include "ba_internal.h"
 
@@ -53,7 +54,7 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
     counting_csr(lm, m, nl, lptr, lobs);
 
     // per landmark: observations sorted by camera, duplicate check, min camera
-    std::vector<int32_t> minc((size_t)nl, 0);
+    std::vector<int32_t> minc((size_t)nl, 0), lcam((size_t)m);   // lcam: cameras of lobs
     for (int l = 0; l < nl; ++l) {
         int64_t a = lptr[l], b = lptr[l + 1];
         int64_t c = b - a;
@@ -63,11 +64,23 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
             err = buf;
             return BA_ERR_UNSUPPORTED;
         }
-        std::sort(lobs.begin() + a, lobs.begin() + b,
-                  [&](int64_t x, int64_t y) { return cam[x] < cam[y] || (cam[x] == cam[y] && x < y); });
+        bool sorted = true;
+        for (int64_t q = a; q < b; ++q) {
+            lcam[(size_t)q] = cam[lobs[(size_t)q]];
+            sorted = sorted && (q == a || lcam[(size_t)q] > lcam[(size_t)q - 1]);
+        }
+        if (!sorted) {
+            std::pair<int32_t, int64_t> by_cam[kTile];
+            for (int64_t q = a; q < b; ++q) by_cam[q - a] = {lcam[(size_t)q], lobs[(size_t)q]};
+            std::sort(by_cam, by_cam + c);
+            for (int64_t q = a; q < b; ++q) {
+                lcam[(size_t)q] = by_cam[q - a].first;
+                lobs[(size_t)q] = by_cam[q - a].second;
+            }
+        }
         for (int64_t q = a + 1; q < b; ++q) {
-            if (cam[lobs[q]] == cam[lobs[q - 1]]) {
-                snprintf(buf, sizeof buf, "camera %d observes landmark %d twice", cam[lobs[q]], l);
+            if (lcam[(size_t)q] == lcam[(size_t)q - 1]) {
+                snprintf(buf, sizeof buf, "camera %d observes landmark %d twice", lcam[(size_t)q], l);
                 err = buf;
                 return BA_ERR_INVALID_ARG;
             }
@@ -77,8 +90,8 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
             err = buf;
             return BA_ERR_NOT_SPD;
         }
-        minc[l] = cam[lobs[a]];
-        if (cam_seg && cam_seg[cam[lobs[b - 1]]] != cam_seg[minc[l]]) {
+        minc[l] = lcam[(size_t)a];
+        if (cam_seg && cam_seg[lcam[(size_t)b - 1]] != cam_seg[minc[l]]) {
             snprintf(buf, sizeof buf, "landmark %d is observed by cameras of two problems of the batch", l);
             err = buf;
             return BA_ERR_INVALID_ARG;
@@ -102,6 +115,7 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
         P.lmk_order.resize((size_t)nl);
         for (int l = 0; l < nl; ++l) P.lmk_order[(size_t)cnt[(size_t)minc[l]]++] = l;
     }
+    std::vector<int32_t> scam;   // camera of every slot
     // tiles: landmarks never straddle a tile boundary.  Tiles are filled from a
     // window of the next kWindow landmarks of the sorted order: a landmark that
     // does not fit the current tile waits while later ones fill the gap, and the
@@ -118,6 +132,9 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
         P.lmk_count.resize((size_t)nl);
         P.slot_obs.clear();
         P.meta.clear();
+        P.slot_obs.reserve((size_t)m + (size_t)m / 16 + kTile);
+        P.meta.reserve((size_t)m + (size_t)m / 16 + kTile);
+        scam.reserve((size_t)m + (size_t)m / 16 + kTile);
         P.tile_lmk_base.clear();
         size_t next = 0;
         int64_t t = 0;
@@ -126,6 +143,7 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
             P.tile_lmk_base.push_back((int32_t)P.lmk_order.size());
             P.slot_obs.resize((size_t)(t + 1) * kTile, -1);
             P.meta.resize((size_t)(t + 1) * kTile, kPad);
+            scam.resize((size_t)(t + 1) * kTile, -1);
             // a tile holds landmarks of one problem: that of the oldest waiting landmark
             const int tseg = seg_of_lmk(pending[0]);
             P.tile_seg.push_back(tseg);
@@ -145,6 +163,7 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
                 for (int q = 0; q < c; ++q) {
                     P.slot_obs[(size_t)(t * kTile + used + q)] = lobs[(size_t)(lptr[l] + q)];
                     P.meta[(size_t)(t * kTile + used + q)] = meta_pack(0, (uint32_t)ll);
+                    scam[(size_t)(t * kTile + used + q)] = lcam[(size_t)(lptr[l] + q)];
                 }
                 used += c;
                 ++ll;
@@ -175,9 +194,8 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
         for (int64_t t = 0; t < tiles; ++t) {
             int fresh = 0;   // cameras of tile t not yet in the current chunk
             for (int q = 0; q < kTile; ++q) {
-                int64_t o = P.slot_obs[(size_t)(t * kTile + q)];
-                if (o < 0) continue;
-                int c = cam[o];
+                const int c = scam[(size_t)(t * kTile + q)];
+                if (c < 0) break;
                 if (stamp[(size_t)c] != chunk && tstamp[(size_t)c] != t) {
                     tstamp[(size_t)c] = t;
                     ++fresh;
@@ -194,9 +212,8 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
             }
             for (int q = 0; q < kTile; ++q) {
                 size_t sidx = (size_t)(t * kTile + q);
-                int64_t o = P.slot_obs[sidx];
-                if (o < 0) continue;
-                int c = cam[o];
+                const int c = scam[sidx];
+                if (c < 0) break;
                 if (stamp[(size_t)c] != chunk) {
                     stamp[(size_t)c] = chunk;
                     slot_of[(size_t)c] = slots++;
@@ -243,11 +260,10 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
     {
         std::vector<int64_t> fill(P.cam_obs_ptr.begin(), P.cam_obs_ptr.end() - 1);
         for (int ch = 0; ch < P.n_chunks; ++ch) {
-            const int32_t *cams = P.part_cam.data() + P.chunk_part[(size_t)ch];   // by chunk slot
             for (int64_t sl = (int64_t)P.chunk_tile[(size_t)ch] * kTile; sl < (int64_t)P.chunk_tile[(size_t)ch + 1] * kTile; ++sl) {
                 const int64_t o = P.slot_obs[(size_t)sl];
                 if (o < 0) continue;
-                const int c = cams[P.meta[(size_t)sl] & 0xFFFFu];
+                const int c = scam[(size_t)sl];
                 const int64_t at = fill[(size_t)c]++;
                 P.cam_obs[(size_t)at] = o;
                 const int64_t k = at - P.cam_obs_ptr[(size_t)c];
@@ -312,66 +328,68 @@ void build_multi_pairs(const HostPlan &P, int N, HostMultiPlan &M, const int32_t
     M.pair_ll.assign((size_t)T * kTile, 0xFF);
     M.slot_ooff.assign((size_t)T * kTile, 0);
     M.tile_oidx.assign((size_t)T + 1, 0);
-    // per tile: landmark pairs (landmark, subset) in order of first appearance
-    std::vector<int32_t> &pair_grp = M.pair_grp;
-    pair_grp.assign((size_t)T * kTile, -1);
-    for (int64_t t = 0; t < T; ++t) {
-        int npairs = 0, rows = 0;
-        int q = 0;
-        while (q < kTile) {
-            size_t s0 = (size_t)(t * kTile + q);
-            if (P.slot_obs[s0] < 0) break;
-            uint32_t ll = P.meta[s0] >> 16;
-            int q1 = q;
-            while (q1 < kTile && P.slot_obs[(size_t)(t * kTile + q1)] >= 0 &&
-                   (P.meta[(size_t)(t * kTile + q1)] >> 16) == ll)
-                ++q1;
-            int base = npairs;
-            for (int a = q; a < q1; ++a) {
-                int c = P.obs_cam[(size_t)P.slot_obs[(size_t)(t * kTile + a)]];
-                int g = group[(size_t)c];
-                int found = -1;
-                for (int pj = base; pj < npairs; ++pj)
-                    if (pair_grp[(size_t)(t * kTile + pj)] == g) found = pj;
-                if (found < 0) {
-                    found = npairs++;
-                    pair_grp[(size_t)(t * kTile + found)] = g;
-                    M.pair_ll[(size_t)(t * kTile + found)] = (uint8_t)ll;
+    M.pair_grp.assign((size_t)T * kTile, -1);
+    // per tile: landmark pairs (landmark, subset) in order of first appearance.  The cameras
+    // come from the chunk's list by chunk slot, which stays in cache (the caller's order of
+    // the observations may be any).
+    for (int ch = 0; ch < P.n_chunks; ++ch) {
+        const int32_t *cams = P.part_cam.data() + P.chunk_part[(size_t)ch];
+        for (int64_t t = P.chunk_tile[(size_t)ch]; t < P.chunk_tile[(size_t)ch + 1]; ++t) {
+            const uint32_t *meta = P.meta.data() + t * kTile;
+            uint32_t *mmeta = M.mmeta.data() + t * kTile;
+            int32_t *slot_cam = M.slot_cam.data() + t * kTile, *pair_grp = M.pair_grp.data() + t * kTile;
+            uint8_t *pair_ll = M.pair_ll.data() + t * kTile;
+            int npairs = 0, rows = 0, q = 0;
+            while (q < kTile && meta[q] != kPad) {
+                const uint32_t ll = meta[q] >> 16;
+                const int base = npairs, q0 = q;
+                for (; q < kTile && meta[q] != kPad && meta[q] >> 16 == ll; ++q) {
+                    const int c = cams[meta[q] & 0xFFFFu], g = group[(size_t)c];
+                    int found = npairs - 1;
+                    while (found >= base && pair_grp[found] != g) --found;
+                    if (found < base) {
+                        found = npairs++;
+                        pair_grp[found] = g;
+                        pair_ll[found] = (uint8_t)ll;
+                    }
+                    slot_cam[q] = c;
+                    mmeta[q] = (uint32_t)found | ((uint32_t)base << 8);
                 }
-                M.slot_cam[(size_t)(t * kTile + a)] = c;
-                M.mmeta[(size_t)(t * kTile + a)] = (uint32_t)found | ((uint32_t)base << 8);
+                const int cnt = npairs - base;
+                for (int a = q0; a < q; ++a) mmeta[a] |= (uint32_t)cnt << 16;
+                rows += cnt * (q - q0);
             }
-            int cnt = npairs - base;
-            for (int a = q; a < q1; ++a) M.mmeta[(size_t)(t * kTile + a)] |= (uint32_t)cnt << 16;
-            rows += cnt * (q1 - q);
-            q = q1;
+            M.out_rows += rows;
+            M.tile_rows = std::max(M.tile_rows, rows);
         }
-        M.out_rows += rows;
-        M.tile_rows = std::max(M.tile_rows, rows);
     }
 }
 
-// distinct out-pairs (camera * N + subset) of tile t, ascending
-static void tile_outputs(const HostPlan &P, const HostMultiPlan &M, int64_t t, std::vector<int64_t> &need) {
-    need.clear();
-    for (int q = 0; q < kTile; ++q) {
-        size_t s = (size_t)(t * kTile + q);
-        if (P.slot_obs[s] < 0) continue;
-        uint32_t mm = M.mmeta[s];
-        int base = (mm >> 8) & 0xFF, cnt = (mm >> 16) & 0xFF;
-        int c = M.slot_cam[s];
-        for (int j = 0; j < cnt; ++j) need.push_back((int64_t)c * M.N + M.pair_grp[(size_t)(t * kTile + base + j)]);
+// The out-pairs (camera * N + subset) of tile t in slot order, repeats included, to `keys`
+// (room for kTile * kTile); returns their number.
+static int tile_outputs(const HostPlan &P, const HostMultiPlan &M, int64_t t, int64_t *keys) {
+    const uint32_t *mmeta = M.mmeta.data() + t * kTile;
+    int n = 0;
+    for (int q = 0; q < kTile && mmeta[q] != kPad; ++q) {
+        const int base = (mmeta[q] >> 8) & 0xFF, cnt = (mmeta[q] >> 16) & 0xFF;
+        const int64_t k0 = (int64_t)M.slot_cam[(size_t)(t * kTile + q)] * M.N;
+        for (int j = 0; j < cnt; ++j) keys[n++] = k0 + M.pair_grp[(size_t)(t * kTile + base + j)];
     }
-    std::sort(need.begin(), need.end());
-    need.erase(std::unique(need.begin(), need.end()), need.end());
+    return n;
 }
 
 int multi_tile_outputs(const HostPlan &P, const HostMultiPlan &M) {
     int most = 0;
-    std::vector<int64_t> need;
+    std::vector<int64_t> keys((size_t)kTile * kTile);
+    std::vector<int32_t> seen((size_t)P.np * M.N, -1);   // last tile that held the out-pair
     for (int64_t t = 0; t < P.n_tiles; ++t) {
-        tile_outputs(P, M, t, need);
-        most = std::max(most, (int)need.size());
+        const int n = tile_outputs(P, M, t, keys.data());
+        int distinct = 0;
+        for (int i = 0; i < n; ++i) {
+            distinct += seen[(size_t)keys[(size_t)i]] != t;
+            seen[(size_t)keys[(size_t)i]] = (int32_t)t;
+        }
+        most = std::max(most, distinct);
     }
     return most;
 }
@@ -385,19 +403,28 @@ ba_status build_multi_plan(const HostPlan &P, int N, int max_out, HostMultiPlan 
 ba_status build_multi_chunks(const HostPlan &P, int max_out, HostMultiPlan &M, std::string &err) {
     const int np = P.np, N = M.N;
     const int64_t T = P.n_tiles;
-    const std::vector<int32_t> &pair_grp = M.pair_grp;
-    std::vector<int64_t> need;
-    // chunks over out-pairs (camera, subset)
-    std::vector<int32_t> stamp((size_t)np * N, -1), local((size_t)np * N, 0);
+    // chunks over out-pairs (camera, subset), numbered within a chunk as they first appear
+    struct Seen {
+        int32_t tile, chunk, local;   // the last tile and chunk that held it, its number there
+    };
+    std::vector<Seen> seen((size_t)np * N, Seen{-1, -1, 0});
+    std::vector<int64_t> keys((size_t)kTile * kTile);
     std::vector<int64_t> part_key;                    // partial row -> camera * N + subset
     int chunk = -1, outs = 0, ntiles_in = 0;
     M.max_out = 0;
+    M.oidx.resize((size_t)M.out_rows);
+    int64_t at = 0;                                   // next entry of oidx
     for (int64_t t = 0; t < T; ++t) {
-        tile_outputs(P, M, t, need);   // out-pairs needed by this tile alone
-        int fresh = 0;
-        if (chunk >= 0)
-            for (int64_t k : need) fresh += stamp[(size_t)k] != chunk;
-        if ((int)need.size() > max_out) max_out = (int)need.size();
+        const int n = tile_outputs(P, M, t, keys.data());
+        int distinct = 0, fresh = 0;   // out-pairs of the tile, and those new to the chunk
+        for (int i = 0; i < n; ++i) {
+            Seen &e = seen[(size_t)keys[(size_t)i]];
+            if (e.tile == t) continue;
+            e.tile = (int32_t)t;
+            ++distinct;
+            fresh += e.chunk != chunk;
+        }
+        max_out = std::max(max_out, distinct);
         if (chunk < 0 || outs + fresh > max_out || ntiles_in >= P.max_tiles_multi ||
             P.tile_seg[(size_t)t] != M.chunk_seg.back()) {
             ++chunk;
@@ -407,28 +434,21 @@ ba_status build_multi_chunks(const HostPlan &P, int max_out, HostMultiPlan &M, s
             M.chunk_part.push_back((int32_t)part_key.size());
             M.chunk_seg.push_back(P.tile_seg[(size_t)t]);
         }
-        for (int64_t k : need) {
-            if (stamp[(size_t)k] != chunk) {
-                stamp[(size_t)k] = chunk;
-                local[(size_t)k] = outs++;
-                part_key.push_back(k);
+        M.tile_oidx[(size_t)t] = (uint32_t)at;
+        for (int i = 0; i < n; ++i) {
+            Seen &e = seen[(size_t)keys[(size_t)i]];
+            if (e.chunk != chunk) {
+                e.chunk = chunk;
+                e.local = outs++;
+                part_key.push_back(keys[(size_t)i]);
             }
+            M.oidx[(size_t)at++] = (uint16_t)e.local;
         }
-        if (outs > M.max_out) M.max_out = outs;
-        M.tile_oidx[(size_t)t] = (uint32_t)M.oidx.size();
+        M.max_out = std::max(M.max_out, outs);
         int off = 0;
-        for (int q = 0; q < kTile; ++q) {
-            size_t s = (size_t)(t * kTile + q);
-            if (P.slot_obs[s] < 0) continue;
-            uint32_t mm = M.mmeta[s];
-            int base = (mm >> 8) & 0xFF, cnt = (mm >> 16) & 0xFF;
-            int c = M.slot_cam[s];
-            M.slot_ooff[s] = (uint16_t)off;
-            for (int j = 0; j < cnt; ++j) {
-                int64_t k = (int64_t)c * N + pair_grp[(size_t)(t * kTile + base + j)];
-                M.oidx.push_back((uint16_t)local[(size_t)k]);
-            }
-            off += cnt;
+        for (int q = 0; q < kTile && M.mmeta[(size_t)(t * kTile + q)] != kPad; ++q) {
+            M.slot_ooff[(size_t)(t * kTile + q)] = (uint16_t)off;
+            off += (M.mmeta[(size_t)(t * kTile + q)] >> 16) & 0xFF;
         }
         ++ntiles_in;
     }
