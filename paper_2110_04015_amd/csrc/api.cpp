@@ -1841,8 +1841,8 @@ struct ba_batch {
     BatchProb *prob = nullptr;
     BatchDyn *dyn = nullptr;
     int32_t *skip_single = nullptr, *skip_multi = nullptr, *off = nullptr, *count = nullptr;
-    double *alpha = nullptr, *gamma = nullptr, *gpart = nullptr, *upart = nullptr, *resid = nullptr;
-    double *r = nullptr, *z = nullptr, *pstage = nullptr, *qstage = nullptr, *Y = nullptr;
+    double *alpha = nullptr, *gpart = nullptr, *upart = nullptr, *resid = nullptr;
+    double *r = nullptr, *z = nullptr, *pstage = nullptr, *Y = nullptr;
     double *Ph = nullptr, *Qh = nullptr, *Dp = nullptr, *Phi = nullptr, *beta = nullptr;
     int32_t *blk_off = nullptr, *blk_k = nullptr;
     int64_t *blk_dp = nullptr;
@@ -1882,14 +1882,12 @@ void free_batch_ws(ba_batch *b) {
     dfree(b->off);
     dfree(b->count);
     dfree(b->alpha);
-    dfree(b->gamma);
     dfree(b->gpart);
     dfree(b->upart);
     dfree(b->resid);
     dfree(b->r);
     dfree(b->z);
     dfree(b->pstage);
-    dfree(b->qstage);
     dfree(b->Y);
     dfree(b->Ph);
     dfree(b->Qh);
@@ -1937,17 +1935,16 @@ ba_status ensure_batch_ws(ba_batch *b, int N, int64_t cap) {
     hipStream_t q = b->sys->stream;
     ba_status st;
     if ((st = upload(&b->prob, hp, q)) != BA_OK) return st;
-    if ((st = dalloc(&b->dyn, (size_t)B)) != BA_OK) return st;
+    if ((st = dalloc(&b->dyn, (size_t)B * 2)) != BA_OK) return st;
     if ((st = dalloc(&b->skip_single, (size_t)B)) != BA_OK) return st;
     if ((st = dalloc(&b->skip_multi, (size_t)B)) != BA_OK) return st;
     if ((st = dalloc(&b->off, (size_t)B)) != BA_OK) return st;
     if ((st = dalloc(&b->count, 1)) != BA_OK) return st;
     if ((st = dalloc(&b->alpha, (size_t)B * kMaxBlock)) != BA_OK) return st;
-    if ((st = dalloc(&b->gamma, (size_t)B * kMaxBlock)) != BA_OK) return st;
     if ((st = dalloc(&b->gpart, (size_t)B * kBatchGramBlocks * (size_t)(N * N + N))) != BA_OK) return st;
     if ((st = dalloc(&b->upart, (size_t)B * kBatchVecBlocks * 2)) != BA_OK) return st;
     if ((st = dalloc(&b->resid, (size_t)B * 2)) != BA_OK) return st;
-    for (double **v : {&b->r, &b->z, &b->pstage, &b->qstage, &b->btp, &b->d, &b->tmp, &b->xprev})
+    for (double **v : {&b->r, &b->z, &b->pstage, &b->btp, &b->d, &b->tmp, &b->xprev})
         if ((st = dalloc(v, (size_t)ntot)) != BA_OK) return st;
     if ((st = dalloc(&b->Y, (size_t)ntot * N)) != BA_OK) return st;
     if ((st = dalloc(&b->Ph, (size_t)hb)) != BA_OK) return st;
@@ -1978,12 +1975,12 @@ BatchLaunch batch_launch(ba_batch *b, double *x) {
     L.ntot = (int64_t)b->sys->np * 9;
     L.prob = b->prob;
     L.dyn = b->dyn;
+    L.cur = b->dyn + b->B;
     L.Dchol = b->sys->Dchol;
     L.x = x;
     L.r = b->r;
     L.z = b->z;
     L.pstage = b->pstage;
-    L.qstage = b->qstage;
     L.Y = b->Y;
     L.Ph = b->Ph;
     L.Qh = b->Qh;
@@ -1991,7 +1988,6 @@ BatchLaunch batch_launch(ba_batch *b, double *x) {
     L.Phi = b->Phi;
     L.beta = b->beta;
     L.alpha = b->alpha;
-    L.gamma = b->gamma;
     L.gpart = b->gpart;
     L.upart = b->upart;
     L.blk_off = b->blk_off;
@@ -2009,8 +2005,7 @@ void batch_iteration(const BatchLaunch &L, const SchurArgs &sa, const MultiArgs 
     launch_biter_head(L, tau, eps, q);
     if (L.N > 1) launch_schur_multi(ma, L.z, L.Y, q);
     launch_biter_tail(L, q);
-    launch_schur_matvec(sa, L.pstage, L.qstage, q);
-    launch_bqcopy_advance(L, q);
+    launch_schur_matvec(sa, L.pstage, nullptr, q);   // Q into the history
 }
 
 struct BatchRun {
@@ -2027,6 +2022,9 @@ BatchRun batch_run(ba_batch *b, int precision, double *x) {
     R.sa.chunk_seg = s->seg_chunk;
     R.sa.cam_seg = s->seg_cam;
     R.sa.seg_skip = b->skip_single;
+    R.sa.prob = b->prob;
+    R.sa.dyn = b->dyn;
+    R.sa.hist = b->Qh;
     R.ma = b->N > 1 ? multi_args(s, precision) : MultiArgs();
     if (b->N > 1) {
         R.ma.chunk_seg = s->multi.chunk_seg;
@@ -2045,8 +2043,7 @@ ba_status batch_start(ba_batch *b, const BatchRun &R, const double *bt, const in
     launch_bstart(R.L, bt, nullptr, off, q, only, max_iter, max_it);
     SchurArgs s0 = R.sa;
     if (only) s0.seg_skip = only_skip;   // the problems that keep running are left alone
-    launch_schur_matvec(s0, R.L.pstage, R.L.qstage, q);
-    launch_bqcopy_advance(R.L, q, only);
+    launch_schur_matvec(s0, R.L.pstage, nullptr, q);
     HIPCHK(hipGetLastError());
     return BA_OK;
 }

@@ -8,7 +8,13 @@
 // direction history with its own width per block, Phi, beta.  Per-problem
 // scalars and counters live in BatchDyn and are advanced by the kernels
 // themselves, so an iteration is a fixed sequence of launches with no read-back
-// and can be captured into a graph.
+// and can be captured into a graph.  Most of these launches last about as long as a
+// launch takes, so an iteration has as few as the dependences allow: the state
+// alternates between two buffers (dyn between iterations, cur inside one), which lets
+// k_bpinv take the new block over and every block of k_bphi work out the scalars that
+// it needs, and the S product stores Q straight into the history.  24 ring problems of
+// 50 to 200 cameras (101,342 tiles), N = 16, FP32, 128 iterations: 31.1 ms per solve with
+// 13 launches an iteration, 28.3 ms with these 10, of which the S product takes 12.2.
 #include "ba_internal.h"
 #include "kernels.h"
 #include "dev_la.h"
@@ -104,10 +110,11 @@ __global__ __launch_bounds__(kNT) void k_bgram(int N, const BatchProb *__restric
     const BatchDyn d = dyn[b];
     if (d.done) return;
     const BatchProb P = prob[b];
-    const int k = d.kcur, tot = k * k + k, T = N * N + N;
+    // the block formed last: k_bpinv makes it the current one
+    const int k = d.kn, tot = k * k + k, T = N * N + N;
     const int64_t n = P.n;
-    const double *Pc = Ph + P.hbase + (int64_t)d.cur_off * n;
-    const double *Qc = Qh + P.hbase + (int64_t)d.cur_off * n;
+    const double *Pc = Ph + P.hbase + (int64_t)d.hcols * n;
+    const double *Qc = Qh + P.hbase + (int64_t)d.hcols * n;
     const double *rb = r + P.row0;
     const int64_t lo = n * blockIdx.x / kBGX, hi = n * (blockIdx.x + 1) / kBGX;
     double *out = part + ((int64_t)b * kBGX + blockIdx.x) * T;
@@ -159,6 +166,19 @@ __global__ __launch_bounds__(kNT) void k_bgram(int N, const BatchProb *__restric
                 const double *yv = pr ? sr : sP + (idx - a * k) * ld;
                 double s0 = 0.0, s1 = 0.0;
                 int rr = 0;
+                for (; rr + 8 <= rows; rr += 8) {   // LDS reads of eight rows in flight
+                    double xr[8], yr[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        xr[e] = xv[rr + e];
+                        yr[e] = yv[rr + e];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2) {
+                        s0 += xr[e] * yr[e];
+                        s1 += xr[e + 1] * yr[e + 1];
+                    }
+                }
                 for (; rr + 1 < rows; rr += 2) {
                     s0 += xv[rr] * yv[rr];
                     s1 += xv[rr + 1] * yv[rr + 1];
@@ -176,20 +196,25 @@ __global__ __launch_bounds__(kNT) void k_bgram(int N, const BatchProb *__restric
     }
 }
 
-// Delta^+ (stored as history block nblk), alpha = Delta^+ gamma; rank 0 stops the problem
-__global__ __launch_bounds__(kNT) void k_bpinv(int N, const BatchProb *__restrict__ prob, BatchDyn *__restrict__ dyn,
+// Takes the block formed last over as the current one, forms Delta^+ (stored as history
+// block nblk) and alpha = Delta^+ gamma, and leaves gamma^T alpha in cur's t; rank 0 stops
+// the problem.  Writes cur from dyn for every problem.
+__global__ __launch_bounds__(kNT) void k_bpinv(int N, const BatchProb *__restrict__ prob,
+                                               const BatchDyn *__restrict__ dyn, BatchDyn *__restrict__ cur,
                                                const double *__restrict__ part, double *__restrict__ Dp,
                                                int32_t *__restrict__ blk_off, int32_t *__restrict__ blk_k,
-                                               int64_t *__restrict__ blk_dp, double *__restrict__ alpha,
-                                               double *__restrict__ gamma) {
+                                               int64_t *__restrict__ blk_dp, double *__restrict__ alpha) {
     __shared__ double A[kMaxK * kMaxK], V[kMaxK * kMaxK], G[kMaxK * kMaxK];
-    __shared__ double gam[kMaxK], sh[kNT];
+    __shared__ double gam[kMaxK], al[kMaxK], sh[kNT];
     __shared__ int rank;
     const int b = blockIdx.x;
-    BatchDyn *dp = dyn + b;
-    if (dp->done) return;
+    BatchDyn d = dyn[b];
+    if (d.done) {
+        if (threadIdx.x == 0) cur[b] = d;
+        return;
+    }
     const BatchProb P = prob[b];
-    const int k = dp->kcur, tot = k * k + k, T = N * N + N;
+    const int k = d.kn, tot = k * k + k, T = N * N + N;
     for (int idx = threadIdx.x; idx < tot; idx += kNT) {
         double s = 0.0;
         for (int u = 0; u < kBGX; ++u) s += part[((int64_t)b * kBGX + u) * T + idx];
@@ -203,28 +228,35 @@ __global__ __launch_bounds__(kNT) void k_bpinv(int N, const BatchProb *__restric
     }
     __syncthreads();
     pinv_sym_lds(k, A, V, G, sh, &rank);
-    const int64_t dpo = dp->dp_used;
+    const int64_t dpo = d.dp_used;
     double *Dout = Dp + P.colbase * N + dpo;
     for (int w = threadIdx.x; w < k * k; w += kNT) Dout[w] = G[w];
     for (int a = threadIdx.x; a < k; a += kNT) {
         double s = 0.0;
         for (int c = 0; c < k; ++c) s += G[a * k + c] * gam[c];
         alpha[(int64_t)b * kMaxK + a] = s;
-        gamma[(int64_t)b * kMaxK + a] = gam[a];
+        al[a] = s;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        const int j = dp->nblk;
-        blk_off[P.colbase + j] = dp->cur_off;
+        d.cur_off = d.hcols;
+        d.kcur = k;
+        d.hcols += k;
+        const int j = d.nblk;
+        blk_off[P.colbase + j] = d.cur_off;
         blk_k[P.colbase + j] = k;
         blk_dp[P.colbase + j] = dpo;
-        dp->nblk = j + 1;
-        dp->dp_used = dpo + (int64_t)k * k;
-        dp->rank = rank;
+        d.nblk = j + 1;
+        d.dp_used = dpo + (int64_t)k * k;
+        d.rank = rank;
+        double ga = 0.0;
+        for (int a = 0; a < k; ++a) ga += gam[a] * al[a];
+        d.t = ga;
         if (rank == 0) {
-            dp->done = 1;
-            dp->status = BA_ERR_BREAKDOWN;
+            d.done = 1;
+            d.status = BA_ERR_BREAKDOWN;
         }
+        cur[b] = d;
     }
 }
 
@@ -289,27 +321,18 @@ __global__ __launch_bounds__(kNT) void k_bupdate(const BatchProb *__restrict__ p
     }
 }
 
-// stop test, tau-test (t = gamma^T alpha / r^T D^-1 r), width of the next block, the
-// history capacity check and the per-problem launch flags of the S products
-__global__ void k_bscalars(int B, int N, double tau, double eps, const BatchProb *__restrict__ prob,
-                           BatchDyn *__restrict__ dyn, const double *__restrict__ part,
-                           const double *__restrict__ alpha, const double *__restrict__ gamma,
-                           int32_t *__restrict__ skip_single, int32_t *__restrict__ skip_multi) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    BatchDyn d = dyn[b];
-    if (d.done) {
-        skip_single[b] = 1;
-        skip_multi[b] = 1;
-        return;
-    }
+// Stop test, tau-test (t = gamma^T alpha / r^T D^-1 r), width of the next block and the
+// history capacity check of one problem: the state after an iteration from that inside it.
+__device__ __forceinline__ BatchDyn next_state(BatchDyn d, int N, double tau, double eps, int cap,
+                                               const double *__restrict__ part) {
+    if (d.done) return d;
     double rr = 0.0, rho = 0.0;
+#pragma unroll
     for (int u = 0; u < kBUX; ++u) {
-        rr += part[((int64_t)b * kBUX + u) * 2];
-        rho += part[((int64_t)b * kBUX + u) * 2 + 1];
+        rr += part[u * 2];
+        rho += part[u * 2 + 1];
     }
-    double ga = 0.0;
-    for (int a = 0; a < d.kcur; ++a) ga += gamma[(int64_t)b * kMaxK + a] * alpha[(int64_t)b * kMaxK + a];
+    const double ga = d.t;
     d.rr = rr;
     d.rho = rho;
     d.iters += 1;
@@ -324,7 +347,7 @@ __global__ void k_bscalars(int B, int N, double tau, double eps, const BatchProb
         d.t = rho > 0.0 ? ga / rho : INFINITY;
         d.multi = (N > 1 && d.t < tau) ? 1 : 0;
         d.kn = d.multi ? N : 1;
-        if (d.hcols + d.kn > prob[b].cap) {
+        if (d.hcols + d.kn > cap) {
             d.done = 1;
             d.status = BA_ERR_WORKSPACE;
             d.multi = 0;
@@ -336,99 +359,120 @@ __global__ void k_bscalars(int B, int N, double tau, double eps, const BatchProb
             }
         }
     }
-    dyn[b] = d;
-    skip_single[b] = d.done || d.multi;
-    skip_multi[b] = d.done || !d.multi;
+    return d;
 }
 
-// Phi[col][p] = Q_hist[:, col]^T z restricted to subset p, for every history column of
-// every running problem (one wavefront per subset, fixed-order reductions)
-__global__ __launch_bounds__(kNT) void k_bphi(int N, const BatchProb *__restrict__ prob,
-                                              const BatchDyn *__restrict__ dyn, const double *__restrict__ Qh,
-                                              const double *__restrict__ z, double *__restrict__ Phi) {
+// The state after the update (block 0 of a problem writes it and the problem's launch flags
+// of the S products), and Phi[col][p] = Q_hist[:, col]^T z restricted to subset p, for every
+// history column of every running problem (one wavefront per subset, fixed-order reductions)
+__global__ __launch_bounds__(kNT) void k_bphi(int N, double tau, double eps, const BatchProb *__restrict__ prob,
+                                              const BatchDyn *__restrict__ cur, BatchDyn *__restrict__ dyn,
+                                              const double *__restrict__ part, const double *__restrict__ Qh,
+                                              const double *__restrict__ z, double *__restrict__ Phi,
+                                              int32_t *__restrict__ skip_single, int32_t *__restrict__ skip_multi) {
     const int b = blockIdx.y;
-    const BatchDyn d = dyn[b];
-    if (d.done) return;
     const BatchProb P = prob[b];
+    const BatchDyn d = next_state(cur[b], N, tau, eps, P.cap, part + (int64_t)b * kBUX * 2);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        dyn[b] = d;
+        skip_single[b] = d.done || d.multi;
+        skip_multi[b] = d.done || !d.multi;
+    }
+    if (d.done) return;
     const double *zb = z + P.row0;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // a fixed grid whatever the history width: block x takes columns x, x + gridDim.x, ...
     for (int col = blockIdx.x; col < d.hcols; col += gridDim.x) {
-    const double *q = Qh + P.hbase + (int64_t)col * P.n;
-    for (int p = wave; p < N; p += kNT / 64) {
-        const int64_t lo = (int64_t)p * P.gs * 9;
-        const int64_t hi = (p == N - 1) ? (int64_t)P.n : (int64_t)(p + 1) * P.gs * 9;
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;   // four rows per lane in flight
-        int64_t i = lo + lane;
-        for (; i + 192 < hi; i += 256) {
-            a0 += q[i] * zb[i];
-            a1 += q[i + 64] * zb[i + 64];
-            a2 += q[i + 128] * zb[i + 128];
-            a3 += q[i + 192] * zb[i + 192];
+        const double *q = Qh + P.hbase + (int64_t)col * P.n;
+        for (int p = wave; p < N; p += kNT / 64) {
+            const int64_t lo = (int64_t)p * P.gs * 9;
+            const int64_t hi = (p == N - 1) ? (int64_t)P.n : (int64_t)(p + 1) * P.gs * 9;
+            double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;   // four rows per lane in flight
+            int64_t i = lo + lane;
+            for (; i + 192 < hi; i += 256) {
+                a0 += q[i] * zb[i];
+                a1 += q[i + 64] * zb[i + 64];
+                a2 += q[i + 128] * zb[i + 128];
+                a3 += q[i + 192] * zb[i + 192];
+            }
+            for (; i < hi; i += 64) a0 += q[i] * zb[i];
+            const double acc = wave_sum((a0 + a1) + (a2 + a3));
+            if (lane == 0) Phi[(P.colbase + col) * N + p] = acc;
         }
-        for (; i < hi; i += 64) a0 += q[i] * zb[i];
-        const double acc = wave_sum((a0 + a1) + (a2 + a3));
-        if (lane == 0) Phi[(P.colbase + col) * N + p] = acc;
-    }
     }
 }
 
 // beta rows of history block j: beta[off_j + a][p] = sum_c Delta_j^+[a][c] Phi_(off_j + c, p);
 // for a one-column next block the subsets' Phi are summed first (Z = D^-1 r)
+// Bound by the latency of its loads: 20 us with every row summing the subsets of every column
+// by itself (kj N dependent additions), 4.8 us with each column's sum formed once.
 __global__ __launch_bounds__(kNT) void k_bbeta(int N, const BatchProb *__restrict__ prob,
                                                const BatchDyn *__restrict__ dyn, const int32_t *__restrict__ blk_off,
                                                const int32_t *__restrict__ blk_k, const int64_t *__restrict__ blk_dp,
                                                const double *__restrict__ Dp, const double *__restrict__ Phi,
                                                double *__restrict__ beta) {
+    __shared__ double fs[kMaxK];
     const int b = blockIdx.y;
     const BatchDyn d = dyn[b];
     if (d.done) return;
     const BatchProb P = prob[b];
+    // rows of hist_ldb(N) values; a multidirectional block's are padded with zeros
+    const int kn = d.kn, ldb = hist_ldb(N);
     // a fixed grid whatever the number of blocks: block x takes blocks x, x + gridDim.x, ...
     for (int j = blockIdx.x; j < d.nblk; j += gridDim.x) {
-    const int off = blk_off[P.colbase + j], kj = blk_k[P.colbase + j];
-    const double *D = Dp + P.colbase * N + blk_dp[P.colbase + j];
-    const double *F = Phi + P.colbase * N;
-    const int kn = d.kn;
-    // rows of hist_ldb(N) values; a multidirectional block's are padded with zeros
-    const int ldb = hist_ldb(N), w_row = kn == 1 ? 1 : ldb;
-    for (int w = threadIdx.x; w < kj * w_row; w += kNT) {
-        const int a = w / w_row, p = w - a * w_row;
-        double s = 0.0;
-        if (p < kn) {
-            for (int c = 0; c < kj; ++c) {
-                double f;
-                if (kn == 1) {
-                    f = 0.0;
-                    for (int q = 0; q < N; ++q) f += F[(int64_t)(off + c) * N + q];
-                } else {
-                    f = F[(int64_t)(off + c) * N + p];
-                }
-                s += D[a * kj + c] * f;
+        const int off = blk_off[P.colbase + j], kj = blk_k[P.colbase + j];
+        const double *D = Dp + P.colbase * N + blk_dp[P.colbase + j];
+        const double *F = Phi + (P.colbase + off) * N;
+        double *bt = beta + (P.colbase + off) * ldb;
+        if (kn == 1) {
+            // the sums over the subsets once per column, not once per (row, column)
+            for (int c = threadIdx.x; c < kj; c += kNT) {
+                double f = 0.0;
+#pragma unroll 8
+                for (int q = 0; q < N; ++q) f += F[(int64_t)c * N + q];
+                fs[c] = f;
             }
+            __syncthreads();
+            for (int a = threadIdx.x; a < kj; a += kNT) {
+                double s = 0.0;
+#pragma unroll 8
+                for (int c = 0; c < kj; ++c) s += D[a * kj + c] * fs[c];
+                bt[a * ldb] = s;
+            }
+            __syncthreads();
+            continue;
         }
-        beta[(P.colbase + off + a) * ldb + p] = s;
-    }
+        for (int w = threadIdx.x; w < kj * ldb; w += kNT) {
+            const int a = w / ldb, p = w - a * ldb;
+            double s = 0.0;
+            if (p < kn) {
+#pragma unroll 8
+                for (int c = 0; c < kj; ++c) s += D[a * kj + c] * F[(int64_t)c * N + p];
+            }
+            bt[a * ldb + p] = s;
+        }
     }
 }
 
 // Sums over the history of one row: ap[j] += sum_col P_hist[row, col] beta[col][j]
-// (and aq with Q_hist), four columns per step so that four loads per lane are in flight.
-// beta rows are ldb long; outputs beyond the block's width read the zero padding.
+// (and aq with Q_hist), eight columns per step so that eight loads per lane (sixteen with
+// Q) are in flight.  beta rows are ldb long; outputs beyond the block's width read the
+// zero padding.
 template <int KB, bool WITH_Q>
 __device__ inline void bhist_rows(const double *__restrict__ ph, const double *__restrict__ qh, int64_t n, int h,
                                   const double *__restrict__ bt, int ldb, double *ap, double *aq) {
+    constexpr int U = WITH_Q ? 8 : 16;
     int col = 0;
-    for (; col + 4 <= h; col += 4) {
-        double hp[4], hq[4];
+    for (; col + U <= h; col += U) {
+        double hp[U], hq[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
             hp[u] = ph[(int64_t)(col + u) * n];
             if (WITH_Q) hq[u] = qh[(int64_t)(col + u) * n];
         }
         const double *bc = bt + (int64_t)col * ldb;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
 #pragma unroll
             for (int j = 0; j < KB; ++j) {
                 ap[j] += hp[u] * bc[u * ldb + j];
@@ -436,6 +480,7 @@ __device__ inline void bhist_rows(const double *__restrict__ ph, const double *_
             }
         }
     }
+#pragma unroll 4
     for (; col < h; ++col) {
         const double hp = ph[(int64_t)col * n];
         const double hq = WITH_Q ? qh[(int64_t)col * n] : 0.0;
@@ -495,28 +540,6 @@ __global__ __launch_bounds__(64) void k_bhist(int N, int64_t ntot, const BatchPr
         Ph[P.hbase + (int64_t)(d.hcols + p) * P.n + row] = base - ap[j];
         Qh[P.hbase + (int64_t)(d.hcols + p) * P.n + row] = Y[(int64_t)p * ntot + P.row0 + row] - aq[j];
     }
-}
-
-// Q of a one-column block: copy S P_new from the staging vector into the history
-__global__ void k_bqcopy(const BatchProb *__restrict__ prob, const BatchDyn *__restrict__ dyn,
-                         const double *__restrict__ qstage, double *__restrict__ Qh, const int32_t *__restrict__ only) {
-    const int b = blockIdx.y;
-    const BatchDyn d = dyn[b];
-    if (d.done || d.multi || (only && !only[b])) return;
-    const BatchProb P = prob[b];
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < P.n; i += (int64_t)gridDim.x * blockDim.x)
-        Qh[P.hbase + (int64_t)d.hcols * P.n + i] = qstage[P.row0 + i];
-}
-
-// the new block becomes the current one
-__global__ void k_badvance(int B, BatchDyn *__restrict__ dyn, const int32_t *__restrict__ only) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B || dyn[b].done || (only && !only[b])) return;
-    BatchDyn d = dyn[b];
-    d.cur_off = d.hcols;
-    d.kcur = d.kn;
-    d.hcols += d.kn;
-    dyn[b] = d;
 }
 
 // per-problem |bt + Sx|^2 and |bt|^2; btp = bt + Sx (the right-hand side of the
@@ -607,33 +630,22 @@ void launch_bstart(const BatchLaunch &L, const double *bt, const double *x0, con
                        L.Ph, L.pstage, only);
 }
 
-void launch_bqcopy_advance(const BatchLaunch &L, hipStream_t s, const int32_t *only) {
-    hipLaunchKernelGGL(k_bqcopy, dim3((unsigned)((L.max_n + 255) / 256), L.B), dim3(256), 0, s, L.prob, L.dyn,
-                       L.qstage, L.Qh, only);
-    hipLaunchKernelGGL(k_badvance, dim3((L.B + 63) / 64), dim3(64), 0, s, L.B, L.dyn, only);
-}
-
 void launch_biter_head(const BatchLaunch &L, double tau, double eps, hipStream_t s) {
     hipLaunchKernelGGL(k_bgram, dim3(kBGX, L.B), dim3(kNT), 0, s, L.N, L.prob, L.dyn, L.Ph, L.Qh, L.r, L.gpart);
-    hipLaunchKernelGGL(k_bpinv, dim3(L.B), dim3(kNT), 0, s, L.N, L.prob, L.dyn, L.gpart, L.Dp, L.blk_off, L.blk_k,
-                       L.blk_dp, L.alpha, L.gamma);
-    hipLaunchKernelGGL(k_bupdate, dim3(kBUX, L.B), dim3(kNT), 0, s, L.prob, L.dyn, L.Ph, L.Qh, L.alpha, L.Dchol, L.x,
+    hipLaunchKernelGGL(k_bpinv, dim3(L.B), dim3(kNT), 0, s, L.N, L.prob, L.dyn, L.cur, L.gpart, L.Dp, L.blk_off,
+                       L.blk_k, L.blk_dp, L.alpha);
+    hipLaunchKernelGGL(k_bupdate, dim3(kBUX, L.B), dim3(kNT), 0, s, L.prob, L.cur, L.Ph, L.Qh, L.alpha, L.Dchol, L.x,
                        L.r, L.z, L.upart);
-    hipLaunchKernelGGL(k_bscalars, dim3((L.B + 63) / 64), dim3(64), 0, s, L.B, L.N, tau, eps, L.prob, L.dyn,
-                       L.upart, L.alpha, L.gamma, L.skip_single, L.skip_multi);
+    hipLaunchKernelGGL(k_bphi, dim3(kBatchPhiBlocks, L.B), dim3(kNT), 0, s, L.N, tau, eps, L.prob, L.cur, L.dyn,
+                       L.upart, L.Qh, L.z, L.Phi, L.skip_single, L.skip_multi);
 }
 
 void launch_biter_tail(const BatchLaunch &L, hipStream_t s) {
-    hipLaunchKernelGGL(k_bphi, dim3(kBatchPhiBlocks, L.B), dim3(kNT), 0, s, L.N, L.prob, L.dyn, L.Qh, L.z, L.Phi);
     hipLaunchKernelGGL(k_bbeta, dim3(kBatchBetaBlocks, L.B), dim3(kNT), 0, s, L.N, L.prob, L.dyn, L.blk_off, L.blk_k,
                        L.blk_dp, L.Dp, L.Phi, L.beta);
     const unsigned tiles = (unsigned)((L.max_n + 63) / 64);
-    if (L.N <= 16)
-        hipLaunchKernelGGL((k_bhist<16>), dim3(tiles, L.B, 1), dim3(64), 0, s, L.N, L.ntot, L.prob, L.dyn, L.Ph,
-                           L.Qh, L.beta, L.z, L.Y, L.pstage);
-    else
-        hipLaunchKernelGGL((k_bhist<16>), dim3(tiles, L.B, (L.N + 15) / 16), dim3(64), 0, s, L.N, L.ntot, L.prob,
-                           L.dyn, L.Ph, L.Qh, L.beta, L.z, L.Y, L.pstage);
+    hipLaunchKernelGGL((k_bhist<16>), dim3(tiles, L.B, (L.N + 15) / 16), dim3(64), 0, s, L.N, L.ntot, L.prob, L.dyn,
+                       L.Ph, L.Qh, L.beta, L.z, L.Y, L.pstage);
 }
 
 }  // namespace ba

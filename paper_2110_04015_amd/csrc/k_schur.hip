@@ -351,7 +351,7 @@ __device__ __forceinline__ double wave_rows(const double *__restrict__ rows, int
 // camera reads the last camera's and drops them).  With z (PCG) the product's vector is
 // z - beta v, which every chunk formed for its cameras and this kernel, after all of them,
 // stores in v: a launch less per iteration (571 cameras and fewer: 2 us and the gap of one).
-template <int DP>
+template <int DP, bool HIST = false>
 __global__ __launch_bounds__(256) void k_reduce1(int np, const int32_t *__restrict__ ptr,
                                                  const double *__restrict__ partial,
                                                  const double *__restrict__ dU, double *__restrict__ v,
@@ -359,7 +359,9 @@ __global__ __launch_bounds__(256) void k_reduce1(int np, const int32_t *__restri
                                                  double *__restrict__ y, const double *__restrict__ done,
                                                  const int32_t *__restrict__ cam_seg,
                                                  const int32_t *__restrict__ seg_skip, double *__restrict__ gram,
-                                                 const double *__restrict__ gr, float *__restrict__ y32) {
+                                                 const double *__restrict__ gr, float *__restrict__ y32,
+                                                 const BatchProb *__restrict__ prob,
+                                                 const BatchDyn *__restrict__ dyn, double *__restrict__ hist) {
     __shared__ double sh[4][64];
     __shared__ double gsum[2][4];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -371,6 +373,12 @@ __global__ __launch_bounds__(256) void k_reduce1(int np, const int32_t *__restri
     double vi = v[i];
     const double du = dU[i], zi = z ? z[i] : 0.0, be = z ? *beta : 0.0;
     const double gi = gram ? gr[i] : 0.0;
+    double *yo = HIST ? nullptr : y + i;
+    if (HIST) {   // the row's place in its problem's next history column
+        const int b = cam_seg[cl];
+        const BatchProb P = prob[b];
+        yo = hist + P.hbase + (int64_t)dyn[b].hcols * P.n + (i - P.row0);
+    }
     if (dn != 0.0) return;
     if (z) vi = next_direction(zi, be, vi);
     double qp = 0.0, pr = 0.0;
@@ -378,7 +386,7 @@ __global__ __launch_bounds__(256) void k_reduce1(int np, const int32_t *__restri
         const double t = wave_rows<DP>(partial, ra, rb, sh[w]);
         if (lane < DP) {
             const double yi = du * vi + t;
-            y[i] = yi;
+            *yo = yi;
             if (z) v[i] = vi;
             if (y32) y32[i] = (float)yi;
             if (gram) {
@@ -429,12 +437,9 @@ int schur_gram_blocks(int np) { return (np + 3) / 4; }
 void launch_schur_reduce(const SchurArgs &a, const double *v, double *y, hipStream_t s) {
     const dim3 g((unsigned)schur_gram_blocks(a.np)), b(256);
     double *vw = const_cast<double *>(v);   // written with a.z only (then the caller's own vector)
-    if (a.dp == 6)
-        hipLaunchKernelGGL(k_reduce1<6>, g, b, 0, s, a.np, a.cam_part_ptr, a.partial, a.dU, vw, a.z, a.beta, y, a.done,
-                           a.cam_seg, a.seg_skip, a.gram, a.gram_r, a.y32);
-    else
-        hipLaunchKernelGGL(k_reduce1<9>, g, b, 0, s, a.np, a.cam_part_ptr, a.partial, a.dU, vw, a.z, a.beta, y, a.done,
-                           a.cam_seg, a.seg_skip, a.gram, a.gram_r, a.y32);
+    auto kernel = a.dp == 6 ? k_reduce1<6> : a.hist ? k_reduce1<9, true> : k_reduce1<9>;   // batches: d_p = 9
+    hipLaunchKernelGGL(kernel, g, b, 0, s, a.np, a.cam_part_ptr, a.partial, a.dU, vw, a.z, a.beta, y, a.done, a.cam_seg,
+                       a.seg_skip, a.gram, a.gram_r, a.y32, a.prob, a.dyn, a.hist);
 }
 
 void launch_schur_matvec(const SchurArgs &a, const double *v, double *y, hipStream_t s) {

@@ -109,6 +109,25 @@ struct CameraArgs {
 constexpr int camera_part(int dp) { return dp * (dp + 1) + 2 * dp; }
 void launch_cameras(const CameraArgs &a, hipStream_t s);
 
+struct BatchProb {            // problem b of a batch (static)
+    int64_t row0;             // first row in the batch vectors (9 x first camera)
+    int64_t hbase;            // history column 0 in Ph and Qh (doubles)
+    int64_t colbase;          // first history slot: block tables at colbase, Phi / beta / Delta^+ at colbase * N
+    int32_t n, np;            // rows, cameras
+    int32_t cam0, gs;         // first camera; poses per subset (the last subset takes the rest)
+    int32_t cap, pad;         // history capacity (columns)
+};
+
+struct BatchDyn {             // per-problem solver state, advanced by the kernels
+    // between iterations: the block formed last (kn columns from hcols) is not counted yet;
+    // inside one (from the pseudo-inverse on) it is the current block
+    int32_t hcols, nblk, cur_off, kcur;   // history columns and blocks; current block (first column, width)
+    int32_t kn, multi, done, status;      // width of the next block, tau-test outcome, stopped, ba_status
+    int32_t iters, multi_steps, rank, max_it;   // ...; iterations this solve may take
+    int64_t dp_used;                      // Delta^+ storage used (doubles)
+    double rr0, rr, rho, t;               // t: gamma^T alpha inside an iteration, then the tau-test's value
+};
+
 // ---- Schur products (k_schur.hip)
 struct SchurArgs {
     const void *J = nullptr;                 // tile stream in the chosen precision
@@ -126,6 +145,10 @@ struct SchurArgs {
     const double *done = nullptr;            // nullable: when *done != 0 the launch does nothing
     // batches (nullable): a chunk / camera of problem b does nothing when seg_skip[b] != 0
     const int32_t *chunk_seg = nullptr, *cam_seg = nullptr, *seg_skip = nullptr;
+    // batches (nullable): y goes to the problem's next history column, hist + hbase + hcols n
+    const BatchProb *prob = nullptr;
+    const BatchDyn *dyn = nullptr;
+    double *hist = nullptr;
     int dp = 9;                              // pose dimension: 9, or 6 for extrinsics only
     // nullable, single systems only: the camera reduction also leaves the partials of
     // y^T v and v^T gram_r, gram[2 b], gram[2 b + 1] for b < schur_gram_blocks(np)
@@ -372,32 +395,15 @@ void launch_bsr_mm_grouped(int np, int N, const int32_t *row_ptr, const int32_t 
 
 // ---------------------------------------------------------------- batches (Algorithm 2 per problem)
 
-struct BatchProb {            // problem b of a batch (static)
-    int64_t row0;             // first row in the batch vectors (9 x first camera)
-    int64_t hbase;            // history column 0 in Ph and Qh (doubles)
-    int64_t colbase;          // first history slot: block tables at colbase, Phi / beta / Delta^+ at colbase * N
-    int32_t n, np;            // rows, cameras
-    int32_t cam0, gs;         // first camera; poses per subset (the last subset takes the rest)
-    int32_t cap, pad;         // history capacity (columns)
-};
-
-struct BatchDyn {             // per-problem solver state, advanced by the kernels
-    int32_t hcols, nblk, cur_off, kcur;   // history columns and blocks; current block (first column, width)
-    int32_t kn, multi, done, status;      // width of the next block, tau-test outcome, stopped, ba_status
-    int32_t iters, multi_steps, rank, max_it;   // ...; iterations this solve may take
-    int64_t dp_used;                      // Delta^+ storage used (doubles)
-    double rr0, rr, rho, t;
-};
-
 struct BatchLaunch {
     int B = 0, N = 1, max_np = 0;
     int64_t max_n = 0, ntot = 0;
     const BatchProb *prob = nullptr;
-    BatchDyn *dyn = nullptr;
+    BatchDyn *dyn = nullptr, *cur = nullptr;   // state between iterations, inside one
     const double *Dchol = nullptr;
-    double *x = nullptr, *r = nullptr, *z = nullptr, *pstage = nullptr, *qstage = nullptr, *Y = nullptr;
+    double *x = nullptr, *r = nullptr, *z = nullptr, *pstage = nullptr, *Y = nullptr;
     double *Ph = nullptr, *Qh = nullptr, *Dp = nullptr, *Phi = nullptr, *beta = nullptr;
-    double *alpha = nullptr, *gamma = nullptr, *gpart = nullptr, *upart = nullptr;
+    double *alpha = nullptr, *gpart = nullptr, *upart = nullptr;
     int32_t *blk_off = nullptr, *blk_k = nullptr;
     int64_t *blk_dp = nullptr;
     int32_t *skip_single = nullptr, *skip_multi = nullptr;
@@ -416,9 +422,6 @@ void launch_bstart(const BatchLaunch &L, const double *bt, const double *x0, con
 void launch_biter_head(const BatchLaunch &L, double tau, double eps, hipStream_t s);
 // Phi, beta and the new history block
 void launch_biter_tail(const BatchLaunch &L, hipStream_t s);
-// Q of one-column blocks from the staging product; the new block becomes current (`only`:
-// just the flagged problems)
-void launch_bqcopy_advance(const BatchLaunch &L, hipStream_t s, const int32_t *only = nullptr);
 // per-problem |bt + Sx|^2 and |bt|^2 (out [B][2]) and, when btp is given, btp = bt + Sx
 // (`only`: just the flagged problems)
 void launch_bresidual(const BatchLaunch &L, const double *bt, const double *Sx, double *btp, double *out,
