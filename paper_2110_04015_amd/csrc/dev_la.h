@@ -11,42 +11,76 @@ constexpr int kMaxK = 64;   // widest direction block (Delta_i is at most 64 x 6
 
 constexpr int kNT = 256;   // threads of the reduction blocks
 
-__device__ __forceinline__ double block_sum(double v, double *sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = kNT / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    double r = sh[0];
-    __syncthreads();
-    return r;
+// Cross-lane move of a double by a DPP control (lanes whose source lies outside the
+// control's reach, or outside row_mask, read 0).
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ double dpp_move(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROW_MASK, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROW_MASK, 0xf, false);
+    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
 }
 
-// block_sum of two values with one barrier: the sums are added in block_sum's order (halves of
-// the block, then of the wavefront) by the first wavefront, whose lanes alone hold them.
+// Halves of two values added: lanes below 32 get x[lane] + x[lane + 32], the others
+// y[lane - 32] + y[lane]; add_halves16 the same within each 32 lanes, by rows of 16.
+__device__ __forceinline__ double add_halves32(double x, double y) {
+    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(y), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(y), false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+
+__device__ __forceinline__ double add_halves16(double x, double y) {
+    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(y), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(y), false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+
+// x plus its value in lane xor 1, then that plus its value in lane xor 2
+__device__ __forceinline__ double quad_sum(double x) {
+    x += dpp_move<0xB1>(x);           // quad_perm:[1,0,3,2]
+    return x + dpp_move<0x4E>(x);     // quad_perm:[2,3,0,1]
+}
+
+// Sum over the lanes of a wavefront by a fixed butterfly (lanes xor 32, 16, 8, 4, 2, 1).
+// Partners add the same two values (in swapped order, which is exact), so every lane ends
+// with the same sum, independent of scheduling.  The moves are the row swaps and DPP
+// controls, not reads through the LDS pipe: after the steps before them the values repeat
+// every 16 and every 8 lanes, so that a rotation by 8 and by 4 within a row of 16 brings
+// the partner's value.  Latency bound: with six dependent LDS reads instead, the iteration end
+// of PCG (k_pcg_xrz, 50 cameras) took 6.4 us, and 5.9 us so.
+__device__ __forceinline__ double wave_sum(double v) {
+    v = add_halves32(v, v);
+    v = add_halves16(v, v);
+    v += dpp_move<0x128>(v);   // row_ror:8
+    v += dpp_move<0x124>(v);   // row_ror:4
+    v += dpp_move<0x4E>(v);    // quad_perm:[2,3,0,1]
+    v += dpp_move<0xB1>(v);    // quad_perm:[1,0,3,2]
+    return v;
+}
+
+// Sum over the block's threads, in every thread: halves of the block, of those, then the
+// butterfly, by every wavefront for itself, so that nothing waits for one.  sh holds kNT
+// doubles and is free again on return.
+__device__ __forceinline__ double block_sum(double v, double *sh) {
+    static_assert(kNT == 256, "four wavefronts");
+    const int lane = threadIdx.x & 63;
+    sh[threadIdx.x] = v;
+    __syncthreads();
+    v = wave_sum((sh[lane] + sh[lane + 128]) + (sh[lane + 64] + sh[lane + 192]));
+    __syncthreads();
+    return v;
+}
+
+// block_sum of two values with one barrier: the sums are added in block_sum's order by the
+// first wavefront, whose lanes alone hold them.
 __device__ __forceinline__ void block_sum_first(double &u, double &v, double (*sh)[kNT]) {
     const int t = threadIdx.x;
     sh[0][t] = u;
     sh[1][t] = v;
     __syncthreads();
     if (t >= 64) return;
-    u = (sh[0][t] + sh[0][t + 128]) + (sh[0][t + 64] + sh[0][t + 192]);
-    v = (sh[1][t] + sh[1][t + 128]) + (sh[1][t + 64] + sh[1][t + 192]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        u += __shfl_xor(u, o, 64);
-        v += __shfl_xor(v, o, 64);
-    }
-}
-
-// Sum over the lanes of a wavefront by a fixed butterfly.  Partners add the same two
-// values (in swapped order, which is exact), so every lane ends with the same sum,
-// independent of scheduling.
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    u = wave_sum((sh[0][t] + sh[0][t + 128]) + (sh[0][t + 64] + sh[0][t + 192]));
+    v = wave_sum((sh[1][t] + sh[1][t + 128]) + (sh[1][t + 64] + sh[1][t + 192]));
 }
 
 // Sum of nb block partials a[b * stride] by the calling wavefront (all 64 lanes must
@@ -211,8 +245,7 @@ __device__ __forceinline__ void sym_eig(int k, double *A, double *V) {
             double sum = 0.0;
             if (r4 < m)
                 for (int c = q4; c < m; c += 4) sum += A[(o + r4) * k + o + c] * (c == 0 ? v0 : A[(o + c) * k + j]);
-            sum += __shfl_xor(sum, 1, 64);
-            sum += __shfl_xor(sum, 2, 64);
+            sum = quad_sum(sum);
             if (q4 == 0 && r4 < m) hp[r4] = b * sum;
         }
         __syncthreads();
@@ -256,8 +289,7 @@ __device__ __forceinline__ void sym_eig(int k, double *A, double *V) {
         double u = 0.0;
         if (r4 < m)
             for (int r = q4; r < m; r += 4) u += (r == 0 ? v0 : A[(o + r) * k + j]) * V[(o + r) * k + o + r4];
-        u += __shfl_xor(u, 1, 64);
-        u += __shfl_xor(u, 2, 64);
+        u = quad_sum(u);
         if (q4 == 0 && r4 < m) hp[r4] = b * u;
         __syncthreads();
         if (r4 < m) {
@@ -335,16 +367,6 @@ __device__ __forceinline__ void sym_eig(int k, double *A, double *V) {
     __syncthreads();
     for (int i = tid; i < k; i += kNT) A[i * k + i] = hd[i];
     __syncthreads();
-}
-
-// Cross-lane move of a double by a DPP control (lanes whose source lies outside the
-// control's reach, or outside row_mask, read 0).
-template <int CTRL, int ROW_MASK = 0xf>
-__device__ __forceinline__ double dpp_move(double x) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROW_MASK, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROW_MASK, 0xf, false);
-    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
 }
 
 // Segments of a wavefront's lanes by a key that is equal on runs of consecutive lanes

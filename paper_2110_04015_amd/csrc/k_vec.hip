@@ -1061,15 +1061,13 @@ __global__ __launch_bounds__(kNT) void k_beta(const int32_t *__restrict__ blk_of
         double f = 0.0;
         if (r4 < kj)
             for (int g = q4; g < seg; g += 4) f += sF[r4 * seg + g];
-        f += __shfl_xor(f, 1, 64);
-        f += __shfl_xor(f, 2, 64);
+        f = quad_sum(f);
         if (q4 == 0 && r4 < kj) f1[r4] = f;
         __syncthreads();
         double s = 0.0;
         if (r4 < kj)
             for (int b = q4; b < kj; b += 4) s += sDt[b * kj + r4] * f1[b];
-        s += __shfl_xor(s, 1, 64);
-        s += __shfl_xor(s, 2, 64);
+        s = quad_sum(s);
         if (q4 == 0 && r4 < kj) beta[off + r4] = s;
         return;
     }
