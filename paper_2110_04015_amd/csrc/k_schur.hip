@@ -16,6 +16,8 @@
 // subset p.  An observation of camera c in subset q contributes e_o to column q
 // only; its landmark then carries one h_{l,p} per subset p among its observers,
 // and every observation of l receives a contribution in each such column.
+#include <utility>
+
 #include "ba_internal.h"
 #include "kernels.h"
 #include "dev_la.h"
@@ -715,7 +717,7 @@ __global__ __launch_bounds__(256) void k_reduce_multi(int np, int N, const int32
 //   k_pair_reduce: the work-groups of a camera, in order.
 // Every term is formed as the one-pass form forms it.
 // The 571-camera dense problem (897k observations, N = 47), one-pass form -> this one: FP64
-// 845 + 100 us (product, reduction) -> 38 + 98 + 12 us, FP32 888 + 101 us -> 24 + 82 + 13 us.
+// 845 + 100 us (product, reduction) -> 38 + 98 + 12 us, FP32 888 + 101 us -> 24 + 79 + 13 us.
 // k_pair_h streams the records (5 TB/s); the camera side is bound by the issue of its vector
 // instructions (95 per four observations in FP64, beside 35 us of the matrix cores).
 
@@ -844,17 +846,42 @@ __device__ __forceinline__ void pair_store(const double (&sh)[4][DP][64], int N,
 // there are and not the number of subsets.  pair_obs: the observation's first pair entry and,
 // in y, its slot in that tile (bits 0..5) and its landmark's pairs (bits 8..14).
 
+// x of lane `AT` of the lane's row of 16, in every lane of the row (all lanes active)
+template <int AT>
+__device__ __forceinline__ float row_bcast(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + AT, 0xF, 0xF, true));
+}
+
+// Component C of a record that lies two components per lane in the lanes of a row
+template <int C>
+__device__ __forceinline__ float row_comp(const float (&x)[2]) {
+    return row_bcast<C / 2>(x[C & 1]);
+}
+
+// Terms J_p^T f of a pair, rounded as the one-pass form rounds them
+template <int DP, int... K>
+__device__ __forceinline__ void pair_terms(const float (&x)[2], float f0, float f1, float (&t)[DP],
+                                           std::integer_sequence<int, K...>) {
+    ((t[K] = fmaf(row_comp<K>(x), f0, row_comp<DP + K>(x) * f1)), ...);
+}
+
 // FP32 and BF16: the lane forms its pair's column terms and adds them in the wavefront's
-// column sums in LDS.  (With a column per lane and the records in scalar registers the kernel
-// took 111 us instead of 82: the terms of the subsets that do not see a landmark are work too.)
+// column sums in LDS.  The 16 lanes of an observation hold its record between them, two
+// components each, and its F in lane 15; row broadcasts hand every lane the component that an
+// operation needs.  Bound by the LDS atomics, which take 24 cycles of the CU each: their
+// columns are scattered.  FP32 on the problem above 84 us with the whole record in every lane
+// (six 1 KB loads for four observations), 79 us so; 111 us with a column per lane and the
+// records in scalar registers, the terms of the subsets that do not see a landmark being work
+// too.
 template <int PREC, typename T, int DP>
 __global__ __launch_bounds__(256) void k_pair_out(MultiArgs a, const void *__restrict__ records,
                                                   const uint2 *__restrict__ obs, const T *__restrict__ F,
                                                   const PairH<T> *__restrict__ H, double *__restrict__ partial) {
     if (a.skip && *a.skip != 0.0) return;
-    typedef Stream<PREC, DP> St;
-    typedef typename St::word_t W;
-    constexpr int L0 = 2 * DP, L1 = 2 * DP + 3;   // J_l rows 0 and 1
+    constexpr int kLanes = DP + 3;                // lanes that hold a pair of components
+    constexpr int kPairWords = PREC == 1 ? 2 : 1;    // 4-byte words of a pair
+    constexpr int kRecWords = Stream<PREC, DP>::kWords * 4;
+    static_assert(kLanes < 16, "lane 15 of a row holds F");
     __shared__ double sh[4][DP][64];
     const int lane = threadIdx.x & 63, i = lane & 15, o = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -862,14 +889,14 @@ __global__ __launch_bounds__(256) void k_pair_out(MultiArgs a, const void *__res
     if (a.seg_skip && a.seg_skip[a.cam_seg[me.c]]) return;
     const int lo = me.lo, hi = me.hi;
     const int own = a.group[me.c];
-    const W *rec = reinterpret_cast<const W *>(records) + me.b0 * St::kWords;
+    const uint32_t *rec = reinterpret_cast<const uint32_t *>(records) + me.b0 * kRecWords + (i < kLanes ? i : 0) * kPairWords;
     obs += me.b0;
 #pragma unroll
     for (int k = 0; k < DP; ++k) sh[w][k][lane] = 0.0;
     wave_sync();
     struct Group {
-        W rw[St::kWords];
-        T f0, f1;
+        uint2 x;      // FP32: the lane's two components, lane 15: F
+        float f[2];   // BF16: F
         PairH<T> h;
         int cnt;
         uint32_t first;
@@ -877,27 +904,48 @@ __global__ __launch_bounds__(256) void k_pair_out(MultiArgs a, const void *__res
     auto words = [&](int j) { return obs[min(j + o, hi - 1)]; };
     auto load = [&](int j, const uint2 &d, Group &g) {
         const int at = min(j + o, hi - 1);
-#pragma unroll
-        for (int q = 0; q < St::kWords; ++q) g.rw[q] = rec[(int64_t)at * St::kWords + q];
         const uint32_t slot = (d.x & ~63u) | (d.y & 63u);
-        g.f0 = F[(int64_t)slot * 2];
-        g.f1 = F[(int64_t)slot * 2 + 1];
+        const uint32_t *r = rec + (int64_t)at * kRecWords;
+        const uint32_t *f = reinterpret_cast<const uint32_t *>(F + (int64_t)slot * 2);
+        if constexpr (PREC == 1) {
+            g.x = *reinterpret_cast<const uint2 *>(i == 15 ? f : r);
+        } else {
+            g.x.x = *r;
+            const uint2 fw = *reinterpret_cast<const uint2 *>(f);
+            g.f[0] = __uint_as_float(fw.x);
+            g.f[1] = __uint_as_float(fw.y);
+        }
         g.cnt = j + o < hi ? (int)(d.y >> 8) : 0;
         g.first = d.x;
         g.h = H[d.x + (i < g.cnt ? i : 0)];
     };
     auto add = [&](Group &g) {
-        T J[2 * DP + 6];
-        St::template unpack<T>(g.rw, J);
+        float x[2], fo[2];
+        if constexpr (PREC == 1) {
+            x[0] = __uint_as_float(g.x.x);
+            x[1] = __uint_as_float(g.x.y);
+            fo[0] = row_bcast<15>(x[0]);
+            fo[1] = row_bcast<15>(x[1]);
+        } else {
+            x[0] = bf16_to_f32(g.x.x & 0xFFFFu);
+            x[1] = bf16_to_f32(g.x.x >> 16);
+            fo[0] = g.f[0];
+            fo[1] = g.f[1];
+        }
         for (int p = i;;) {
+            // every lane takes part up to here: the broadcasts read their neighbours
+            const float l0[3] = {row_comp<2 * DP>(x), row_comp<2 * DP + 1>(x), row_comp<2 * DP + 2>(x)};
+            const float l1[3] = {row_comp<2 * DP + 3>(x), row_comp<2 * DP + 4>(x), row_comp<2 * DP + 5>(x)};
+            float f0 = dot3(l0, g.h.h), f1 = dot3(l1, g.h.h);
+            if (g.h.grp == own) {
+                f0 = fo[0];
+                f1 = fo[1];
+            }
+            float t[DP];
+            pair_terms<DP>(x, f0, f1, t, std::make_integer_sequence<int, DP>());
             if (p < g.cnt) {
-                T f0 = dot3(J + L0, g.h.h), f1 = dot3(J + L1, g.h.h);
-                if (g.h.grp == own) {
-                    f0 = g.f0;
-                    f1 = g.f1;
-                }
 #pragma unroll
-                for (int k = 0; k < DP; ++k) atomicAdd(&sh[w][k][g.h.grp], (double)fmaf(J[k], f0, J[DP + k] * f1));
+                for (int k = 0; k < DP; ++k) atomicAdd(&sh[w][k][g.h.grp], (double)t[k]);
             }
             p += 16;
             if (!__any(p < g.cnt)) break;
