@@ -158,6 +158,15 @@ void free_all(ba_system *s) {
     sfree(s, s->cam_part_idx);
     sfree(s, s->part_dst);
     sfree(s, s->partial);
+    for (DevChunks &c : s->own_chunks) {
+        sfree(s, c.meta);
+        sfree(s, c.chunk_tile);
+        sfree(s, c.chunk_part);
+        sfree(s, c.part_cam);
+        sfree(s, c.part_dst);
+        sfree(s, c.cam_part_ptr);
+        sfree(s, c.partial);
+    }
     sfree(s, s->vinv);
     sfree(s, s->bl);
     sfree(s, s->dU);
@@ -211,8 +220,21 @@ SchurArgs schur_args(ba_system *s, int precision) {
     // LDS rows per chunk: the most cameras any chunk holds (often well below the
     // max_slots limit, which leaves room for more resident wavefronts)
     a.max_slots = s->plan.max_used_slots;
+    a.n_part = s->plan.n_part;
     a.partial = s->partial;
     a.cam_part_ptr = s->cam_part_ptr;
+    if (const DevChunks &c = s->own_chunks[precision]; c.meta) {
+        a.meta = c.meta;
+        a.chunk_tile = c.chunk_tile;
+        a.chunk_part = c.chunk_part;
+        a.part_cam = c.part_cam;
+        a.part_dst = c.part_dst;
+        a.n_chunks = c.n_chunks;
+        a.max_slots = c.max_slots;
+        a.n_part = c.n_part;
+        a.partial = c.partial;
+        a.cam_part_ptr = c.cam_part_ptr;
+    }
     a.dU = s->dU;
     a.np = s->np;
     a.done = nullptr;
@@ -785,6 +807,9 @@ static ba_status reserve_solvers(ba_system *s, const ba_build_opts *o) {
     return BA_OK;
 }
 
+// slots whose FP64 camera rows (two of 72 bytes each, and 1.5 KB) fit six times in 160 KiB
+constexpr int kSlotsOfSix = 178;
+
 // ws (nullable): the caller's device workspace of ws_bytes; counting: the sizing pass, which
 // plans the layout on the host and counts the device bytes without allocating or launching.
 static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opts, void *stream,
@@ -803,8 +828,7 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
         return fail(BA_ERR_INVALID_ARG, "a problem array is NULL");
     if (!std::isfinite(d->lambda)) return fail(BA_ERR_NONFINITE, "lambda is not finite");
     if (d->lambda < 0.0) return fail(BA_ERR_INVALID_ARG, "lambda must be >= 0");
-    int max_slots = opts && opts->max_slots ? opts->max_slots : 128;
-    // max_tiles 0: chunks sized so that the S product's chunks are all resident at once
+    int max_slots = opts && opts->max_slots ? opts->max_slots : cam_seg ? 128 : 256;
     int max_tiles = opts && opts->max_tiles ? opts->max_tiles : 0;
     // the chunk kernel keeps 2 * max_slots camera rows of 9 doubles in LDS (<= 64 KiB)
     const int max_tiles_multi = opts ? opts->max_tiles_multi : 0;
@@ -840,10 +864,25 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
         hipMemcpyAsync(hlm.data(), d->obs_lm, (size_t)m * 4, hipMemcpyDeviceToHost, q) != hipSuccess ||
         hipStreamSynchronize(q) != hipSuccess)
         return bail(fail(BA_ERR_HIP, "copying the observation indices to the host failed"));
+    // Chunks of the S product (max_tiles 0).  A chunk costs its start (three dependent round
+    // trips) and its camera rows, written as partial rows and read again, and two tiles per
+    // wavefront in flight saturate memory with few of them: just under three chunks per compute
+    // unit (a few more than three cost up to 15 %, a fourth round for some), not the twelve that
+    // can be resident.  Fewer chunks see more cameras each, hence 256 slots where 128 would end
+    // them early.  The other precisions stream less per tile and want more wavefronts; the FP64
+    // product is the same with and without their copies, so they have chunks of their own:
+    // FP32 twice as many (while the camera rows of six fit a compute unit), BF16 the resident
+    // number, its product being bound by instructions that fewer wavefronts do not overlap
+    // (1,936 cameras: 69 us against 80).  So do batches, whose problems stop one by one.
+    // Per product, resident -> now, FP64 / FP32: 1,936 cameras along a walk (82k tiles) 171 / 97 us -> 160 / 94;
+    // a ring of 333 (11.5k) 31.7 / 21.0 -> 28.9 / 19.4; a dense cap of 571 (14.4k) 78.6 / 66.6 -> 60.5 / 50.6, of
+    // 120 (2.5k) 34.2 / 31.5 -> 21.0 / 24.5.
+    const int few = schur1_few_chunks();
     std::string err;
     ba_status st = build_plan(s->np, s->nl, m, hcam.data(), hlm.data(), max_slots, max_tiles, s->plan, err,
-                              cam_seg, max_tiles == 0 ? schur1_resident_chunks(d->d_p) : 0, max_tiles_multi,
-                              max_tiles == 0 && max_tiles_multi == 0 ? schur_multi_resident_chunks(d->d_p) : 0);
+                              cam_seg, max_tiles == 0 && cam_seg ? schur1_resident_chunks(d->d_p) : 0, max_tiles_multi,
+                              max_tiles == 0 && max_tiles_multi == 0 ? schur_multi_resident_chunks(d->d_p) : 0,
+                              max_tiles == 0 && !cam_seg ? few : 0);
     if (st != BA_OK) return bail(fail(st, err));
     if (cam_seg) {
         if ((st = supload(s, &s->seg_cam, s->plan.cam_seg)) != BA_OK) return bail(st);
@@ -885,6 +924,29 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
     if ((st = supload(s, &s->lmk_count, P.lmk_count)) != BA_OK) return bail(st);
     const int dp = s->dp;
     if ((st = salloc(s, &s->partial, (size_t)std::max<int64_t>(P.n_part, 1) * dp)) != BA_OK) return bail(st);
+    HostChunks own[3];   // until the uploads have ended
+    if (max_tiles == 0 && !cam_seg && few > 0 && P.n_tiles > few) {
+        const int slots = opts && opts->max_slots ? opts->max_slots : 128, resident = schur1_resident_chunks(dp);
+        if (opts && opts->store_fp32) build_chunks(P, max_slots, 0, 2 * few, own[1]);
+        if (own[1].max_used_slots > kSlotsOfSix) own[1].n_chunks = 0;
+        if (opts && opts->store_bf16 && resident > 0)
+            build_chunks(P, slots, (int)std::min<int64_t>(4096, (P.n_tiles + resident - 1) / resident), 0, own[2]);
+        for (int p = 1; p < 3; ++p) {
+            const HostChunks &h = own[p];
+            DevChunks &c = s->own_chunks[p];
+            if (h.n_chunks == 0) continue;
+            if ((st = supload(s, &c.meta, h.meta)) != BA_OK) return bail(st);
+            if ((st = supload(s, &c.chunk_tile, h.chunk_tile)) != BA_OK) return bail(st);
+            if ((st = supload(s, &c.chunk_part, h.chunk_part)) != BA_OK) return bail(st);
+            if ((st = supload(s, &c.part_cam, h.part_cam)) != BA_OK) return bail(st);
+            if ((st = supload(s, &c.part_dst, h.part_dst)) != BA_OK) return bail(st);
+            if ((st = supload(s, &c.cam_part_ptr, h.cam_part_ptr)) != BA_OK) return bail(st);
+            if ((st = salloc(s, &c.partial, (size_t)h.n_part * dp)) != BA_OK) return bail(st);
+            c.n_chunks = h.n_chunks;
+            c.max_slots = h.max_used_slots;
+            c.n_part = h.n_part;
+        }
+    }
     if ((st = salloc(s, &s->J64, (size_t)nslots * 24)) != BA_OK) return bail(st);
     if (opts && opts->store_fp32 && (st = salloc(s, &s->J32, (size_t)nslots * 24)) != BA_OK) return bail(st);
     if (opts && opts->store_bf16 && (st = salloc(s, &s->J16, (size_t)nslots * 24)) != BA_OK) return bail(st);
@@ -1137,7 +1199,7 @@ ba_status ba_back_substitute(ba_system *s, const double *dxp, double *dxl) {
     if (!s || !dxp || !dxl) return fail(BA_ERR_INVALID_ARG, "NULL argument");
     const HostPlan &P = s->plan;
     launch_back_substitute(s->J64, s->meta, s->tile_lmk_base, s->chunk_tile, s->chunk_part, s->part_cam,
-                           P.n_chunks, P.max_used_slots, s->vinv, s->bl, s->lmk_order, dxp, dxl, s->stream, s->dp);
+                           P.n_chunks, P.max_used_slots, P.max_tiles, s->vinv, s->bl, s->lmk_order, dxp, dxl, s->stream, s->dp);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(s->stream));
     return BA_OK;

@@ -36,28 +36,37 @@ constexpr int kCamObs = 256;
 // landmark's index inside its tile.  Padding slots hold kPad.
 __host__ __device__ inline uint32_t meta_pack(uint32_t slot, uint32_t ll) { return slot | (ll << 16); }
 
-struct HostPlan {
-    int np = 0, nl = 0;
-    int64_t m = 0;
-    int64_t n_tiles = 0;
+// Chunks of consecutive tiles: a wavefront of the one-column product takes one, with the
+// cameras it sees in slots of its LDS.
+struct HostChunks {
     int n_chunks = 0;
     int64_t n_part = 0;
-    int max_slots = 128, max_tiles = 16;
-    int max_tiles_multi = 16;             // tiles per chunk of the multidirectional product
+    int max_tiles = 16;                   // most tiles of a chunk
     int max_used_slots = 0;               // most cameras of one chunk (sizes the chunk kernels' LDS)
-    std::vector<int32_t> lmk_order;       // storage index -> landmark id
-    std::vector<int32_t> lmk_store;       // landmark id -> storage index
-    std::vector<int64_t> slot_obs;        // tile slot -> observation index or -1
     std::vector<uint32_t> meta;           // tile slot -> meta word
-    std::vector<int32_t> tile_lmk_base;   // tile -> storage index of its first landmark
-    std::vector<int64_t> lmk_first_slot;  // storage index -> first tile slot
-    std::vector<int32_t> lmk_count;       // storage index -> observations
     std::vector<int32_t> chunk_tile;      // [n_chunks + 1]
     std::vector<int32_t> chunk_part;      // [n_chunks + 1] first partial row
     std::vector<int32_t> part_cam;        // partial row -> camera
     std::vector<int32_t> cam_part_ptr;    // [np + 1]
     std::vector<int32_t> cam_part_idx;    // partial rows, camera-major, ascending
     std::vector<int32_t> part_dst;        // partial row -> its position in camera-major order
+    std::vector<int32_t> chunk_seg;       // batches: problem of every chunk
+};
+
+// The chunks themselves are those of the FP64 product and of every kernel that is not told
+// otherwise.
+struct HostPlan : HostChunks {
+    int np = 0, nl = 0;
+    int64_t m = 0;
+    int64_t n_tiles = 0;
+    int max_slots = 128;
+    int max_tiles_multi = 16;             // tiles per chunk of the multidirectional product
+    std::vector<int32_t> lmk_order;       // storage index -> landmark id
+    std::vector<int32_t> lmk_store;       // landmark id -> storage index
+    std::vector<int64_t> slot_obs;        // tile slot -> observation index or -1
+    std::vector<int32_t> tile_lmk_base;   // tile -> storage index of its first landmark
+    std::vector<int64_t> lmk_first_slot;  // storage index -> first tile slot
+    std::vector<int32_t> lmk_count;       // storage index -> observations
     std::vector<int64_t> cam_obs_ptr;     // [np + 1]
     std::vector<int64_t> cam_obs;         // observation indices, camera-major, in slot order
     // work-groups of the camera-major kernels: up to kCamObs observations of one camera
@@ -65,9 +74,19 @@ struct HostPlan {
     std::vector<int32_t> cam_blk;         // [np + 1] camera -> its first work-group
     std::vector<int32_t> blk_order;       // work-groups by their first slot
     std::vector<int32_t> obs_cam;         // host copy of the camera of each observation
-    // batches: problem of every camera (nondecreasing), of every tile and of every chunk;
-    // tiles and chunks never mix problems.  Empty for a single problem.
-    std::vector<int32_t> cam_seg, tile_seg, chunk_seg;
+    // batches: problem of every camera (nondecreasing) and of every tile; tiles and chunks
+    // never mix problems.  Empty for a single problem.
+    std::vector<int32_t> cam_seg, tile_seg;
+};
+
+// Chunks of a product whose precision wants another number of them than the plan's own
+struct DevChunks {
+    int n_chunks = 0, max_slots = 0;
+    int64_t n_part = 0;
+    uint32_t *meta = nullptr;
+    int32_t *chunk_tile = nullptr, *chunk_part = nullptr, *part_cam = nullptr, *part_dst = nullptr;
+    int32_t *cam_part_ptr = nullptr;
+    double *partial = nullptr;
 };
 
 // Plan of the multidirectional product for one partition (N subsets).
@@ -118,14 +137,17 @@ struct DevMulti {
 
 // Plan construction (host, plan.cpp).  Returns BA_OK or an error with message.
 // cam_seg (nullable, host, [np], nondecreasing): problem of every camera of a batch.
-// max_tiles = 0: the S product's chunks take ceil(n_tiles / target_chunks) tiles each
-// (16 when target_chunks is 0), so that all of them are resident at once.  The
+// max_tiles = 0: the S product's chunks take ceil(n_tiles / target_chunks) tiles each (16 when
+// target_chunks is 0), or with shares > 0 as many as make that number of chunks.  The
 // multidirectional product's chunks take max_tiles_multi tiles (0: max_tiles when it is
 // set, else ceil(n_tiles / target_multi), else 16).
 ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_t *lm,
                      int max_slots, int max_tiles, HostPlan &plan, std::string &err,
                      const int32_t *cam_seg = nullptr, int target_chunks = 0, int max_tiles_multi = 0,
-                     int target_multi = 0);
+                     int target_multi = 0, int shares = 0);
+// Another division of the plan's tiles into chunks: with shares > 0 into that many of about
+// equal length, else of max_tiles tiles each; at most max_slots cameras per chunk.
+void build_chunks(const HostPlan &plan, int max_slots, int max_tiles, int shares, HostChunks &chunks);
 // group (nullable, host, [np]): subset of every camera; default partition_groups(np, N)
 // build_multi_pairs: the (landmark, subset) pairs of every tile only; build_multi_chunks: the
 // one-pass product's chunks and output rows on top of them; build_multi_plan: both
@@ -170,6 +192,7 @@ struct ba_system {
     int32_t *chunk_tile = nullptr, *chunk_part = nullptr, *part_cam = nullptr;
     int32_t *cam_part_ptr = nullptr, *cam_part_idx = nullptr, *part_dst = nullptr;
     double *partial = nullptr;      // n_part * 9, camera-major
+    ba::DevChunks own_chunks[3];        // by precision; without a meta: those above
     double *vinv = nullptr;         // nl * 6 (storage order): V_lambda^-1, symmetric
     double *bl = nullptr;           // nl * 3 (storage order)
     double *dU = nullptr;           // np * 9: lambda * diag(J_p^T J_p)

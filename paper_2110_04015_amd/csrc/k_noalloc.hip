@@ -57,7 +57,7 @@ extern "C" ba_status ba_schur_matvec_noalloc(ba_system *s, const double *v, doub
         // the explicit S product keeps no partial rows
         ba::launch_bsr_mv(s->np, s->bsr_ptr, s->bsr_col, s->bsr_val, v, y, nullptr, s->stream, nullptr, nullptr);
     } else {
-        const size_t need = (size_t)std::max<int64_t>(s->plan.n_part, 1) * (size_t)s->dp;
+        const size_t need = (size_t)std::max<int64_t>(base.n_part, 1) * (size_t)s->dp;
         if (need > kScratchDoubles)
             return ba::set_error(BA_ERR_WORKSPACE, "the product's partial rows (" + std::to_string(need) +
                                                        " doubles) exceed the allocation-free scratch (" +

@@ -1228,26 +1228,33 @@ void launch_schur_multi(const MultiArgs &a, const double *z, double *Y, hipStrea
 // ---------------------------------------------------------------- eq. (16)
 
 // dx_l = -V^-1 (b_l + W^T dx_p) for every landmark; the first observation of a
-// landmark inside its tile writes the result.
+// landmark inside its tile writes the result.  A work-group of up to eight wavefronts takes a
+// chunk, its cameras' rows of dx_p in LDS, and each wavefront a share of its tiles: the
+// product's few chunks would leave too few wavefronts.  Bound by latency and the landmarks'
+// scattered values: 1,936 cameras, 5.08M observations 188 -> 186 us against a wavefront per
+// chunk of 2,961, a dense cap of 571 cameras 52 -> 48 us with the call; with the next tile
+// requested ahead (one landmark per lane) no faster and 55 us on the cap.
+constexpr int kBackWaves = 8;
 template <int DP>
-__global__ __launch_bounds__(64) void k_backsub(const double *__restrict__ J64, const uint32_t *__restrict__ meta,
-                                                const int32_t *__restrict__ tile_lmk_base,
-                                                const int32_t *__restrict__ chunk_tile,
-                                                const int32_t *__restrict__ chunk_part,
-                                                const int32_t *__restrict__ part_cam, int max_slots,
-                                                const double *__restrict__ vinv, const double *__restrict__ bl,
-                                                const int32_t *__restrict__ lmk_order,
-                                                const double *__restrict__ dxp, double *__restrict__ dxl) {
+__global__ __launch_bounds__(64 * kBackWaves) void k_backsub(const double *__restrict__ J64, const uint32_t *__restrict__ meta,
+                                                 const int32_t *__restrict__ tile_lmk_base,
+                                                 const int32_t *__restrict__ chunk_tile,
+                                                 const int32_t *__restrict__ chunk_part,
+                                                 const int32_t *__restrict__ part_cam, int max_slots,
+                                                 const double *__restrict__ vinv, const double *__restrict__ bl,
+                                                 const int32_t *__restrict__ lmk_order,
+                                                 const double *__restrict__ dxp, double *__restrict__ dxl) {
     extern __shared__ __align__(16) unsigned char smem[];
+    const int chunk = blockIdx.x, waves = blockDim.x / kTile;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     double *vloc = reinterpret_cast<double *>(smem);
-    double *gloc = vloc + max_slots * DP;
-    const int chunk = blockIdx.x;
-    const int lane = threadIdx.x;
+    double *gloc = vloc + max_slots * DP + w * 3 * kTile;
     const int pb = chunk_part[chunk];
     const int ns = chunk_part[chunk + 1] - pb;
-    for (int i = lane; i < ns * DP; i += kTile) vloc[i] = dxp[(int64_t)part_cam[pb + i / DP] * DP + i % DP];
+    const int c0 = chunk_tile[chunk], len = chunk_tile[chunk + 1] - c0;
+    for (int i = threadIdx.x; i < ns * DP; i += blockDim.x) vloc[i] = dxp[(int64_t)part_cam[pb + i / DP] * DP + i % DP];
     __syncthreads();
-    for (int t = chunk_tile[chunk]; t < chunk_tile[chunk + 1]; ++t) {
+    for (int t = c0 + len * w / waves; t < c0 + len * (w + 1) / waves; ++t) {
         double J[2 * DP + 6];
         Loader<0, DP>::load(J64, t, lane, J);
         const uint32_t mt = meta[(int64_t)t * kTile + lane];
@@ -1257,6 +1264,7 @@ __global__ __launch_bounds__(64) void k_backsub(const double *__restrict__ J64, 
         const uint32_t prev = lane > 0 ? meta[(int64_t)t * kTile + lane - 1] : kPad;
         const bool first = valid && (prev == kPad || ((prev >> 16) & 63u) != (uint32_t)ll);
         double e0 = 0, e1 = 0;
+#pragma unroll
         for (int k = 0; k < DP; ++k) {
             e0 += J[k] * vloc[slot * DP + k];
             e1 += J[DP + k] * vloc[slot * DP + k];
@@ -1264,10 +1272,10 @@ __global__ __launch_bounds__(64) void k_backsub(const double *__restrict__ J64, 
         gloc[lane * 3 + 0] = 0;
         gloc[lane * 3 + 1] = 0;
         gloc[lane * 3 + 2] = 0;
-        __syncthreads();
+        wave_sync();
         if (valid)
             for (int k = 0; k < 3; ++k) atomicAdd(&gloc[ll * 3 + k], J[2 * DP + k] * e0 + J[2 * DP + 3 + k] * e1);
-        __syncthreads();
+        wave_sync();
         if (first) {
             const int64_t ls = tile_lmk_base[t] + ll;
             const double *vi = vinv + ls * 6;
@@ -1278,22 +1286,20 @@ __global__ __launch_bounds__(64) void k_backsub(const double *__restrict__ J64, 
             o[1] = -(vi[1] * g0 + vi[3] * g1 + vi[4] * g2);
             o[2] = -(vi[2] * g0 + vi[4] * g1 + vi[5] * g2);
         }
-        __syncthreads();
+        wave_sync();   // the landmark rows are reset by the next tile
     }
 }
 
 void launch_back_substitute(const double *J64, const uint32_t *meta, const int32_t *tile_lmk_base,
                             const int32_t *chunk_tile, const int32_t *chunk_part, const int32_t *part_cam,
-                            int n_chunks, int max_slots, const double *vinv, const double *bl,
+                            int n_chunks, int max_slots, int max_tiles, const double *vinv, const double *bl,
                             const int32_t *lmk_order, const double *dxp, double *dxl, hipStream_t s, int dp) {
     if (n_chunks <= 0) return;
-    size_t lds = (size_t)(max_slots * dp + 3 * kTile) * sizeof(double);
-    if (dp == 6)
-        hipLaunchKernelGGL(k_backsub<6>, dim3(n_chunks), dim3(kTile), lds, s, J64, meta, tile_lmk_base, chunk_tile,
-                           chunk_part, part_cam, max_slots, vinv, bl, lmk_order, dxp, dxl);
-    else
-        hipLaunchKernelGGL(k_backsub<9>, dim3(n_chunks), dim3(kTile), lds, s, J64, meta, tile_lmk_base, chunk_tile,
-                           chunk_part, part_cam, max_slots, vinv, bl, lmk_order, dxp, dxl);
+    const int waves = std::min(kBackWaves, std::max(1, max_tiles));
+    const size_t lds = (size_t)(max_slots * dp + waves * 3 * kTile) * sizeof(double);
+    auto kernel = dp == 6 ? k_backsub<6> : k_backsub<9>;
+    hipLaunchKernelGGL(kernel, dim3(n_chunks), dim3(waves * kTile), lds, s, J64, meta, tile_lmk_base, chunk_tile,
+                       chunk_part, part_cam, max_slots, vinv, bl, lmk_order, dxp, dxl);
 }
 
 // Chunk wavefronts of a kernel the device keeps resident at once (register-limited
@@ -1310,6 +1316,14 @@ static int resident_waves(const void *f) {
 int schur1_resident_chunks(int dp) {
     return resident_waves(dp == 6 ? reinterpret_cast<const void *>(&k_schur1<0, double, 6>)
                                   : reinterpret_cast<const void *>(&k_schur1<0, double, 9>));
+}
+
+int schur1_few_chunks() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    return 3 * cus * 31 / 32;
 }
 
 int schur_multi_resident_chunks(int dp) {

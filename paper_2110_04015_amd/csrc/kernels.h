@@ -138,6 +138,7 @@ struct SchurArgs {
     const int32_t *chunk_tile = nullptr, *chunk_part = nullptr, *part_cam = nullptr, *part_dst = nullptr;
     int n_chunks = 0;
     int max_slots = 0;
+    int64_t n_part = 0;                      // partial rows
     double *partial = nullptr;
     const int32_t *cam_part_ptr = nullptr;
     const double *dU = nullptr;
@@ -165,6 +166,8 @@ int schur_gram_blocks(int np);
 // once on the current device (0: unknown)
 int schur1_resident_chunks(int dp);
 int schur_multi_resident_chunks(int dp);
+// just under three chunk wavefronts per compute unit of the current device (0: unknown)
+int schur1_few_chunks();
 // y = S v (partials then the camera reduction)
 void launch_schur_matvec(const SchurArgs &a, const double *v, double *y, hipStream_t s);
 void launch_schur_chunks(const SchurArgs &a, const double *v, hipStream_t s);
@@ -223,7 +226,7 @@ void launch_schur_multi(const MultiArgs &a, const double *z, double *Y, hipStrea
 // dx_l = -V^-1 (b_l + W^T dx_p), written in original landmark order
 void launch_back_substitute(const double *J64, const uint32_t *meta, const int32_t *tile_lmk_base,
                             const int32_t *chunk_tile, const int32_t *chunk_part, const int32_t *part_cam,
-                            int n_chunks, int max_slots, const double *vinv, const double *bl,
+                            int n_chunks, int max_slots, int max_tiles, const double *vinv, const double *bl,
                             const int32_t *lmk_order, const double *dxp, double *dxl, hipStream_t s, int dp = 9);
 
 // ---- vectors, reductions, small dense (k_vec.hip)

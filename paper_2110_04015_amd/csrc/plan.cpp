@@ -30,9 +30,94 @@ static void counting_csr(const int32_t *key, int64_t m, int nk, std::vector<int6
     for (int64_t o = 0; o < m; ++o) idx[(size_t)fill[(size_t)key[o]]++] = o;
 }
 
+// Chunks of consecutive tiles with at most max_slots distinct cameras; scam: camera of every
+// slot.  C may be P's own (its meta words hold the landmark indices already).
+static void make_chunks(const HostPlan &P, const std::vector<int32_t> &scam, int max_slots, int max_tiles, int shares,
+                        HostChunks &C) {
+    const int np = P.np;
+    const int64_t tiles = P.n_tiles;
+    // with a number of chunks to make, they take equal shares of the tiles in turn (whole
+    // tiles: floor or ceiling): with every chunk of the same length some lengths (43, 55 and
+    // their doubles among those tried) cost the product 10 % or more, and a ceiling for all
+    // leaves the last round short
+    if (shares > 0) max_tiles = (int)std::min<int64_t>(4096, std::max<int64_t>(1, (tiles + shares - 1) / shares));
+    C.max_tiles = max_tiles;
+    std::vector<int32_t> stamp((size_t)np, -1), slot_of((size_t)np, 0);
+    std::vector<int64_t> tstamp((size_t)np, -1);
+    C.chunk_tile.clear();
+    C.chunk_part.clear();
+    C.chunk_seg.clear();
+    C.part_cam.clear();
+    int64_t chunk = -1;
+    int slots = 0, ntiles_in = 0, room = max_tiles;
+    for (int64_t t = 0; t < tiles; ++t) {
+        int fresh = 0;   // cameras of tile t not yet in the current chunk
+        for (int q = 0; q < kTile; ++q) {
+            const int c = scam[(size_t)(t * kTile + q)];
+            if (c < 0) break;
+            if (stamp[(size_t)c] != chunk && tstamp[(size_t)c] != t) {
+                tstamp[(size_t)c] = t;
+                ++fresh;
+            }
+        }
+        if (chunk < 0 || slots + fresh > max_slots || ntiles_in >= room || P.tile_seg[(size_t)t] != C.chunk_seg.back()) {
+            ++chunk;
+            slots = 0;
+            ntiles_in = 0;
+            if (shares > 0) {
+                const int64_t share = (chunk + 1) * tiles / shares - chunk * tiles / shares;
+                room = (int)std::min<int64_t>(max_tiles, std::max<int64_t>(1, share));
+            }
+            C.chunk_tile.push_back((int32_t)t);
+            C.chunk_part.push_back((int32_t)C.part_cam.size());
+            C.chunk_seg.push_back(P.tile_seg[(size_t)t]);
+        }
+        for (int q = 0; q < kTile; ++q) {
+            const size_t sidx = (size_t)(t * kTile + q);
+            const int c = scam[sidx];
+            if (c < 0) break;
+            if (stamp[(size_t)c] != chunk) {
+                stamp[(size_t)c] = (int32_t)chunk;
+                slot_of[(size_t)c] = slots++;
+                C.part_cam.push_back(c);
+            }
+            C.meta[sidx] = meta_pack((uint32_t)slot_of[(size_t)c], P.meta[sidx] >> 16);
+        }
+        ++ntiles_in;
+    }
+    C.n_chunks = (int)chunk + 1;
+    C.chunk_tile.push_back((int32_t)tiles);
+    C.chunk_part.push_back((int32_t)C.part_cam.size());
+    C.n_part = (int64_t)C.part_cam.size();
+    C.max_used_slots = 1;
+    for (int ch = 0; ch < C.n_chunks; ++ch)
+        C.max_used_slots = std::max(C.max_used_slots, C.chunk_part[(size_t)ch + 1] - C.chunk_part[(size_t)ch]);
+    // camera-major CSR over partial rows (ascending row order = fixed summation order)
+    std::vector<int64_t> ptr, idx;
+    counting_csr(C.part_cam.data(), C.n_part, np, ptr, idx);
+    C.cam_part_ptr.resize((size_t)np + 1);
+    for (int c = 0; c <= np; ++c) C.cam_part_ptr[(size_t)c] = (int32_t)ptr[(size_t)c];
+    C.cam_part_idx.resize((size_t)C.n_part);
+    for (int64_t i = 0; i < C.n_part; ++i) C.cam_part_idx[(size_t)i] = (int32_t)idx[(size_t)i];
+    // a chunk writes its partial row straight into the camera-major position
+    C.part_dst.resize((size_t)C.n_part);
+    for (int64_t j = 0; j < C.n_part; ++j) C.part_dst[(size_t)C.cam_part_idx[(size_t)j]] = (int32_t)j;
+}
+
+void build_chunks(const HostPlan &P, int max_slots, int max_tiles, int shares, HostChunks &C) {
+    std::vector<int32_t> scam((size_t)P.n_tiles * kTile, -1);
+    for (int ch = 0; ch < P.n_chunks; ++ch) {
+        const int32_t *cams = P.part_cam.data() + P.chunk_part[(size_t)ch];
+        for (int64_t sl = (int64_t)P.chunk_tile[(size_t)ch] * kTile; sl < (int64_t)P.chunk_tile[(size_t)ch + 1] * kTile; ++sl)
+            if (P.meta[(size_t)sl] != kPad) scam[(size_t)sl] = cams[P.meta[(size_t)sl] & 0xFFFFu];
+    }
+    C.meta.assign(P.meta.size(), kPad);
+    make_chunks(P, scam, max_slots, max_tiles, shares, C);
+}
+
 ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_t *lm,
                      int max_slots, int max_tiles, HostPlan &P, std::string &err, const int32_t *cam_seg,
-                     int target_chunks, int max_tiles_multi, int target_multi) {
+                     int target_chunks, int max_tiles_multi, int target_multi, int shares) {
     char buf[256];
     P = HostPlan();
     P.np = np;
@@ -179,7 +264,8 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
     auto per_chunk = [&](int target) {
         return (int)std::min<int64_t>(4096, std::max<int64_t>(1, (tiles + target - 1) / target));
     };
-    if (max_tiles <= 0 && target_chunks > 0) P.max_tiles = per_chunk(target_chunks);
+    if (max_tiles > 0) shares = 0;
+    else if (target_chunks > 0) P.max_tiles = per_chunk(target_chunks);
     // Every iteration of a batch runs the multidirectional product of those problems only
     // that fail the tau-test, and lasts as long as one chunk: with many problems the chunks
     // are made shorter, so that the few that run still fill the device.  24 ring problems of
@@ -192,68 +278,7 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
         target_multi *= std::min(8, std::max(1, problems / 3));
     }
     if (max_tiles <= 0 && max_tiles_multi <= 0 && target_multi > 0) P.max_tiles_multi = per_chunk(target_multi);
-    max_tiles = P.max_tiles;
-    // chunks of consecutive tiles with at most max_slots distinct cameras
-    {
-        std::vector<int32_t> stamp((size_t)np, -1), slot_of((size_t)np, 0);
-        std::vector<int64_t> tstamp((size_t)np, -1);
-        P.chunk_tile.clear();
-        P.chunk_part.clear();
-        P.chunk_seg.clear();
-        P.part_cam.clear();
-        int chunk = -1, slots = 0, ntiles_in = 0;
-        for (int64_t t = 0; t < tiles; ++t) {
-            int fresh = 0;   // cameras of tile t not yet in the current chunk
-            for (int q = 0; q < kTile; ++q) {
-                const int c = scam[(size_t)(t * kTile + q)];
-                if (c < 0) break;
-                if (stamp[(size_t)c] != chunk && tstamp[(size_t)c] != t) {
-                    tstamp[(size_t)c] = t;
-                    ++fresh;
-                }
-            }
-            if (chunk < 0 || slots + fresh > max_slots || ntiles_in >= max_tiles ||
-                P.tile_seg[(size_t)t] != P.chunk_seg.back()) {
-                ++chunk;
-                slots = 0;
-                ntiles_in = 0;
-                P.chunk_tile.push_back((int32_t)t);
-                P.chunk_part.push_back((int32_t)P.part_cam.size());
-                P.chunk_seg.push_back(P.tile_seg[(size_t)t]);
-            }
-            for (int q = 0; q < kTile; ++q) {
-                size_t sidx = (size_t)(t * kTile + q);
-                const int c = scam[sidx];
-                if (c < 0) break;
-                if (stamp[(size_t)c] != chunk) {
-                    stamp[(size_t)c] = chunk;
-                    slot_of[(size_t)c] = slots++;
-                    P.part_cam.push_back(c);
-                }
-                P.meta[sidx] = meta_pack((uint32_t)slot_of[(size_t)c], P.meta[sidx] >> 16);
-            }
-            ++ntiles_in;
-        }
-        P.n_chunks = chunk + 1;
-        P.chunk_tile.push_back((int32_t)tiles);
-        P.chunk_part.push_back((int32_t)P.part_cam.size());
-        P.n_part = (int64_t)P.part_cam.size();
-        P.max_used_slots = 1;
-        for (int ch = 0; ch < P.n_chunks; ++ch)
-            P.max_used_slots = std::max(P.max_used_slots, P.chunk_part[(size_t)ch + 1] - P.chunk_part[(size_t)ch]);
-    }
-    // camera-major CSR over partial rows (ascending row order = fixed summation order)
-    {
-        std::vector<int64_t> ptr, idx;
-        counting_csr(P.part_cam.data(), P.n_part, np, ptr, idx);
-        P.cam_part_ptr.resize((size_t)np + 1);
-        for (int c = 0; c <= np; ++c) P.cam_part_ptr[c] = (int32_t)ptr[c];
-        P.cam_part_idx.resize((size_t)P.n_part);
-        for (int64_t i = 0; i < P.n_part; ++i) P.cam_part_idx[(size_t)i] = (int32_t)idx[(size_t)i];
-        // a chunk writes its partial row straight into the camera-major position
-        P.part_dst.resize((size_t)P.n_part);
-        for (int64_t j = 0; j < P.n_part; ++j) P.part_dst[(size_t)P.cam_part_idx[(size_t)j]] = (int32_t)j;
-    }
+    make_chunks(P, scam, max_slots, P.max_tiles, shares, P);
     // camera-major observations, each camera's in slot order: the work-groups of the cameras
     // that share a stretch of tiles read it at about the same time
     P.cam_obs_ptr.assign((size_t)np + 1, 0);

@@ -1,0 +1,54 @@
+"""The chunks of the one-column product: their number follows from the problem's size and the
+device, FP32 and BF16 copies have chunks of their own, and back-substitution shares a chunk
+between wavefronts.  Against the FP64 oracle (products 1e-12 of the largest entry in FP64; the
+FP32 and BF16 terms of the S product within 64 roundings of the sum of their sizes)."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from oracle import reduced as R
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+ba = pytest.importorskip("paper_2110_04015_amd")
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda", dtype=torch.float64)
+
+
+# one tile; fewer tiles than chunks would be made; one more than that; several per chunk; a
+# dense problem whose chunks see more than 128 cameras
+@pytest.mark.parametrize("make", [
+    lambda: synth.ring_problem(n_cams=5, n_lms=9, c_lo=2, c_hi=4, seed=1, name="ring5"),
+    lambda: synth.ring_problem(n_cams=40, n_lms=5000, c_lo=2, c_hi=8, seed=2, name="ring40"),
+    lambda: synth.ring_problem(n_cams=60, n_lms=9700, c_lo=2, c_hi=8, seed=3, name="ring60"),
+    lambda: synth.walk_problem(n_cams=150, n_lms=26000, seed=4, name="walk150"),
+    lambda: synth.cap_problem(n_cams=300, n_lms=24000, seed=5, name="cap300"),
+], ids=["ring5", "ring40", "ring60", "walk150", "cap300"])
+def test_products_and_back_substitution(make):
+    p = make()
+    o = oracle.System(p)
+    v = np.random.default_rng(6).standard_normal(9 * p.n_cams)
+    ref = o.matvec(v)
+    plain = ba.System.from_problem(p)
+    g = ba.System.from_problem(p, store_fp32=True, store_bf16=True)
+    try:
+        y = plain.matvec(_dev(v))
+        assert np.abs(y.cpu().numpy() - ref).max() <= 1e-12 * np.abs(ref).max()
+        assert torch.equal(g.matvec(_dev(v)), y)   # whatever copies are kept
+        lamd = R.lambda_diag(o.U_blocks(), p.lam)
+        for prec in ("fp32", "bf16"):
+            yr, ya = R.schur_matvec_stored(p.obs_cam, p.obs_lm, p.n_cams, p.n_lms, R.stored(p.J_p, prec),
+                                           R.stored(p.J_l, prec), o.Vinv_blocks(), lamd, v)
+            y16 = g.matvec(_dev(v), precision=prec)
+            assert np.all(np.abs(y16.cpu().numpy() - yr) <= 64 * 2.0 ** -24 * ya), prec
+            assert torch.equal(g.matvec_noalloc(_dev(v), torch.empty_like(y), precision=prec), y16)
+        step = 1e-3 * v
+        dl = g.back_substitute(_dev(step)).cpu().numpy().reshape(-1)
+        rl = np.asarray(o.back_substitute(step)).reshape(-1)
+        assert np.abs(dl - rl).max() <= 1e-11 * np.abs(rl).max()
+    finally:
+        plain.close()
+        g.close()
