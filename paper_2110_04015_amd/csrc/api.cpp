@@ -717,7 +717,7 @@ static ba_status apply_lambda(ba_system *s, const double *r) {
         (void)hipEventCreate(&e0);
         (void)hipEventCreate(&e1);
         if (e0) (void)hipEventRecord(e0, q);
-        launch_bsr_assemble(s->np, bsr_gather(s), s->obs_slot, s->J64, s->vinv, s->Dblk, s->bsr_ptr, s->bsr_col,
+        launch_bsr_assemble(s->np, bsr_gather(s), s->cam_slot, s->cam_lmk, s->J64, s->vinv, s->Dblk, s->bsr_ptr, s->bsr_col,
                             s->bsr_max_row, s->bsr_piece, s->bsr_val, q);
         if (e1) (void)hipEventRecord(e1, q);
         if (hipStreamSynchronize(q) == hipSuccess && e0 && e1) {

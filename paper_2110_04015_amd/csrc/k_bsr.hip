@@ -20,23 +20,6 @@ namespace ba {
 
 typedef double dbl2b_t __attribute__((ext_vector_type(2)));
 
-// W = J_p^T J_l (9 x 3) of the observation in tile-stream slot s (record layout of
-// the S product: 12 x 16 B words per slot, 64 slots per tile)
-__device__ __forceinline__ void w_of_slot(const double *__restrict__ J64, int64_t s, double W[27]) {
-    const dbl2b_t *p = reinterpret_cast<const dbl2b_t *>(J64) + (s >> 6) * 12 * 64 + (s & 63);
-    double v[24];
-#pragma unroll
-    for (int q = 0; q < 12; ++q) {
-        const dbl2b_t d = p[q * 64];
-        v[2 * q] = d.x;
-        v[2 * q + 1] = d.y;
-    }
-#pragma unroll
-    for (int r = 0; r < 9; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) W[r * 3 + c] = v[r] * v[18 + c] + v[9 + r] * v[21 + c];
-}
-
 // ---- pattern on the device: row j's columns are the cameras that share a landmark
 // with camera j (j included).  One work-group per row marks them in an LDS bitmap of
 // n_cams bits (every observation o of camera j, then every observation slot of o's
@@ -111,90 +94,138 @@ __global__ __launch_bounds__(256) void k_bsr_rowfill(int nwords, const int64_t *
     }
 }
 
-// One wavefront per (block row j, piece p of at most `piece` of its blocks): the piece's
-// blocks in LDS (and the row's whole column list); camera j's observations 64 at a time,
-// lane i taking observation o (of landmark l) and adding -W_o V_l^-1 W_q^T into the block
-// of q's camera for every other observation q of l whose block lies in the piece, in slot
-// order.  One wavefront issues all the LDS atomics of a block, so they resolve in program
-// order and, within an instruction, in lane order: the sums are reproducible.  Rows wider
-// than one piece (dense S) are assembled by several wavefronts, each re-reading the row's
-// observations.  The diagonal block is D(S)_j.
+// One wavefront per (block row j, piece p of at most `piece` of its blocks), the piece's
+// blocks in LDS.  It goes through camera j's observations o (of landmark l) 64 at a time and
+// queues the pairs (o, q) with the other observations q of l whose camera's block lies in the
+// piece; whenever 64 are queued, a lane takes each and adds -W_o V_l^-1 W_q^T = -J_p,o^T B
+// J_p,q, B = J_l,o V_l^-1 J_l,q^T, into the block.  One wavefront issues all the LDS atomics
+// of a block, so they resolve in program order and, within an instruction, in lane order: the
+// sums are reproducible.  Every piece goes through the row's observations.  The diagonal block
+// is D(S)_j.
+// Bound by the latency of the scattered record loads, so pieces are small (many wavefronts per
+// compute unit, where a piece of all the blocks that LDS holds left one) and the lanes work on
+// queued pairs (with 8 blocks few of an observation's pairs are wanted).  A dense cap of 571
+// cameras (897k observations, 257k blocks) 100 -> 16.5 ms, of 120 17.8 -> 2.8, 1,936
+// cameras along a walk 19.4 -> 8.0, a ring of 333 3.3 -> 1.4 (ba_set_lambda).
+constexpr int kBsrPiece = 8;
 __global__ __launch_bounds__(64) void k_bsr_assemble(const int64_t *__restrict__ cam_ptr,
-                                                     const int64_t *__restrict__ cam_obs,
-                                                     const int32_t *__restrict__ obs_lm,
-                                                     const int32_t *__restrict__ lmk_store,
+                                                     const uint32_t *__restrict__ cam_slot,
+                                                     const int32_t *__restrict__ cam_lmk,
                                                      const int64_t *__restrict__ lmk_first_slot,
                                                      const int32_t *__restrict__ lmk_count,
                                                      const int32_t *__restrict__ slot_cam,
-                                                     const int64_t *__restrict__ obs_slot,
                                                      const double *__restrict__ J64, const double *__restrict__ vinv,
                                                      const double *__restrict__ Dblk,
                                                      const int32_t *__restrict__ row_ptr,
                                                      const int32_t *__restrict__ col, double *__restrict__ val,
-                                                     int piece) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int j = blockIdx.x;
+                                                     int piece, int pieces) {
+    __shared__ double acc[kBsrPiece * 81];
+    __shared__ int32_t rc[kBsrPiece];                 // the piece's columns, ascending
+    __shared__ uint64_t queue[64 * (kBsrPiece + 1)];  // pairs: o << 6 | q, o in the camera order
+    const int j = blockIdx.x / pieces;
     const int lane = threadIdx.x;
     const int b0 = row_ptr[j], nb = row_ptr[j + 1] - b0;
-    const int pb = blockIdx.y * piece;            // first block of this wavefront's piece
+    const int pb = (blockIdx.x - j * pieces) * piece;   // first block of this wavefront's piece
     if (pb >= nb) return;
     const int pn = min(piece, nb - pb);
-    double *acc = reinterpret_cast<double *>(smem);
-    int32_t *rc = reinterpret_cast<int32_t *>(acc + (size_t)piece * 81);
     for (int e = lane; e < pn * 81; e += 64) acc[e] = 0.0;
-    for (int e = lane; e < nb; e += 64) rc[e] = col[b0 + e];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int64_t u = cam_ptr[j] + lane; u < cam_ptr[j + 1]; u += 64) {
-        const int64_t o = cam_obs[u];
-        const int s = lmk_store[obs_lm[o]];
-        const int64_t f = lmk_first_slot[s];
-        const int c = lmk_count[s];
-        double Wo[27], G[27];
-        w_of_slot(J64, obs_slot[o], Wo);
-        const double *vi = vinv + (int64_t)s * 6;
-        const double v0 = vi[0], v1 = vi[1], v2 = vi[2], v3 = vi[3], v4 = vi[4], v5 = vi[5];
-#pragma unroll
-        for (int r = 0; r < 9; ++r) {   // G = W_o V^-1 (V^-1 symmetric, packed)
-            const double x0 = Wo[r * 3], x1 = Wo[r * 3 + 1], x2 = Wo[r * 3 + 2];
-            G[r * 3] = x0 * v0 + x1 * v1 + x2 * v2;
-            G[r * 3 + 1] = x0 * v1 + x1 * v3 + x2 * v4;
-            G[r * 3 + 2] = x0 * v2 + x1 * v4 + x2 * v5;
+    if (lane < pn) rc[lane] = col[b0 + pb + lane];
+    auto lds_order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    lds_order();
+    const int kfirst = rc[0], klast = rc[pn - 1];
+    // block of column k in the piece (present: k lies in its range and in the row)
+    auto block_of = [&](int k) {
+        int lo = 0, hi = pn - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (rc[mid] < k) lo = mid + 1;
+            else hi = mid;
         }
-        for (int q = 0; q < c; ++q) {
-            const int k = slot_cam[f + q];
-            if (k == j) continue;
-            int lo = 0, hi = nb - 1;   // block of column k (present: k shares landmark l)
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (rc[mid] < k) lo = mid + 1;
-                else hi = mid;
+        return lo;
+    };
+    auto add_pair = [&](uint64_t e) {
+        const int64_t u = (int64_t)(e >> 6);
+        const int64_t l = cam_lmk[u], sq = lmk_first_slot[l] + (int64_t)(e & 63u), so = cam_slot[u];
+        const dbl2b_t *po = reinterpret_cast<const dbl2b_t *>(J64) + (so >> 6) * 12 * 64 + (so & 63);
+        const dbl2b_t *pq = reinterpret_cast<const dbl2b_t *>(J64) + (sq >> 6) * 12 * 64 + (sq & 63);
+        double a[24], c[24];
+#pragma unroll
+        for (int q = 0; q < 12; ++q) {
+            const dbl2b_t d = po[q * 64], g = pq[q * 64];
+            a[2 * q] = d.x;
+            a[2 * q + 1] = d.y;
+            c[2 * q] = g.x;
+            c[2 * q + 1] = g.y;
+        }
+        const double *vi = vinv + l * 6;
+        const double v0 = vi[0], v1 = vi[1], v2 = vi[2], v3 = vi[3], v4 = vi[4], v5 = vi[5];
+        double *blk = acc + (size_t)block_of(slot_cam[sq]) * 81;
+        double B[2][2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {   // row m of J_l,o V^-1 (V^-1 symmetric, packed), times J_l,q^T
+            const double x0 = a[18 + 3 * m], x1 = a[19 + 3 * m], x2 = a[20 + 3 * m];
+            const double t0 = x0 * v0 + x1 * v1 + x2 * v2;
+            const double t1 = x0 * v1 + x1 * v3 + x2 * v4;
+            const double t2 = x0 * v2 + x1 * v4 + x2 * v5;
+            B[m][0] = t0 * c[18] + t1 * c[19] + t2 * c[20];
+            B[m][1] = t0 * c[21] + t1 * c[22] + t2 * c[23];
+        }
+#pragma unroll
+        for (int r = 0; r < 9; ++r) {
+            const double m0 = -(a[r] * B[0][0] + a[9 + r] * B[1][0]), m1 = -(a[r] * B[0][1] + a[9 + r] * B[1][1]);
+#pragma unroll
+            for (int cc = 0; cc < 9; ++cc) atomicAdd(&blk[r * 9 + cc], m0 * c[cc] + m1 * c[9 + cc]);
+        }
+    };
+    const int64_t u1 = cam_ptr[j + 1];
+    int queued = 0;   // uniform, below 64 between trips
+    for (int64_t u0 = cam_ptr[j]; u0 < u1; u0 += 64) {
+        const int64_t u = u0 + lane;
+        uint64_t todo = 0;   // observations q of the landmark with a block here: at most pn of them
+        if (u < u1) {
+            const int s = cam_lmk[u];
+            const int64_t f = lmk_first_slot[s];
+            const int c = lmk_count[s];
+            for (int q = 0; q < c; ++q) {
+                const int k = slot_cam[f + q];
+                if (k >= kfirst && k <= klast && k != j) todo |= 1ull << q;
             }
-            if (lo < pb || lo >= pb + pn) continue;   // another wavefront's piece
-            double Wq[27];
-            w_of_slot(J64, f + q, Wq);
-            double *blk = acc + (size_t)(lo - pb) * 81;
+        }
+        // queue places: lanes in order, a lane's pairs in slot order
+        const int n = __popcll(todo);
+        const uint64_t below = (1ull << lane) - 1;
+        int at = queued, total = 0;
 #pragma unroll
-            for (int r = 0; r < 9; ++r)
-#pragma unroll
-                for (int cc = 0; cc < 9; ++cc)
-                    atomicAdd(&blk[r * 9 + cc],
-                              -(G[r * 3] * Wq[cc * 3] + G[r * 3 + 1] * Wq[cc * 3 + 1] + G[r * 3 + 2] * Wq[cc * 3 + 2]));
+        for (int b = 0; (1 << b) <= kBsrPiece; ++b) {
+            const uint64_t bits = __ballot((n >> b) & 1);
+            at += __popcll(bits & below) << b;
+            total += __popcll(bits) << b;
+        }
+        for (; todo; todo &= todo - 1) queue[at++] = (uint64_t)u << 6 | (uint64_t)(__ffsll((unsigned long long)todo) - 1);
+        queued += total;
+        lds_order();
+        int done = 0;
+        for (; done + 64 <= queued; done += 64) add_pair(queue[done + lane]);
+        if (done > 0) {   // the rest to the front (fewer than 64)
+            queued -= done;
+            const uint64_t e = lane < queued ? queue[done + lane] : 0;
+            lds_order();
+            if (lane < queued) queue[lane] = e;
+            lds_order();
         }
     }
+    if (lane < queued) add_pair(queue[lane]);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     // diagonal block: D(S)_j, formed by the build from the same sums
-    int lo = 0, hi = nb - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (rc[mid] < j) lo = mid + 1;
-        else hi = mid;
-    }
-    if (lo >= pb && lo < pb + pn)
-        for (int e = lane; e < 81; e += 64) acc[(size_t)(lo - pb) * 81 + e] = Dblk[(int64_t)j * 81 + e];
+    const int lo = block_of(j);
+    if (rc[lo] == j)
+        for (int e = lane; e < 81; e += 64) acc[(size_t)lo * 81 + e] = Dblk[(int64_t)j * 81 + e];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -409,14 +440,14 @@ int bsr_assembly_piece(int max_row, size_t lds_bytes) {
     return (int)std::min<size_t>((size_t)max_row, (lds_bytes - cols) / (81 * sizeof(double)));
 }
 
-void launch_bsr_assemble(int np, const BsrGather &g, const int64_t *obs_slot, const double *J64, const double *vinv,
-                         const double *Dblk, const int32_t *row_ptr, const int32_t *col, int max_row, int piece,
-                         double *val, hipStream_t s) {
-    const size_t lds = (size_t)piece * 81 * sizeof(double) + (size_t)max_row * sizeof(int32_t);
-    const unsigned pieces = (unsigned)((max_row + piece - 1) / piece);
-    hipLaunchKernelGGL(k_bsr_assemble, dim3(np, pieces), dim3(64), lds, s, g.cam_ptr, g.cam_obs, g.obs_lm,
-                       g.lmk_store, g.lmk_first_slot, g.lmk_count, g.slot_cam, obs_slot, J64, vinv, Dblk, row_ptr,
-                       col, val, piece);
+void launch_bsr_assemble(int np, const BsrGather &g, const uint32_t *cam_slot, const int32_t *cam_lmk,
+                         const double *J64, const double *vinv, const double *Dblk, const int32_t *row_ptr,
+                         const int32_t *col, int max_row, int piece, double *val, hipStream_t s) {
+    piece = std::min(piece, kBsrPiece);
+    const int pieces = (max_row + piece - 1) / piece;
+    hipLaunchKernelGGL(k_bsr_assemble, dim3((unsigned)np * (unsigned)pieces), dim3(64), 0, s, g.cam_ptr, cam_slot,
+                       cam_lmk, g.lmk_first_slot, g.lmk_count, g.slot_cam, J64, vinv, Dblk, row_ptr, col, val, piece,
+                       pieces);
 }
 
 void launch_bsr_mv(int np, const int32_t *row_ptr, const int32_t *col, const double *val, const double *v, double *y,

@@ -382,11 +382,12 @@ void launch_bsr_rowfill(int np, const BsrGather &g, const int32_t *row_ptr, int3
 // blocks of a row that one wavefront of the assembly holds in lds_bytes of LDS (with the
 // row's column list); 0 when not even one fits
 int bsr_assembly_piece(int max_row, size_t lds_bytes);
-// block values (9 x 9, row-major per block); obs_slot: slot of every observation; rows are
-// assembled in pieces of at most `piece` blocks (bsr_assembly_piece)
-void launch_bsr_assemble(int np, const BsrGather &g, const int64_t *obs_slot, const double *J64, const double *vinv,
-                         const double *Dblk, const int32_t *row_ptr, const int32_t *col, int max_row, int piece,
-                         double *val, hipStream_t s);
+// block values (9 x 9, row-major per block); cam_slot, cam_lmk: tile slot and landmark storage
+// index of every observation of the camera order; `piece`: the most blocks of a row that a
+// wavefront may hold (bsr_assembly_piece)
+void launch_bsr_assemble(int np, const BsrGather &g, const uint32_t *cam_slot, const int32_t *cam_lmk,
+                         const double *J64, const double *vinv, const double *Dblk, const int32_t *row_ptr,
+                         const int32_t *col, int max_row, int piece, double *val, hipStream_t s);
 // y = S v; with gram, row j also leaves gram[2 j] = y_j . v_j, gram[2 j + 1] = v_j . gram_r_j
 // (np partial pairs, see bsr_gram_blocks)
 void launch_bsr_mv(int np, const int32_t *row_ptr, const int32_t *col, const double *val, const double *v, double *y,

@@ -1,0 +1,31 @@
+"""Assembly of the explicit S: rows of as many blocks as a piece holds and one more, cameras
+with about one round of observations, landmarks seen by every camera (a full queue of pairs).
+Products against the oracle's operator within 1e-12 of the largest entry, and the same bits
+from a second assembly."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+ba = pytest.importorskip("paper_2110_04015_amd")
+
+
+@pytest.mark.parametrize("cams,lms,seen", [(2, 40, 2), (8, 64, 8), (9, 63, 9), (9, 65, 9), (17, 300, 17), (40, 900, 12)])
+def test_assembled_rows(cams, lms, seen):
+    p = synth.ring_problem(n_cams=cams, n_lms=lms, c_lo=min(2, seen) if cams > 17 else seen, c_hi=seen, seed=cams, name="rows")
+    o = oracle.System(p)
+    g = ba.System.from_problem(p, explicit_schur=True)
+    try:
+        for k in range(3):
+            v = np.random.default_rng(k).standard_normal(9 * cams)
+            ref = o.matvec(v)
+            y = g.matvec(torch.from_numpy(v).to("cuda"))
+            assert np.abs(y.cpu().numpy() - ref).max() <= 1e-12 * np.abs(ref).max()
+        g.set_lambda(2.0 * p.lam)
+        g.set_lambda(p.lam)
+        assert torch.equal(g.matvec(torch.from_numpy(v).to("cuda")), y)
+    finally:
+        g.close()
