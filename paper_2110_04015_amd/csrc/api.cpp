@@ -103,6 +103,16 @@ ba_status supload(ba_system *s, T **p, const std::vector<T> &v) {
     return BA_OK;
 }
 
+void free_chunks(ba_system *s, DevChunks &c) {
+    sfree(s, c.meta);
+    sfree(s, c.chunk_tile);
+    sfree(s, c.chunk_part);
+    sfree(s, c.part_cam);
+    sfree(s, c.part_dst);
+    sfree(s, c.cam_part_ptr);
+    sfree(s, c.partial);
+}
+
 void free_multi(ba_system *s, DevMulti &m) {
     sfree(s, m.mmeta);
     sfree(s, m.slot_cam);
@@ -158,15 +168,7 @@ void free_all(ba_system *s) {
     sfree(s, s->cam_part_idx);
     sfree(s, s->part_dst);
     sfree(s, s->partial);
-    for (DevChunks &c : s->own_chunks) {
-        sfree(s, c.meta);
-        sfree(s, c.chunk_tile);
-        sfree(s, c.chunk_part);
-        sfree(s, c.part_cam);
-        sfree(s, c.part_dst);
-        sfree(s, c.cam_part_ptr);
-        sfree(s, c.partial);
-    }
+    for (DevChunks &c : s->own_chunks) free_chunks(s, c);
     sfree(s, s->vinv);
     sfree(s, s->bl);
     sfree(s, s->dU);
@@ -306,6 +308,44 @@ void matvec(ba_system *s, const SchurArgs &a, const double *v, double *y) {
     launch_schur_reduce(a, v, y, s->stream);
 }
 
+// slots whose FP64 camera rows (two of 72 bytes each, and 1.5 KB) fit six times in 160 KiB
+constexpr int kSlotsOfSix = 178;
+
+// Chunks of a precision's product, made with its copy of the records (see build_system for
+// their number); without them the product takes the plan's.
+ba_status ensure_chunks(ba_system *s, int precision) {
+    DevChunks &c = s->own_chunks[precision];
+    if (s->own_slots == 0 || c.meta) return BA_OK;
+    const HostPlan &P = s->plan;
+    HostChunks h;
+    if (precision == 1) {
+        build_chunks(P, s->own_slots > 0 ? s->own_slots : 256, 0, 2 * schur1_few_chunks(), h);
+        if (h.max_used_slots > kSlotsOfSix) return BA_OK;
+    } else {
+        const int resident = schur1_resident_chunks(s->dp);
+        if (resident <= 0) return BA_OK;
+        build_chunks(P, s->own_slots > 0 ? s->own_slots : 128,
+                     (int)std::min<int64_t>(4096, (P.n_tiles + resident - 1) / resident), 0, h);
+    }
+    uint32_t *meta = nullptr;   // set last: the chunks are taken when it is there
+    ba_status st;
+    if ((st = supload(s, &c.chunk_tile, h.chunk_tile)) != BA_OK || (st = supload(s, &c.chunk_part, h.chunk_part)) != BA_OK ||
+        (st = supload(s, &c.part_cam, h.part_cam)) != BA_OK || (st = supload(s, &c.part_dst, h.part_dst)) != BA_OK ||
+        (st = supload(s, &c.cam_part_ptr, h.cam_part_ptr)) != BA_OK ||
+        (st = salloc(s, &c.partial, (size_t)h.n_part * s->dp)) != BA_OK || (st = supload(s, &meta, h.meta)) != BA_OK) {
+        (void)hipStreamSynchronize(s->stream);
+        sfree(s, meta);
+        free_chunks(s, c);
+        return st;
+    }
+    c.n_chunks = h.n_chunks;
+    c.max_slots = h.max_used_slots;
+    c.n_part = h.n_part;
+    c.meta = meta;
+    if (!s->ws_counting) HIPCHK(hipStreamSynchronize(s->stream));   // h goes out of scope
+    return BA_OK;
+}
+
 ba_status ensure_precision(ba_system *s, int precision) {
     if (precision < 0 || precision > 2) return fail(BA_ERR_INVALID_ARG, "precision must be 0 (FP64), 1 (FP32) or 2 (BF16)");
     const int64_t nslots = s->plan.n_tiles * kTile;
@@ -314,12 +354,14 @@ ba_status ensure_precision(ba_system *s, int precision) {
         if (st != BA_OK) return st;
         if (!s->ws_counting) launch_convert(s->J64, nslots, s->J32, nullptr, s->stream, s->dp);
         HIPCHK(hipGetLastError());
+        (void)ensure_chunks(s, 1);   // no room for them: the plan's chunks do
     }
     if (precision == 2 && !s->J16) {
         ba_status st = salloc(s, &s->J16, (size_t)nslots * 24);
         if (st != BA_OK) return st;
         if (!s->ws_counting) launch_convert(s->J64, nslots, nullptr, s->J16, s->stream, s->dp);
         HIPCHK(hipGetLastError());
+        (void)ensure_chunks(s, 2);
     }
     return BA_OK;
 }
@@ -807,9 +849,6 @@ static ba_status reserve_solvers(ba_system *s, const ba_build_opts *o) {
     return BA_OK;
 }
 
-// slots whose FP64 camera rows (two of 72 bytes each, and 1.5 KB) fit six times in 160 KiB
-constexpr int kSlotsOfSix = 178;
-
 // ws (nullable): the caller's device workspace of ws_bytes; counting: the sizing pass, which
 // plans the layout on the host and counts the device bytes without allocating or launching.
 static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opts, void *stream,
@@ -873,10 +912,10 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
     // product is the same with and without their copies, so they have chunks of their own:
     // FP32 twice as many (while the camera rows of six fit a compute unit), BF16 the resident
     // number, its product being bound by instructions that fewer wavefronts do not overlap
-    // (1,936 cameras: 69 us against 80).  So do batches, whose problems stop one by one.
-    // Per product, resident -> now, FP64 / FP32: 1,936 cameras along a walk (82k tiles) 171 / 97 us -> 160 / 94;
-    // a ring of 333 (11.5k) 31.7 / 21.0 -> 28.9 / 19.4; a dense cap of 571 (14.4k) 78.6 / 66.6 -> 60.5 / 50.6, of
-    // 120 (2.5k) 34.2 / 31.5 -> 21.0 / 24.5.
+    // (1,936 cameras: 69 us against 80).  So do batches, whose problems stop one by one.  Per
+    // product, resident -> now, FP64 / FP32: 1,936 cameras along a walk (82k tiles) 171 / 97 us
+    // -> 160 / 94; a ring of 333 (11.5k) 31.7 / 21.0 -> 28.9 / 19.4; a dense cap of 571 (14.4k)
+    // 78.6 / 66.6 -> 60.5 / 50.6, of 120 (2.5k) 34.2 / 31.5 -> 21.0 / 24.5.
     const int few = schur1_few_chunks();
     std::string err;
     ba_status st = build_plan(s->np, s->nl, m, hcam.data(), hlm.data(), max_slots, max_tiles, s->plan, err,
@@ -924,29 +963,6 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
     if ((st = supload(s, &s->lmk_count, P.lmk_count)) != BA_OK) return bail(st);
     const int dp = s->dp;
     if ((st = salloc(s, &s->partial, (size_t)std::max<int64_t>(P.n_part, 1) * dp)) != BA_OK) return bail(st);
-    HostChunks own[3];   // until the uploads have ended
-    if (max_tiles == 0 && !cam_seg && few > 0 && P.n_tiles > few) {
-        const int slots = opts && opts->max_slots ? opts->max_slots : 128, resident = schur1_resident_chunks(dp);
-        if (opts && opts->store_fp32) build_chunks(P, max_slots, 0, 2 * few, own[1]);
-        if (own[1].max_used_slots > kSlotsOfSix) own[1].n_chunks = 0;
-        if (opts && opts->store_bf16 && resident > 0)
-            build_chunks(P, slots, (int)std::min<int64_t>(4096, (P.n_tiles + resident - 1) / resident), 0, own[2]);
-        for (int p = 1; p < 3; ++p) {
-            const HostChunks &h = own[p];
-            DevChunks &c = s->own_chunks[p];
-            if (h.n_chunks == 0) continue;
-            if ((st = supload(s, &c.meta, h.meta)) != BA_OK) return bail(st);
-            if ((st = supload(s, &c.chunk_tile, h.chunk_tile)) != BA_OK) return bail(st);
-            if ((st = supload(s, &c.chunk_part, h.chunk_part)) != BA_OK) return bail(st);
-            if ((st = supload(s, &c.part_cam, h.part_cam)) != BA_OK) return bail(st);
-            if ((st = supload(s, &c.part_dst, h.part_dst)) != BA_OK) return bail(st);
-            if ((st = supload(s, &c.cam_part_ptr, h.cam_part_ptr)) != BA_OK) return bail(st);
-            if ((st = salloc(s, &c.partial, (size_t)h.n_part * dp)) != BA_OK) return bail(st);
-            c.n_chunks = h.n_chunks;
-            c.max_slots = h.max_used_slots;
-            c.n_part = h.n_part;
-        }
-    }
     if ((st = salloc(s, &s->J64, (size_t)nslots * 24)) != BA_OK) return bail(st);
     if (opts && opts->store_fp32 && (st = salloc(s, &s->J32, (size_t)nslots * 24)) != BA_OK) return bail(st);
     if (opts && opts->store_bf16 && (st = salloc(s, &s->J16, (size_t)nslots * 24)) != BA_OK) return bail(st);
@@ -1014,6 +1030,9 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(q) != hipSuccess)   // host vectors go out of scope
             return bail(fail(BA_ERR_HIP, "explicit S: pattern failed"));
     }
+    if (max_tiles == 0 && !cam_seg && few > 0 && P.n_tiles > few) s->own_slots = opts && opts->max_slots ? opts->max_slots : -1;
+    if (opts && opts->store_fp32 && (st = ensure_chunks(s, 1)) != BA_OK) return bail(st);
+    if (opts && opts->store_bf16 && (st = ensure_chunks(s, 2)) != BA_OK) return bail(st);
     if (!counting) launch_cam_slots(m, s->cam_obs, s->obs_slot, s->obs_lm, s->lmk_store, s->cam_slot, s->cam_lmk, q);
     if (!counting && (st = fill_values(s, d->J_p, d->J_l, d->r)) != BA_OK) return bail(st);
     if ((st = ensure_pinned(s)) != BA_OK) return bail(st);

@@ -192,7 +192,8 @@ struct ba_system {
     int32_t *chunk_tile = nullptr, *chunk_part = nullptr, *part_cam = nullptr;
     int32_t *cam_part_ptr = nullptr, *cam_part_idx = nullptr, *part_dst = nullptr;
     double *partial = nullptr;      // n_part * 9, camera-major
-    ba::DevChunks own_chunks[3];        // by precision; without a meta: those above
+    ba::DevChunks own_chunks[3];    // by precision; without a meta: those above
+    int own_slots = 0;              // cameras per such chunk (-1: chosen by precision; 0: none are made)
     double *vinv = nullptr;         // nl * 6 (storage order): V_lambda^-1, symmetric
     double *bl = nullptr;           // nl * 3 (storage order)
     double *dU = nullptr;           // np * 9: lambda * diag(J_p^T J_p)

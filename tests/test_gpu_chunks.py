@@ -45,6 +45,8 @@ def test_products_and_back_substitution(make):
             y16 = g.matvec(_dev(v), precision=prec)
             assert np.all(np.abs(y16.cpu().numpy() - yr) <= 64 * 2.0 ** -24 * ya), prec
             assert torch.equal(g.matvec_noalloc(_dev(v), torch.empty_like(y), precision=prec), y16)
+            assert torch.equal(plain.matvec(_dev(v), precision=prec), y16)   # a copy made when asked for
+        assert torch.equal(plain.matvec(_dev(v)), y)
         step = 1e-3 * v
         dl = g.back_substitute(_dev(step)).cpu().numpy().reshape(-1)
         rl = np.asarray(o.back_substitute(step)).reshape(-1)
