@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -312,8 +313,9 @@ void matvec(ba_system *s, const SchurArgs &a, const double *v, double *y) {
 constexpr int kSlotsOfSix = 178;
 
 // Chunks of a precision's product, made with its copy of the records (see build_system for
-// their number); without them the product takes the plan's.
-ba_status ensure_chunks(ba_system *s, int precision) {
+// their number); without them the product takes the plan's.  A failure leaves nothing of them,
+// nor any of the caller's workspace taken.
+ba_status ensure_chunks(ba_system *s, int precision) try {
     DevChunks &c = s->own_chunks[precision];
     if (s->own_slots == 0 || c.meta) return BA_OK;
     const HostPlan &P = s->plan;
@@ -328,6 +330,7 @@ ba_status ensure_chunks(ba_system *s, int precision) {
                      (int)std::min<int64_t>(4096, (P.n_tiles + resident - 1) / resident), 0, h);
     }
     uint32_t *meta = nullptr;   // set last: the chunks are taken when it is there
+    const size_t ws_used = s->ws_used;
     ba_status st;
     if ((st = supload(s, &c.chunk_tile, h.chunk_tile)) != BA_OK || (st = supload(s, &c.chunk_part, h.chunk_part)) != BA_OK ||
         (st = supload(s, &c.part_cam, h.part_cam)) != BA_OK || (st = supload(s, &c.part_dst, h.part_dst)) != BA_OK ||
@@ -336,6 +339,7 @@ ba_status ensure_chunks(ba_system *s, int precision) {
         (void)hipStreamSynchronize(s->stream);
         sfree(s, meta);
         free_chunks(s, c);
+        s->ws_used = ws_used;
         return st;
     }
     c.n_chunks = h.n_chunks;
@@ -344,6 +348,8 @@ ba_status ensure_chunks(ba_system *s, int precision) {
     c.meta = meta;
     if (!s->ws_counting) HIPCHK(hipStreamSynchronize(s->stream));   // h goes out of scope
     return BA_OK;
+} catch (const std::bad_alloc &) {
+    return fail(BA_ERR_NOMEM, "no host memory for the chunks of the S product");
 }
 
 ba_status ensure_precision(ba_system *s, int precision) {

@@ -54,3 +54,26 @@ def test_products_and_back_substitution(make):
     finally:
         plain.close()
         g.close()
+
+
+@pytest.mark.parametrize("prec,words", [("fp32", 24), ("bf16", 12)])
+def test_workspace_without_room_for_the_copys_chunks(prec, words):
+    """A copy made when asked for, in a workspace that has no room for its chunk arrays: the
+    product takes the FP64 product's chunks and nothing but the copy is taken."""
+    p = synth.walk_problem(n_cams=150, n_lms=26000, seed=4, name="walk150")
+    v = _dev(np.random.default_rng(7).standard_normal(9 * p.n_cams))
+    nbytes = ba.System.from_problem(p, size_only=True).ws_bytes
+    plain = ba.System.from_problem(p)
+    copy = plain.info()["n_tiles"] * 64 * words * 4
+    ws = torch.empty(nbytes + copy + 40_000, dtype=torch.uint8, device="cuda")
+    g = ba.System.from_problem(p, workspace=ws)
+    try:
+        used = g.workspace_used()
+        y = g.matvec(v, precision=prec)
+        assert used + copy <= g.workspace_used() < used + copy + 256
+        # the same partial products, added up over other chunks in FP64
+        yp = plain.matvec(v, precision=prec)
+        assert (y - yp).abs().max() <= 1e-12 * yp.abs().max()
+    finally:
+        plain.close()
+        g.close()
