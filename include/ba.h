@@ -83,8 +83,7 @@ typedef struct {
                                 the problem's size and the copies kept */
     int32_t explicit_schur;  /* also form S explicitly in 9x9 block-sparse rows (the paper's representation,
                                 Sec. 3.2 and 4.1); FP64 S products then read it instead of the Jacobians.
-                                Rows wider than one wavefront's LDS (251 blocks on gfx950) are assembled in
-                                pieces; BA_ERR_UNSUPPORTED only when a row's column list alone exceeds it */
+                                BA_ERR_UNSUPPORTED when a row has more than 40,797 blocks */
     int32_t max_tiles_multi; /* tiles per chunk of the multidirectional product; 0: max_tiles when that is
                                 set, else as many as make every chunk of the FP64 product resident at once */
     int32_t ws_groups;       /* caller-owned workspace only (ba_build_system_ws): the solves it reserves memory

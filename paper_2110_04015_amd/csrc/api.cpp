@@ -194,6 +194,7 @@ void free_all(ba_system *s) {
     sfree(s, s->seg_cam);
     sfree(s, s->seg_chunk);
     sfree(s, s->bsr_ptr);
+    sfree(s, s->bsr_pieces);
     sfree(s, s->bsr_col);
     sfree(s, s->bsr_val);
     if (s->host_pinned) (void)hipHostFree(s->host_pinned);
@@ -765,8 +766,8 @@ static ba_status apply_lambda(ba_system *s, const double *r) {
         (void)hipEventCreate(&e0);
         (void)hipEventCreate(&e1);
         if (e0) (void)hipEventRecord(e0, q);
-        launch_bsr_assemble(s->np, bsr_gather(s), s->cam_slot, s->cam_lmk, s->J64, s->vinv, s->Dblk, s->bsr_ptr, s->bsr_col,
-                            s->bsr_max_row, s->bsr_piece, s->bsr_val, q);
+        launch_bsr_assemble(bsr_gather(s), s->cam_slot, s->cam_lmk, s->J64, s->vinv, s->Dblk, s->bsr_ptr, s->bsr_pieces,
+                            s->bsr_n_pieces, s->bsr_col, s->bsr_val, q);
         if (e1) (void)hipEventRecord(e1, q);
         if (hipStreamSynchronize(q) == hipSuccess && e0 && e1) {
             float ms = 0.f;
@@ -1019,17 +1020,20 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
             return bail(fail(BA_ERR_HIP, "device attribute query failed"));
-        // rows wider than one wavefront's LDS are assembled in pieces
-        const int piece = bsr_assembly_piece(max_row, (size_t)lds_max);
-        if (piece < 1)
+        // the widest row supported: its column list and a block fit in a work-group's LDS
+        if ((size_t)max_row * sizeof(int32_t) + 81 * sizeof(double) >= (size_t)lds_max)
             return bail(fail(BA_ERR_UNSUPPORTED, "explicit S: a camera is covisible with " + std::to_string(max_row) +
                                                      " cameras, more than one work-group's LDS holds"));
         if ((size_t)((s->np + 31) / 32) * 4 > (size_t)lds_max)
             return bail(fail(BA_ERR_UNSUPPORTED, "explicit S: too many cameras for the pattern bitmap"));
         if ((st = supload(s, &s->bsr_ptr, rp)) != BA_OK) return bail(st);
         s->bsr_nnzb = (int64_t)rp[(size_t)s->np];
-        s->bsr_max_row = max_row;
-        s->bsr_piece = piece;
+        // (fewer than 2^32 threads in all: the blocks of so many pieces fit no device)
+        std::vector<int2> pieces;
+        for (int j = 0; j < s->np; ++j)
+            for (int b = 0; b < nnz[(size_t)j]; b += kBsrPiece) pieces.push_back(make_int2(j, b));
+        s->bsr_n_pieces = (int64_t)pieces.size();
+        if ((st = supload(s, &s->bsr_pieces, pieces)) != BA_OK) return bail(st);
         if ((st = salloc(s, &s->bsr_col, (size_t)std::max<int64_t>(s->bsr_nnzb, 1))) != BA_OK) return bail(st);
         if (!counting) launch_bsr_rowfill(s->np, bsr_gather(s), s->bsr_ptr, s->bsr_col, q);
         if ((st = salloc(s, &s->bsr_val, (size_t)s->bsr_nnzb * 81)) != BA_OK) return bail(st);

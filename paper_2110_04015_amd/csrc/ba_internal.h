@@ -220,8 +220,8 @@ struct ba_system {
     double *bp = nullptr;           // np * dp: b_p = J_p^T r0
     int64_t *obs_slot = nullptr;    // tile slot of every observation
     int32_t *bsr_slot_cam = nullptr;// explicit S: camera of every observation slot
-    int bsr_max_row = 0;
-    int bsr_piece = 0;              // explicit S: blocks of a row per assembly wavefront
+    int2 *bsr_pieces = nullptr;     // explicit S: row and first block of every assembly wavefront
+    int64_t bsr_n_pieces = 0;
     // solver scratch (allocated on demand)
     double *vec = nullptr;          // work vectors
     size_t vec_cap = 0;

@@ -10,8 +10,8 @@
 // (v_(col t))_c, which the products load once for all nine.
 //   S_jj = D(S)_j                                   (already formed by the build)
 //   S_jk = - sum_{l observed by j and k} W_jl V_l^-1 W_kl^T,   W_jl = J_p,jl^T J_l,jl
-// Assembly: one wavefront per block row j holds the row's blocks in LDS and adds the
-// row's contributions, 64 at a time, in a fixed order.
+// Assembly: one wavefront per kBsrPiece blocks of a row holds them in LDS and adds their
+// contributions, 64 at a time, in a fixed order.
 #include "ba_internal.h"
 #include "kernels.h"
 #include "dev_la.h"
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void k_bsr_rowfill(int nwords, const int64_t *
     }
 }
 
-// One wavefront per (block row j, piece p of at most `piece` of its blocks), the piece's
+// One wavefront per piece, at most kBsrPiece consecutive blocks of a block row j, the piece's
 // blocks in LDS.  It goes through camera j's observations o (of landmark l) 64 at a time and
 // queues the pairs (o, q) with the other observations q of l whose camera's block lies in the
 // piece; whenever 64 are queued, a lane takes each and adds -W_o V_l^-1 W_q^T = -J_p,o^T B
@@ -104,10 +104,11 @@ __global__ __launch_bounds__(256) void k_bsr_rowfill(int nwords, const int64_t *
 // is D(S)_j.
 // Bound by the latency of the scattered record loads, so pieces are small (many wavefronts per
 // compute unit, where a piece of all the blocks that LDS holds left one) and the lanes work on
-// queued pairs (with 8 blocks few of an observation's pairs are wanted).  A dense cap of 571
+// queued pairs (with 8 blocks few of an observation's pairs are wanted).  The pieces are
+// listed, so that a row takes no work-groups but its own however wide the widest row is.  A
+// dense cap of 571
 // cameras (897k observations, 257k blocks) 100 -> 16.5 ms, of 120 17.8 -> 2.8, 1,936
 // cameras along a walk 19.4 -> 8.0, a ring of 333 3.3 -> 1.4 (ba_set_lambda).
-constexpr int kBsrPiece = 8;
 __global__ __launch_bounds__(64) void k_bsr_assemble(const int64_t *__restrict__ cam_ptr,
                                                      const uint32_t *__restrict__ cam_slot,
                                                      const int32_t *__restrict__ cam_lmk,
@@ -117,17 +118,15 @@ __global__ __launch_bounds__(64) void k_bsr_assemble(const int64_t *__restrict__
                                                      const double *__restrict__ J64, const double *__restrict__ vinv,
                                                      const double *__restrict__ Dblk,
                                                      const int32_t *__restrict__ row_ptr,
-                                                     const int32_t *__restrict__ col, double *__restrict__ val,
-                                                     int piece, int pieces) {
+                                                     const int2 *__restrict__ pieces,
+                                                     const int32_t *__restrict__ col, double *__restrict__ val) {
     __shared__ double acc[kBsrPiece * 81];
     __shared__ int32_t rc[kBsrPiece];                 // the piece's columns, ascending
     __shared__ uint64_t queue[64 * (kBsrPiece + 1)];  // pairs: o << 6 | q, o in the camera order
-    const int j = blockIdx.x / pieces;
     const int lane = threadIdx.x;
+    const int j = pieces[blockIdx.x].x, pb = pieces[blockIdx.x].y;   // the row, the piece's first block in it
     const int b0 = row_ptr[j], nb = row_ptr[j + 1] - b0;
-    const int pb = (blockIdx.x - j * pieces) * piece;   // first block of this wavefront's piece
-    if (pb >= nb) return;
-    const int pn = min(piece, nb - pb);
+    const int pn = min(kBsrPiece, nb - pb);
     for (int e = lane; e < pn * 81; e += 64) acc[e] = 0.0;
     if (lane < pn) rc[lane] = col[b0 + pb + lane];
     auto lds_order = [] {
@@ -434,20 +433,11 @@ void launch_bsr_rowfill(int np, const BsrGather &g, const int32_t *row_ptr, int3
                        g.obs_lm, g.lmk_store, g.lmk_first_slot, g.lmk_count, g.slot_cam, row_ptr, col);
 }
 
-int bsr_assembly_piece(int max_row, size_t lds_bytes) {
-    const size_t cols = (size_t)max_row * sizeof(int32_t);
-    if (lds_bytes <= cols + 81 * sizeof(double)) return 0;
-    return (int)std::min<size_t>((size_t)max_row, (lds_bytes - cols) / (81 * sizeof(double)));
-}
-
-void launch_bsr_assemble(int np, const BsrGather &g, const uint32_t *cam_slot, const int32_t *cam_lmk,
-                         const double *J64, const double *vinv, const double *Dblk, const int32_t *row_ptr,
-                         const int32_t *col, int max_row, int piece, double *val, hipStream_t s) {
-    piece = std::min(piece, kBsrPiece);
-    const int pieces = (max_row + piece - 1) / piece;
-    hipLaunchKernelGGL(k_bsr_assemble, dim3((unsigned)np * (unsigned)pieces), dim3(64), 0, s, g.cam_ptr, cam_slot,
-                       cam_lmk, g.lmk_first_slot, g.lmk_count, g.slot_cam, J64, vinv, Dblk, row_ptr, col, val, piece,
-                       pieces);
+void launch_bsr_assemble(const BsrGather &g, const uint32_t *cam_slot, const int32_t *cam_lmk, const double *J64,
+                         const double *vinv, const double *Dblk, const int32_t *row_ptr, const int2 *pieces,
+                         int64_t n_pieces, const int32_t *col, double *val, hipStream_t s) {
+    hipLaunchKernelGGL(k_bsr_assemble, dim3((unsigned)n_pieces), dim3(64), 0, s, g.cam_ptr, cam_slot, cam_lmk,
+                       g.lmk_first_slot, g.lmk_count, g.slot_cam, J64, vinv, Dblk, row_ptr, pieces, col, val);
 }
 
 void launch_bsr_mv(int np, const int32_t *row_ptr, const int32_t *col, const double *val, const double *v, double *y,

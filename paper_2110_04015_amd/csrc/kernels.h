@@ -379,15 +379,13 @@ struct BsrGather {
 // nonzero blocks per block row; then the rows' columns (ascending) at row_ptr
 void launch_bsr_rowcount(int np, const BsrGather &g, int32_t *nnz, hipStream_t s);
 void launch_bsr_rowfill(int np, const BsrGather &g, const int32_t *row_ptr, int32_t *col, hipStream_t s);
-// blocks of a row that one wavefront of the assembly holds in lds_bytes of LDS (with the
-// row's column list); 0 when not even one fits
-int bsr_assembly_piece(int max_row, size_t lds_bytes);
+constexpr int kBsrPiece = 8;   // most blocks of a row that a wavefront of the assembly holds
 // block values (9 x 9, row-major per block); cam_slot, cam_lmk: tile slot and landmark storage
-// index of every observation of the camera order; `piece`: the most blocks of a row that a
-// wavefront may hold (bsr_assembly_piece)
-void launch_bsr_assemble(int np, const BsrGather &g, const uint32_t *cam_slot, const int32_t *cam_lmk,
-                         const double *J64, const double *vinv, const double *Dblk, const int32_t *row_ptr,
-                         const int32_t *col, int max_row, int piece, double *val, hipStream_t s);
+// index of every observation of the camera order; pieces: row and first block in it of every
+// kBsrPiece blocks of a row
+void launch_bsr_assemble(const BsrGather &g, const uint32_t *cam_slot, const int32_t *cam_lmk, const double *J64,
+                         const double *vinv, const double *Dblk, const int32_t *row_ptr, const int2 *pieces,
+                         int64_t n_pieces, const int32_t *col, double *val, hipStream_t s);
 // y = S v; with gram, row j also leaves gram[2 j] = y_j . v_j, gram[2 j + 1] = v_j . gram_r_j
 // (np partial pairs, see bsr_gram_blocks)
 void launch_bsr_mv(int np, const int32_t *row_ptr, const int32_t *col, const double *val, const double *v, double *y,

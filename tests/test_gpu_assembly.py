@@ -29,3 +29,26 @@ def test_assembled_rows(cams, lms, seen):
         assert torch.equal(g.matvec(torch.from_numpy(v).to("cuda")), y)
     finally:
         g.close()
+
+
+def test_one_camera_that_sees_all():
+    """One row as wide as S and 23,400 rows of ten blocks: with as many work-groups per row as the
+    widest one has pieces, the launch would take more than 2^32 threads."""
+    groups, rng = 2600, np.random.default_rng(8)
+    cams, lms = 9 * groups + 1, 8 * groups
+    assert cams * -(-cams // 8) * 64 > 2 ** 32
+    cam = np.concatenate([np.zeros((lms, 1), np.int64),
+                          1 + 9 * (np.arange(lms) // 8)[:, None] + np.arange(9)[None, :]], 1).reshape(-1)
+    m = cam.size
+    p = synth.Problem(name="star", seed=8, n_cams=cams, n_lms=lms, obs_cam=cam.astype(np.int32),
+                      obs_lm=np.repeat(np.arange(lms, dtype=np.int32), 10), J_p=rng.standard_normal((m, 2, 9)),
+                      J_l=rng.standard_normal((m, 2, 3)), r=rng.standard_normal((m, 2)), lam=1e-2)
+    g = ba.System.from_problem(p, explicit_schur=True)
+    try:
+        v = rng.standard_normal(9 * cams)
+        ref = oracle.System(p).matvec(v)
+        y = g.matvec(torch.from_numpy(v).to("cuda")).cpu().numpy()
+        for rows in (slice(0, 9), slice(9, None)):
+            assert np.abs(y[rows] - ref[rows]).max() <= 1e-12 * np.abs(ref[rows]).max()
+    finally:
+        g.close()
