@@ -253,13 +253,20 @@ __device__ __forceinline__ double next_direction(double z, double beta, double p
 
 // Software pipeline over the tiles of the chunk with two buffers: the record and
 // V^-1 of tile t + 1 and the slot word of tile t + 2 are requested before tile t
-// is processed, so a wavefront keeps up to two tiles of the stream in flight.
-template <int PREC, typename T, int DP>
+// is processed, so a wavefront keeps up to two tiles of the stream in flight.  PCG: the
+// product's vector is z - beta v.  A small problem's product lasts as long as its reads take
+// one after another, those of the arguments among them: 50 cameras 4.56 us, 4.72 with PCG's
+// test at run time, 4.80 with a test of its own as well for each of the reasons not to run.
+template <int PREC, typename T, int DP, bool PCG = false>
 __global__ __launch_bounds__(64) void k_schur1(SchurArgs a, const double *__restrict__ v) {
-    if (a.seg_skip && a.seg_skip[a.chunk_seg[blockIdx.x]]) return;
     extern __shared__ __align__(16) unsigned char smem[];
     // (the flag and beta are requested with the chunk's bounds)
-    const double done = a.done ? *a.done : 0.0, beta = a.z ? *a.beta : 0.0;
+    double done = 0.0;
+    if (a.done || a.seg_skip) {
+        if (a.seg_skip && a.seg_skip[a.chunk_seg[blockIdx.x]]) return;
+        if (a.done) done = *a.done;
+    }
+    const double beta = PCG ? *a.beta : 0.0;
     double *yloc = reinterpret_cast<double *>(smem);
     double *gloc = yloc + a.max_slots * DP;                                   // FP64: landmark rows
     T *vloc = reinterpret_cast<T *>(gloc + (PREC == 0 ? 3 * kTile : 0));
@@ -279,7 +286,7 @@ __global__ __launch_bounds__(64) void k_schur1(SchurArgs a, const double *__rest
     }
     for (int i = lane; i < ns * DP; i += kTile) {
         const int64_t k = (int64_t)a.part_cam[pb + i / DP] * DP + i % DP;
-        vloc[i] = (T)(a.z ? next_direction(a.z[k], beta, v[k]) : v[k]);
+        vloc[i] = (T)(PCG ? next_direction(a.z[k], beta, v[k]) : v[k]);
         yloc[i] = 0.0;
     }
     wave_sync();
@@ -411,26 +418,22 @@ __global__ __launch_bounds__(256) void k_reduce1(int np, const int32_t *__restri
     }
 }
 
+template <int PREC, typename T>
+static auto schur1_kernel(int dp, bool pcg) {
+    if (dp == 6) return pcg ? k_schur1<PREC, T, 6, true> : k_schur1<PREC, T, 6>;
+    return pcg ? k_schur1<PREC, T, 9, true> : k_schur1<PREC, T, 9>;
+}
+
 void launch_schur_chunks(const SchurArgs &a, const double *v, hipStream_t s) {
     if (a.n_chunks > 0) {
         // FP64 camera rows (and, for the FP64 product, landmark rows), v in the product precision
         const size_t esz = a.precision == 0 ? sizeof(double) : sizeof(float);
         const size_t lds = (size_t)(a.max_slots * a.dp + (a.precision == 0 ? 3 * kTile : 0)) * sizeof(double) +
                            (size_t)a.max_slots * a.dp * esz;
-        const dim3 g(a.n_chunks), b(kTile);
-        if (a.dp == 6) {
-            switch (a.precision) {
-                case 0: hipLaunchKernelGGL((k_schur1<0, double, 6>), g, b, lds, s, a, v); break;
-                case 1: hipLaunchKernelGGL((k_schur1<1, float, 6>), g, b, lds, s, a, v); break;
-                default: hipLaunchKernelGGL((k_schur1<2, float, 6>), g, b, lds, s, a, v); break;
-            }
-        } else {
-            switch (a.precision) {
-                case 0: hipLaunchKernelGGL((k_schur1<0, double, 9>), g, b, lds, s, a, v); break;
-                case 1: hipLaunchKernelGGL((k_schur1<1, float, 9>), g, b, lds, s, a, v); break;
-                default: hipLaunchKernelGGL((k_schur1<2, float, 9>), g, b, lds, s, a, v); break;
-            }
-        }
+        auto kernel = a.precision == 0   ? schur1_kernel<0, double>(a.dp, a.z)
+                      : a.precision == 1 ? schur1_kernel<1, float>(a.dp, a.z)
+                                         : schur1_kernel<2, float>(a.dp, a.z);
+        hipLaunchKernelGGL(kernel, dim3(a.n_chunks), dim3(kTile), lds, s, a, v);
     }
 }
 
