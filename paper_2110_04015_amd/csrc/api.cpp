@@ -63,13 +63,36 @@ void dfree(T *&p) {
     p = nullptr;
 }
 
+// What only makes a product faster is taken while the build runs, when ba_build_workspace_bytes
+// counts it, and from the device's memory, but not from what a caller's workspace has to spare:
+// that is for the solves and copies that it was made large enough for.
+bool may_take(const ba_system *s) { return !s->ws_base || s->building; }
+
+// Gives the two-pass product's copies of the records back (it then reads the tile stream).
+bool release_records(ba_system *s) {
+    bool any = false;
+    for (int p = 0; p < 3; ++p) any = any || s->multi.records[p];
+    if (!any || s->ws_base || s->ws_counting) return false;
+    (void)hipStreamSynchronize(s->stream);
+    for (int p = 0; p < 3; ++p) {
+        s->multi.no_room[p] = true;
+        dfree(s->multi.records[p]);
+    }
+    ++s->multi_serial;
+    return true;
+}
+
 // Device memory of a system: from the caller's workspace when it brought one (a bump
 // allocation, 256-byte aligned; BA_ERR_WORKSPACE when it is used up), else hipMalloc.  In
 // the sizing pass (ws_counting) nothing is allocated: the offsets are only counted and a
 // non-null stand-in address that nothing dereferences is returned.
 template <typename T>
 ba_status salloc(ba_system *s, T **p, size_t count) {
-    if (!s->ws_base && !s->ws_counting) return dalloc(p, count);
+    if (!s->ws_base && !s->ws_counting) {
+        ba_status st = dalloc(p, count);
+        if (st != BA_OK && release_records(s)) st = dalloc(p, count);
+        return st;
+    }
     *p = nullptr;
     if (count == 0) count = 1;
     const size_t bytes = count * sizeof(T);
@@ -383,12 +406,17 @@ ba_status ensure_precision(ba_system *s, int precision) {
 constexpr double kTwoPassRows = 5.0;
 
 // The two-pass product's camera-major records in a precision (the tile stream of that
-// precision must exist); fill_values renews those that were made.
+// precision must exist), where there is room for them; fill_values renews those that were made.
 ba_status ensure_records(ba_system *s, int precision) {
     DevMulti &m = s->multi;
-    if (!m.two_pass || m.records[precision]) return BA_OK;
-    ba_status st = salloc(s, &m.records[precision], (size_t)s->m * record_words(precision, s->dp) * 4);
-    if (st != BA_OK) return st;
+    if (!m.two_pass || m.records[precision] || m.no_room[precision] || !may_take(s)) return BA_OK;
+    const size_t words = (size_t)s->m * record_words(precision, s->dp) * 4;
+    if (s->ws_base || s->ws_counting) {
+        if (ba_status st = salloc(s, &m.records[precision], words); st != BA_OK) return st;
+    } else if (dalloc(&m.records[precision], words) != BA_OK) {
+        m.no_room[precision] = true;
+        return BA_OK;
+    }
     if (!s->ws_counting)
         launch_pair_records(s->m, precision, s->dp, s->cam_slot, tile_stream(s, precision), m.records[precision],
                             s->stream);
@@ -472,13 +500,14 @@ ba_status ensure_multi(ba_system *s, int N, int precision, bool plan = true) {
                                                                std::to_string(lds_rows) + " fit in LDS");
     };
     hipStream_t q = s->stream;
-    if (N <= kMaxBlock && s->plan.n_tiles * kTile <= (int64_t)UINT32_MAX && (double)mp.out_rows >= kTwoPassRows * (double)s->m) {
+    if (N <= kMaxBlock && s->plan.n_tiles * kTile <= (int64_t)UINT32_MAX &&
+        (double)mp.out_rows >= kTwoPassRows * (double)s->m && may_take(s)) {
         if (mp.tile_rows > lds_rows && (st = check_rows(multi_tile_outputs(s->plan, mp))) != BA_OK) return st;
-        if ((st = supload(s, &m.group, grp)) != BA_OK || (st = make_two_pass(s, mp)) != BA_OK) {
-            free_multi(s, m);
-            return st;
-        }
-        return ensure_records(s, precision);
+        if ((st = supload(s, &m.group, grp)) == BA_OK && (st = make_two_pass(s, mp)) == BA_OK)
+            return ensure_records(s, precision);
+        HIPCHK(hipStreamSynchronize(q));
+        free_multi(s, m);
+        if (st != BA_ERR_NOMEM) return st;   // (no device memory: the one-pass form may need less)
     }
     st = build_multi_chunks(s->plan, 512, mp, err);
     if (st != BA_OK) return fail(st, err);
@@ -888,6 +917,7 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
     s->ws_base = ws;
     s->ws_size = ws_bytes;
     s->ws_counting = counting;
+    s->building = true;
     if (hipGetDevice(&s->device) != hipSuccess) {
         delete s;
         return fail(BA_ERR_HIP, "no current HIP device");
@@ -1047,6 +1077,7 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
     if (!counting && (st = fill_values(s, d->J_p, d->J_l, d->r)) != BA_OK) return bail(st);
     if ((st = ensure_pinned(s)) != BA_OK) return bail(st);
     if ((ws || counting) && (st = reserve_solvers(s, opts)) != BA_OK) return bail(st);
+    s->building = false;
     *out = s;
     return BA_OK;
 }
@@ -2323,7 +2354,9 @@ ba_status ba_batch_mcg_solve(ba_batch *b, int32_t N, double tau, double *x, cons
     if (N > 1 && (st = ensure_multi(s, N, opts.precision)) != BA_OK) return st;
     const int inner_max = opts.precision == 0 ? opts.max_iter : std::min(opts.max_inner, opts.max_iter);
     const int64_t cap = opts.max_history_cols > 0 ? opts.max_history_cols : 1 + (int64_t)inner_max * N;
-    if ((st = ensure_batch_ws(b, N, cap)) != BA_OK) return st;
+    st = ensure_batch_ws(b, N, cap);
+    if (st == BA_ERR_NOMEM && release_records(s)) st = ensure_batch_ws(b, N, cap);
+    if (st != BA_OK) return st;
     const int B = b->B;
     std::vector<double> done_ms((size_t)B, 0.0), rel((size_t)B, 0.0);
     std::vector<int32_t> iters((size_t)B, 0), multis((size_t)B, 0), outer((size_t)B, 0), status((size_t)B, BA_MAXITER);

@@ -132,7 +132,9 @@ struct DevMulti {
     uint2 *pair_obs = nullptr;
     uint8_t *pair_grp = nullptr;
     double *pair_f = nullptr, *pair_h = nullptr, *pair_partial = nullptr;
-    uint32_t *records[3] = {nullptr, nullptr, nullptr};   // by precision, made when first asked for
+    // by precision, made when first asked for; without them the product reads the tile stream
+    uint32_t *records[3] = {nullptr, nullptr, nullptr};
+    bool no_room[3] = {false, false, false};              // there was no memory for them
 };
 
 // Plan construction (host, plan.cpp).  Returns BA_OK or an error with message.
@@ -244,6 +246,7 @@ struct ba_system {
     char *ws_base = nullptr;
     size_t ws_size = 0, ws_used = 0;
     bool ws_counting = false;       // sizing pass (ba_build_workspace_bytes): count, allocate nothing
+    bool building = false;          // the build takes what ba_build_workspace_bytes counts
     double *Ulr = nullptr;          // learned low-rank preconditioner term, n x 8 (row-major), or null
     int32_t *degree = nullptr;      // covisibility degree per camera (learned features)
     double *lr_proj = nullptr;      // kRedBlocks x 8 projections U^T r

@@ -848,6 +848,9 @@ __device__ __forceinline__ void pair_store(const double (&sh)[4][DP][64], int N,
 // (a landmark with more than 16 pairs takes further rounds), so the work follows the pairs
 // there are and not the number of subsets.  pair_obs: the observation's first pair entry and,
 // in y, its slot in that tile (bits 0..5) and its landmark's pairs (bits 8..14).
+// DIRECT: there is no room for camera-major records, and they are read from the tile stream
+// (a record's 16-byte words 64 words apart), to the same bits.  The product of the dense problem
+// above takes 310 us so in FP64 and 173 us with records, 188 / 134 us in FP32, 140 / 125 in BF16.
 
 // x of lane `AT` of the lane's row of 16, in every lane of the row (all lanes active)
 template <int AT>
@@ -876,7 +879,7 @@ __device__ __forceinline__ void pair_terms(const float (&x)[2], float f0, float 
 // (six 1 KB loads for four observations), 79 us so; 111 us with a column per lane and the
 // records in scalar registers, the terms of the subsets that do not see a landmark being work
 // too.
-template <int PREC, typename T, int DP>
+template <int PREC, typename T, int DP, bool DIRECT>
 __global__ __launch_bounds__(256) void k_pair_out(MultiArgs a, const void *__restrict__ records,
                                                   const uint2 *__restrict__ obs, const T *__restrict__ F,
                                                   const PairH<T> *__restrict__ H, double *__restrict__ partial) {
@@ -892,7 +895,9 @@ __global__ __launch_bounds__(256) void k_pair_out(MultiArgs a, const void *__res
     if (a.seg_skip && a.seg_skip[a.cam_seg[me.c]]) return;
     const int lo = me.lo, hi = me.hi;
     const int own = a.group[me.c];
-    const uint32_t *rec = reinterpret_cast<const uint32_t *>(records) + me.b0 * kRecWords + (i < kLanes ? i : 0) * kPairWords;
+    const int e = (i < kLanes ? i : 0) * kPairWords;   // the lane's first 4-byte word of a record
+    const uint32_t *rec = reinterpret_cast<const uint32_t *>(records) +
+                          (DIRECT ? (e & ~3) * kTile + (e & 3) : me.b0 * kRecWords + e);
     obs += me.b0;
 #pragma unroll
     for (int k = 0; k < DP; ++k) sh[w][k][lane] = 0.0;
@@ -908,7 +913,8 @@ __global__ __launch_bounds__(256) void k_pair_out(MultiArgs a, const void *__res
     auto load = [&](int j, const uint2 &d, Group &g) {
         const int at = min(j + o, hi - 1);
         const uint32_t slot = (d.x & ~63u) | (d.y & 63u);
-        const uint32_t *r = rec + (int64_t)at * kRecWords;
+        const uint32_t *r = rec + (DIRECT ? (int64_t)(slot >> 6) * (kRecWords * kTile) + (slot & 63u) * 4
+                                          : (int64_t)at * kRecWords);
         const uint32_t *f = reinterpret_cast<const uint32_t *>(F + (int64_t)slot * 2);
         if constexpr (PREC == 1) {
             g.x = *reinterpret_cast<const uint2 *>(i == 15 ? f : r);
@@ -989,7 +995,7 @@ __device__ __forceinline__ double row_bcast(double x) {
 // 15, and DPP hands them to the row; the pairs' f go to their columns through LDS (98 us on
 // the problem above; with f formed per column from gathered h 112 us, a column per lane with
 // FMAs and scalar loads 141 us).
-template <int DP, int NT>
+template <int DP, int NT, bool DIRECT>
 __global__ __launch_bounds__(256) void k_pair_out_mfma(MultiArgs a, const double *__restrict__ records,
                                                        const uint2 *__restrict__ obs,
                                                        const double *__restrict__ F,
@@ -1006,8 +1012,9 @@ __global__ __launch_bounds__(256) void k_pair_out_mfma(MultiArgs a, const double
     const int lo = me.lo, hi = me.hi;
     const int own = a.group[me.c];
     // record values of the lane: J_p row 0 (i < DP), then J_l; J_p row 1; lane 15: F
-    const double *rec0 = records + me.b0 * NV + (i < DP ? i : i < DP + 6 ? DP + i : 0);
-    const double *rec1 = records + me.b0 * NV + DP + (i < DP ? i : 0);
+    const int e0 = i < DP ? i : i < DP + 6 ? DP + i : 0, e1 = DP + (i < DP ? i : 0);
+    const double *rec0 = records + (DIRECT ? (e0 & ~1) * kTile + (e0 & 1) : me.b0 * NV + e0);
+    const double *rec1 = records + (DIRECT ? (e1 & ~1) * kTile + (e1 & 1) : me.b0 * NV + e1);
     obs += me.b0;
     double (*fc)[2][16 * NT] = fsh[w];
 #pragma unroll
@@ -1024,8 +1031,9 @@ __global__ __launch_bounds__(256) void k_pair_out_mfma(MultiArgs a, const double
     };
     auto words = [&](int j) { return obs[min(j + o, hi - 1)]; };
     auto load = [&](int j, const uint2 &d, Group &g) {
-        const int64_t at = (int64_t)min(j + o, hi - 1) * NV;
-        const double *fp = F + (int64_t)((d.x & ~63u) | (d.y & 63u)) * 2;
+        const uint32_t slot = (d.x & ~63u) | (d.y & 63u);
+        const int64_t at = DIRECT ? (int64_t)(slot >> 6) * (NV * kTile) + (slot & 63u) * 2 : (int64_t)min(j + o, hi - 1) * NV;
+        const double *fp = F + (int64_t)slot * 2;
         g.x0 = *(i == 15 ? fp : rec0 + at);
         g.x1 = *(i == 15 ? fp + 1 : rec1 + at);
         g.cnt = j + o < hi ? (int)(d.y >> 8) : 0;   // past the share: no pair, so f = 0
@@ -1096,17 +1104,17 @@ __global__ __launch_bounds__(256) void k_pair_out_mfma(MultiArgs a, const double
     pair_store<DP>(sh, a.N, partial);
 }
 
-template <int DP>
-static void launch_pair_out_mfma(const MultiArgs &a, hipStream_t s) {
+template <int DP, bool DIRECT>
+static void launch_pair_out_mfma(const MultiArgs &a, const void *records, hipStream_t s) {
     const dim3 g((unsigned)a.n_blocks), b(256);
-    const double *rec = reinterpret_cast<const double *>(a.records);
+    const double *rec = reinterpret_cast<const double *>(records);
     const double *F = reinterpret_cast<const double *>(a.pair_f);
     const PairH<double> *H = reinterpret_cast<const PairH<double> *>(a.pair_h);
     switch ((a.N + 15) / 16) {
-    case 1: hipLaunchKernelGGL((k_pair_out_mfma<DP, 1>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial); break;
-    case 2: hipLaunchKernelGGL((k_pair_out_mfma<DP, 2>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial); break;
-    case 3: hipLaunchKernelGGL((k_pair_out_mfma<DP, 3>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial); break;
-    default: hipLaunchKernelGGL((k_pair_out_mfma<DP, 4>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial);
+    case 1: hipLaunchKernelGGL((k_pair_out_mfma<DP, 1, DIRECT>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial); break;
+    case 2: hipLaunchKernelGGL((k_pair_out_mfma<DP, 2, DIRECT>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial); break;
+    case 3: hipLaunchKernelGGL((k_pair_out_mfma<DP, 3, DIRECT>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial); break;
+    default: hipLaunchKernelGGL((k_pair_out_mfma<DP, 4, DIRECT>), g, b, 0, s, a, rec, a.pair_obs, F, H, a.pair_partial);
     }
 }
 
@@ -1172,15 +1180,21 @@ void launch_pair_obs(int64_t m, const uint32_t *cam_slot, const uint32_t *mmeta,
     hipLaunchKernelGGL(k_pair_obs, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, m, cam_slot, mmeta, obs);
 }
 
+template <int PREC, typename T, int DP, bool DIRECT>
+static void launch_pair_out(const MultiArgs &a, const void *records, hipStream_t s) {
+    if constexpr (PREC == 0)
+        launch_pair_out_mfma<DP, DIRECT>(a, records, s);
+    else
+        hipLaunchKernelGGL((k_pair_out<PREC, T, DP, DIRECT>), dim3((unsigned)a.n_blocks), dim3(256), 0, s, a, records,
+                           a.pair_obs, reinterpret_cast<const T *>(a.pair_f),
+                           reinterpret_cast<const PairH<T> *>(a.pair_h), a.pair_partial);
+}
+
 template <int PREC, typename T, int DP>
 static void launch_two_pass(const MultiArgs &a, const double *z, double *Y, hipStream_t s) {
     hipLaunchKernelGGL((k_pair_h<PREC, T, DP>), dim3((unsigned)((a.n_tiles + 3) / 4)), dim3(256), 0, s, a, z);
-    if constexpr (PREC == 0)
-        launch_pair_out_mfma<DP>(a, s);
-    else
-        hipLaunchKernelGGL((k_pair_out<PREC, T, DP>), dim3((unsigned)a.n_blocks), dim3(256), 0, s, a, a.records,
-                           a.pair_obs, reinterpret_cast<const T *>(a.pair_f),
-                           reinterpret_cast<const PairH<T> *>(a.pair_h), a.pair_partial);
+    if (a.records) launch_pair_out<PREC, T, DP, false>(a, a.records, s);
+    else launch_pair_out<PREC, T, DP, true>(a, a.J, s);
     hipLaunchKernelGGL(k_pair_reduce<DP>, dim3((unsigned)(a.np * DP)), dim3(256), 0, s, a, a.pair_partial, z, Y);
 }
 

@@ -205,7 +205,7 @@ struct MultiArgs {
     const int32_t *cam_blk = nullptr;         // [np + 1] camera -> its first work-group
     const int64_t *cam_obs_ptr = nullptr;     // [np + 1] camera -> range of the camera order
     const int32_t *tile_seg = nullptr;        // batches: tile -> problem
-    const void *records = nullptr;            // camera-major records in the product's precision
+    const void *records = nullptr;            // camera-major records in the product's precision (nullable: J is read)
     const uint2 *pair_obs = nullptr;          // camera-major observation words
     const uint8_t *pair_grp = nullptr;        // 64 tile + pair -> subset
     void *pair_f = nullptr, *pair_h = nullptr;  // own terms per slot, h and subset per pair

@@ -3,7 +3,8 @@
 The problems are dense enough for the two-pass form (five subsets or more among a landmark's
 observers, on average), at the edges of its work split: one to four tiles of 16 columns and
 their remainders, landmarks with more pairs than a row of 16 lanes, cameras with one work-group
-and with several, both pose dimensions, new values in place, and the skipped problems of a batch.
+and with several, both pose dimensions, new values in place, the skipped problems of a batch, and
+systems without room for camera-major records.
 """
 import numpy as np
 import pytest
@@ -40,10 +41,10 @@ def mean_subsets(p, N):
     return float(np.bincount(pairs // 64, minlength=p.n_lms)[p.obs_lm].mean())
 
 
-def check(p, g, o, N, z, tag):
+def check(p, g, o, N, z, tag, precisions=("fp64", "fp32", "bf16")):
     dp = p.d_p
     grp = np.repeat(oracle.partition(p.n_cams, N), dp)
-    for prec in ("fp64", "fp32", "bf16"):
+    for prec in precisions:
         Y = _h(g.matmat_grouped(N, _dev(z), precision=prec))
         assert np.array_equal(Y, _h(g.matmat_grouped(N, _dev(z), precision=prec))), (tag, prec)
         for q in range(N):
@@ -88,3 +89,43 @@ def test_batch_skips_and_layout_change():
             assert s.multi_steps == so.multi_steps
             assert np.linalg.norm(_h(xi) - xo) <= 1e-9 * np.linalg.norm(xo), (win, other)
     b.close()
+
+
+@pytest.mark.parametrize("name,N", [("cap70", 17), ("ring64", 64), ("dp6", 47)])
+def test_without_room_for_records(name, N):
+    """The product reads the tile stream then, to the same bits: after a solve whose history fits no
+    device, and for a copy that is made in a workspace with room for the copy alone."""
+    p = problem(name)
+    g = ba.System.from_problem(p)
+    z = _dev(np.random.default_rng(N).standard_normal(g.n))
+    ref = {}
+    for prec in ("fp64", "fp32", "bf16"):
+        ref[prec] = g.matmat_grouped(N, z, precision=prec)
+    with pytest.raises(ba.BAError) as e:
+        g.mcg(N, 3.3, max_history_cols=2 ** 31 - 1)
+    assert e.value.status == ba.BA_ERR_NOMEM
+    for prec, y in ref.items():
+        assert torch.equal(g.matmat_grouped(N, z, precision=prec), y), prec
+    tiles = g.info()["n_tiles"]
+    g.close()
+    kw = dict(ws_groups=N, ws_max_iter=2)
+    nbytes = ba.System.from_problem(p, size_only=True, **kw).ws_bytes
+    for prec, words in (("fp32", 24), ("bf16", 12)):
+        copy = tiles * 64 * words * 4
+        ws = torch.empty(nbytes + copy, dtype=torch.uint8, device="cuda")
+        g = ba.System.from_problem(p, workspace=ws, **kw)
+        assert torch.equal(g.matmat_grouped(N, z, precision=prec), ref[prec]), prec
+        assert torch.equal(g.matmat_grouped(N, z), ref["fp64"]), prec
+        g.close()
+
+
+def test_first_use_in_a_workspace():
+    """Subsets that no layout was reserved for take no records from the caller's workspace."""
+    p = synth.cap_problem(n_cams=24, n_lms=60000, seed=14, name="cap24")
+    N = 12
+    assert mean_subsets(p, N) >= 5.0
+    nbytes = ba.System.from_problem(p, size_only=True).ws_bytes
+    ws = torch.empty(nbytes + 24 * 8 * p.n_obs, dtype=torch.uint8, device="cuda")
+    g = ba.System.from_problem(p, workspace=ws)
+    check(p, g, oracle.System(p), N, np.random.default_rng(N).standard_normal(g.n), "cap24", ("fp64",))
+    g.close()
