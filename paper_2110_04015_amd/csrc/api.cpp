@@ -336,12 +336,12 @@ void matvec(ba_system *s, const SchurArgs &a, const double *v, double *y) {
 // slots whose FP64 camera rows (two of 72 bytes each, and 1.5 KB) fit six times in 160 KiB
 constexpr int kSlotsOfSix = 178;
 
-// Chunks of a precision's product, made with its copy of the records (see build_system for
-// their number); without them the product takes the plan's.  A failure leaves nothing of them,
-// nor any of the caller's workspace taken.
+// Chunks of a precision's product, made with its copy of the records where they may be (see
+// build_system for their number); without them the product takes the plan's.  A failure leaves
+// nothing of them.
 ba_status ensure_chunks(ba_system *s, int precision) try {
     DevChunks &c = s->own_chunks[precision];
-    if (s->own_slots == 0 || c.meta) return BA_OK;
+    if (s->own_slots == 0 || c.meta || !may_take(s)) return BA_OK;
     const HostPlan &P = s->plan;
     HostChunks h;
     if (precision == 1) {
@@ -354,7 +354,6 @@ ba_status ensure_chunks(ba_system *s, int precision) try {
                      (int)std::min<int64_t>(4096, (P.n_tiles + resident - 1) / resident), 0, h);
     }
     uint32_t *meta = nullptr;   // set last: the chunks are taken when it is there
-    const size_t ws_used = s->ws_used;
     ba_status st;
     if ((st = supload(s, &c.chunk_tile, h.chunk_tile)) != BA_OK || (st = supload(s, &c.chunk_part, h.chunk_part)) != BA_OK ||
         (st = supload(s, &c.part_cam, h.part_cam)) != BA_OK || (st = supload(s, &c.part_dst, h.part_dst)) != BA_OK ||
@@ -363,7 +362,6 @@ ba_status ensure_chunks(ba_system *s, int precision) try {
         (void)hipStreamSynchronize(s->stream);
         sfree(s, meta);
         free_chunks(s, c);
-        s->ws_used = ws_used;
         return st;
     }
     c.n_chunks = h.n_chunks;

@@ -77,3 +77,27 @@ def test_workspace_without_room_for_the_copys_chunks(prec, words):
     finally:
         plain.close()
         g.close()
+
+
+@pytest.mark.parametrize("prec,words", [("fp32", 24), ("bf16", 12)])
+def test_copy_takes_nothing_else_from_a_workspaces_spare_room(prec, words):
+    """A copy made when asked for, in a workspace with room for its chunk arrays as well: they were
+    not counted, so what is left is for what the caller has in mind (a solve of its own, here)."""
+    p = synth.walk_problem(n_cams=150, n_lms=26000, seed=4, name="walk150")
+    v = _dev(np.random.default_rng(7).standard_normal(9 * p.n_cams))
+    nbytes = ba.System.from_problem(p, size_only=True, ws_groups=1, ws_max_iter=300).ws_bytes
+    plain = ba.System.from_problem(p)
+    copy = plain.info()["n_tiles"] * 64 * words * 4
+    # (vectors that the solve needs longer are taken anew: some kilobytes, a tenth of the chunk arrays at most)
+    ws = torch.empty(nbytes + copy + 65536, dtype=torch.uint8, device="cuda")
+    g = ba.System.from_problem(p, workspace=ws)
+    try:
+        used = g.workspace_used()
+        g.matvec(v, precision=prec)
+        assert used + copy <= g.workspace_used() < used + copy + 256
+        x, st = g.mcg(1, 3.3, max_iter=300)
+        y, su = plain.mcg(1, 3.3, max_iter=300)
+        assert torch.equal(x, y) and st.iterations == su.iterations
+    finally:
+        plain.close()
+        g.close()
