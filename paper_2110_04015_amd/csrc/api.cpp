@@ -181,7 +181,6 @@ void free_all(ba_system *s) {
     sfree(s, s->Vraw);
     sfree(s, s->Uraw);
     sfree(s, s->bp);
-    sfree(s, s->obs_slot);
     sfree(s, s->bsr_slot_cam);
     sfree(s, s->meta);
     sfree(s, s->tile_lmk_base);
@@ -189,7 +188,6 @@ void free_all(ba_system *s) {
     sfree(s, s->chunk_part);
     sfree(s, s->part_cam);
     sfree(s, s->cam_part_ptr);
-    sfree(s, s->cam_part_idx);
     sfree(s, s->part_dst);
     sfree(s, s->partial);
     for (DevChunks &c : s->own_chunks) free_chunks(s, c);
@@ -982,16 +980,12 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
     if ((st = salloc(s, &s->Vraw, (size_t)s->nl * 6)) != BA_OK) return bail(st);
     if ((st = salloc(s, &s->Uraw, (size_t)s->np * (d->d_p * (d->d_p + 1) / 2))) != BA_OK) return bail(st);
     if ((st = salloc(s, &s->bp, (size_t)s->np * d->d_p)) != BA_OK) return bail(st);
-    // tile slot of every observation (the lambda kernels read the packed stream by it)
-    if ((st = salloc(s, &s->obs_slot, (size_t)m)) != BA_OK) return bail(st);
-    if (!counting) launch_obs_slots(nslots, s->slot_obs, s->obs_slot, q);
     if ((st = supload(s, &s->meta, P.meta)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->tile_lmk_base, P.tile_lmk_base)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->chunk_tile, P.chunk_tile)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->chunk_part, P.chunk_part)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->part_cam, P.part_cam)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->cam_part_ptr, P.cam_part_ptr)) != BA_OK) return bail(st);
-    if ((st = supload(s, &s->cam_part_idx, P.cam_part_idx)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->part_dst, P.part_dst)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->lmk_order, P.lmk_order)) != BA_OK) return bail(st);
     if ((st = supload(s, &s->lmk_first_slot, P.lmk_first_slot)) != BA_OK) return bail(st);
@@ -1071,8 +1065,13 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
     if (max_tiles == 0 && !cam_seg && few > 0 && P.n_tiles > few) s->own_slots = opts && opts->max_slots ? opts->max_slots : -1;
     if (opts && opts->store_fp32 && (st = ensure_chunks(s, 1)) != BA_OK) return bail(st);
     if (opts && opts->store_bf16 && (st = ensure_chunks(s, 2)) != BA_OK) return bail(st);
-    if (!counting) launch_cam_slots(m, s->cam_obs, s->obs_slot, s->obs_lm, s->lmk_store, s->cam_slot, s->cam_lmk, q);
-    if (!counting && (st = fill_values(s, d->J_p, d->J_l, d->r)) != BA_OK) return bail(st);
+    if (!counting) {
+        // the observations' tile slots, in the memory of the tile stream that is written next
+        int64_t *obs_slot = reinterpret_cast<int64_t *>(s->J64);
+        launch_obs_slots(nslots, s->slot_obs, obs_slot, q);
+        launch_cam_slots(m, s->cam_obs, obs_slot, s->obs_lm, s->lmk_store, s->cam_slot, s->cam_lmk, q);
+        if ((st = fill_values(s, d->J_p, d->J_l, d->r)) != BA_OK) return bail(st);
+    }
     if ((st = ensure_pinned(s)) != BA_OK) return bail(st);
     if ((ws || counting) && (st = reserve_solvers(s, opts)) != BA_OK) return bail(st);
     s->building = false;

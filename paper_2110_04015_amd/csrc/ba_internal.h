@@ -192,7 +192,7 @@ struct ba_system {
     uint32_t *meta = nullptr;
     int32_t *tile_lmk_base = nullptr;
     int32_t *chunk_tile = nullptr, *chunk_part = nullptr, *part_cam = nullptr;
-    int32_t *cam_part_ptr = nullptr, *cam_part_idx = nullptr, *part_dst = nullptr;
+    int32_t *cam_part_ptr = nullptr, *part_dst = nullptr;
     double *partial = nullptr;      // n_part * 9, camera-major
     ba::DevChunks own_chunks[3];    // by precision; without a meta: those above
     int own_slots = 0;              // cameras per such chunk (-1: chosen by precision; 0: none are made)
@@ -220,7 +220,6 @@ struct ba_system {
     double *Vraw = nullptr;         // nl * 6: undamped J_l^T J_l (storage order)
     double *Uraw = nullptr;         // np * dp (dp + 1) / 2: undamped J_p^T J_p, packed upper triangle
     double *bp = nullptr;           // np * dp: b_p = J_p^T r0
-    int64_t *obs_slot = nullptr;    // tile slot of every observation
     int32_t *bsr_slot_cam = nullptr;// explicit S: camera of every observation slot
     int2 *bsr_pieces = nullptr;     // explicit S: row and first block of every assembly wavefront
     int64_t bsr_n_pieces = 0;

@@ -72,3 +72,19 @@ def test_workspace_build_equals_library_build(name, explicit):
     g.close()
     ref.close()
     del ws
+
+
+def test_memory_per_observation():
+    """What a system keeps is what its kernels read: per tile slot the FP64 record, the observation
+    and the slot word; per observation its places in the camera order; and the sums and tables of
+    landmarks, cameras and chunks.  A map of eight bytes per observation would be 4.8 MB more."""
+    p = synth.ring_problem(n_cams=64, n_lms=10_000, c_lo=60, c_hi=60, seed=5)
+    g = ba.System.from_problem(p)
+    info = g.info()
+    g.close()
+    slots, m = 64 * info["n_tiles"], p.n_obs
+    blocks = m // 256 + p.n_cams
+    kept = (slots * (24 * 8 + 8 + 4) + m * (8 + 4 + 4 + 4) + p.n_lms * (18 * 8 + 4 + 4 + 8 + 4) +
+            info["n_chunks"] * p.n_cams * (9 * 8 + 4 + 4) + blocks * (108 * 8 + 12))
+    nbytes = ba.System.from_problem(p, size_only=True).ws_bytes
+    assert nbytes <= kept + 1_000_000   # cameras' blocks, a PCG solve's vectors, alignment
