@@ -1149,21 +1149,23 @@ __global__ __launch_bounds__(256) void k_pair_reduce(MultiArgs a, const double *
 }
 
 // Camera-major copy of the tile stream: 16-byte word q of the i-th observation of the
-// camera order goes to word i kw + q (consecutive threads take consecutive words).
+// camera order goes to word i kw + q (consecutive threads take consecutive words; a thread
+// takes several where there are more words than a launch has threads).
 __global__ __launch_bounds__(256) void k_pair_records(int64_t m, int kw, const uint32_t *__restrict__ cam_slot,
                                                       const u32x4_t *__restrict__ J, u32x4_t *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= m * kw) return;
-    const int64_t o = i / kw;
-    const int q = (int)(i - o * kw);
-    const int64_t s = cam_slot[o];
-    out[i] = J[(s / kTile * kw + q) * kTile + s % kTile];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < m * kw; i += (int64_t)gridDim.x * 256) {
+        const int64_t o = i / kw;
+        const int q = (int)(i - o * kw);
+        const int64_t s = cam_slot[o];
+        out[i] = J[(s / kTile * kw + q) * kTile + s % kTile];
+    }
 }
 
 void launch_pair_records(int64_t m, int precision, int dp, const uint32_t *cam_slot, const void *J, void *out,
                          hipStream_t s) {
     const int kw = record_words(precision, dp);
-    hipLaunchKernelGGL(k_pair_records, dim3((unsigned)((m * kw + 255) / 256)), dim3(256), 0, s, m, kw, cam_slot,
+    const int64_t blocks = std::min<int64_t>((m * kw + 255) / 256, 1 << 23);
+    hipLaunchKernelGGL(k_pair_records, dim3((unsigned)blocks), dim3(256), 0, s, m, kw, cam_slot,
                        reinterpret_cast<const u32x4_t *>(J), reinterpret_cast<u32x4_t *>(out));
 }
 
