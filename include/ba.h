@@ -321,7 +321,8 @@ ba_status ba_profile_read(ba_system *sys, double *ms_total, int64_t *launches, i
 /* HOST-ONLY check of the HBM layout plan (no GPU needed): plans the layout of
  * the host index arrays cam, lm [n_obs] exactly as ba_build_system does, and the
  * layout of the multidirectional product for each N in Ns[n_Ns] (host), then
- * checks every invariant the kernels index by.  stats (host, nullable,
+ * checks every invariant the kernels index by; with max_tiles = 0 also those of
+ * layouts by shares of the tiles and of the copies' chunks.  stats (host, nullable,
  * 4 + 3 n_Ns entries): tiles, chunks, partial rows, largest chunk slot count,
  * then per N: chunks, (camera, subset) partial rows, largest chunk out count.
  * Returns BA_OK, the planner's error, or BA_ERR_INVALID_ARG with

@@ -21,6 +21,85 @@ bool bad(const char *what, int64_t a = 0, int64_t b = 0) {
     return false;
 }
 
+// Chunks of the plan's tiles (its own, or those of a copy of the Jacobian stream).
+bool check_chunks(const HostPlan &P, const HostChunks &C, int max_slots, const int32_t *cam) {
+    const int64_t T = P.n_tiles;
+    if ((int64_t)C.meta.size() != T * kTile) return bad("chunk meta size");
+    if ((int)C.chunk_tile.size() != C.n_chunks + 1 || C.chunk_tile[0] != 0 || C.chunk_tile[(size_t)C.n_chunks] != T ||
+        (int)C.chunk_part.size() != C.n_chunks + 1 || C.chunk_part[(size_t)C.n_chunks] != C.n_part ||
+        (int64_t)C.part_cam.size() != C.n_part)
+        return bad("chunk tile ranges");
+    int max_used = 0;
+    for (int ch = 0; ch < C.n_chunks; ++ch) {
+        int t0 = C.chunk_tile[(size_t)ch], t1 = C.chunk_tile[(size_t)ch + 1];
+        if (t1 <= t0 || t1 - t0 > C.max_tiles) return bad("chunk tile count", ch, t1 - t0);
+        int pb = C.chunk_part[(size_t)ch], ns = C.chunk_part[(size_t)ch + 1] - pb;
+        if (ns < 1 || ns > max_slots) return bad("chunk slot count", ch, ns);
+        if (ns > max_used) max_used = ns;
+        std::vector<int> used((size_t)ns, 0);
+        for (int64_t s = (int64_t)t0 * kTile; s < (int64_t)t1 * kTile; ++s) {
+            if (C.meta[(size_t)s] >> 16 != P.meta[(size_t)s] >> 16) return bad("chunk landmark index", ch, s);
+            if (C.meta[(size_t)s] == kPad) continue;
+            int slot = (int)(C.meta[(size_t)s] & 0xFFFFu);
+            if (slot >= ns) return bad("slot beyond chunk", ch, slot);
+            if (C.part_cam[(size_t)(pb + slot)] != cam[P.slot_obs[(size_t)s]]) return bad("slot camera", ch, slot);
+            used[(size_t)slot] = 1;
+        }
+        for (int k = 0; k < ns; ++k)
+            if (!used[(size_t)k]) return bad("unused slot", ch, k);
+    }
+    if (C.max_used_slots != max_used) return bad("largest chunk", C.max_used_slots, max_used);
+    // camera CSR over partial rows
+    if ((int64_t)C.cam_part_idx.size() != C.n_part || C.cam_part_ptr[0] != 0 || C.cam_part_ptr[(size_t)P.np] != C.n_part)
+        return bad("partial CSR size");
+    for (int c = 0; c < P.np; ++c) {
+        for (int j = C.cam_part_ptr[(size_t)c]; j < C.cam_part_ptr[(size_t)c + 1]; ++j) {
+            int row = C.cam_part_idx[(size_t)j];
+            if (row < 0 || row >= C.n_part || C.part_cam[(size_t)row] != c) return bad("partial CSR row", c, row);
+            if (j > C.cam_part_ptr[(size_t)c] && row <= C.cam_part_idx[(size_t)j - 1]) return bad("CSR order", c, j);
+            if (C.part_dst[(size_t)row] != j) return bad("partial destination", row, j);
+        }
+    }
+    return true;
+}
+
+// Camera-major order: every observation once, each camera's in slot order, and the work-groups
+// of up to kCamObs of them.
+bool check_cameras(const HostPlan &P, const int32_t *cam) {
+    std::vector<int64_t> slot((size_t)P.m);
+    for (int64_t s = 0; s < P.n_tiles * kTile; ++s)
+        if (P.slot_obs[(size_t)s] >= 0) slot[(size_t)P.slot_obs[(size_t)s]] = s;
+    const int nb = (int)P.blk_cam.size();
+    if ((int64_t)P.cam_obs.size() != P.m || P.cam_obs_ptr[0] != 0 || P.cam_obs_ptr[(size_t)P.np] != P.m ||
+        P.cam_blk[0] != 0 || P.cam_blk[(size_t)P.np] != nb)
+        return bad("camera order size");
+    for (int c = 0; c < P.np; ++c) {
+        const int64_t a = P.cam_obs_ptr[(size_t)c], b = P.cam_obs_ptr[(size_t)c + 1];
+        for (int64_t i = a; i < b; ++i) {
+            const int64_t o = P.cam_obs[(size_t)i];
+            if (o < 0 || o >= P.m || cam[o] != c) return bad("camera of an observation", c, o);
+            if (i > a && slot[(size_t)o] <= slot[(size_t)P.cam_obs[(size_t)i - 1]]) return bad("slot order", c, i);
+        }
+        const int b0 = P.cam_blk[(size_t)c], b1 = P.cam_blk[(size_t)c + 1];
+        if (b1 - b0 != (b - a + kCamObs - 1) / kCamObs) return bad("camera work-groups", c, b1 - b0);
+        for (int k = b0; k < b1; ++k)
+            if (P.blk_cam[(size_t)k] != c) return bad("work-group camera", k, c);
+    }
+    std::vector<int> seen((size_t)nb, 0);
+    int64_t last = -1;
+    if ((int)P.blk_order.size() != nb) return bad("work-group order size");
+    for (int i = 0; i < nb; ++i) {
+        const int b = P.blk_order[(size_t)i];
+        if (b < 0 || b >= nb || seen[(size_t)b]++) return bad("work-group order", i, b);
+        const int c = P.blk_cam[(size_t)b];
+        const int64_t first = P.cam_obs_ptr[(size_t)c] + (int64_t)(b - P.cam_blk[(size_t)c]) * kCamObs;
+        const int64_t s = slot[(size_t)P.cam_obs[(size_t)first]];
+        if (s < last) return bad("work-groups by first slot", i, b);
+        last = s;
+    }
+    return true;
+}
+
 bool check_plan(const HostPlan &P, const int32_t *cam, const int32_t *lm) {
     const int64_t T = P.n_tiles;
     if ((int64_t)P.slot_obs.size() != T * kTile || (int64_t)P.meta.size() != T * kTile) return bad("slot arrays");
@@ -56,39 +135,7 @@ bool check_plan(const HostPlan &P, const int32_t *cam, const int32_t *lm) {
             if ((P.meta[(size_t)(f + q)] >> 16) != ll) return bad("ll differs inside a landmark", s, q);
         }
     }
-    // chunks
-    if ((int)P.chunk_tile.size() != P.n_chunks + 1 || P.chunk_tile[0] != 0 || P.chunk_tile[(size_t)P.n_chunks] != T)
-        return bad("chunk tile ranges");
-    int max_used = 0;
-    for (int ch = 0; ch < P.n_chunks; ++ch) {
-        int t0 = P.chunk_tile[(size_t)ch], t1 = P.chunk_tile[(size_t)ch + 1];
-        if (t1 <= t0 || t1 - t0 > P.max_tiles) return bad("chunk tile count", ch, t1 - t0);
-        int pb = P.chunk_part[(size_t)ch], ns = P.chunk_part[(size_t)ch + 1] - pb;
-        if (ns < 1 || ns > P.max_slots) return bad("chunk slot count", ch, ns);
-        if (ns > max_used) max_used = ns;
-        std::vector<int> used((size_t)ns, 0);
-        for (int64_t s = (int64_t)t0 * kTile; s < (int64_t)t1 * kTile; ++s) {
-            if (P.meta[(size_t)s] == kPad) continue;
-            int slot = (int)(P.meta[(size_t)s] & 0xFFFFu);
-            if (slot >= ns) return bad("slot beyond chunk", ch, slot);
-            if (P.part_cam[(size_t)(pb + slot)] != cam[P.slot_obs[(size_t)s]]) return bad("slot camera", ch, slot);
-            used[(size_t)slot] = 1;
-        }
-        for (int k = 0; k < ns; ++k)
-            if (!used[(size_t)k]) return bad("unused slot", ch, k);
-    }
-    // camera CSR over partial rows
-    if ((int64_t)P.cam_part_idx.size() != P.n_part || P.cam_part_ptr[(size_t)P.np] != P.n_part)
-        return bad("partial CSR size");
-    for (int c = 0; c < P.np; ++c) {
-        for (int j = P.cam_part_ptr[(size_t)c]; j < P.cam_part_ptr[(size_t)c + 1]; ++j) {
-            int row = P.cam_part_idx[(size_t)j];
-            if (row < 0 || row >= P.n_part || P.part_cam[(size_t)row] != c) return bad("partial CSR row", c, row);
-            if (j > P.cam_part_ptr[(size_t)c] && row <= P.cam_part_idx[(size_t)j - 1]) return bad("CSR order", c, j);
-            if (P.part_dst[(size_t)row] != j) return bad("partial destination", row, j);
-        }
-    }
-    return true;
+    return check_chunks(P, P, P.max_slots, cam) && check_cameras(P, cam);
 }
 
 bool check_multi(const HostPlan &P, const HostMultiPlan &M, const int32_t *cam) {
@@ -129,6 +176,8 @@ bool check_multi(const HostPlan &P, const HostMultiPlan &M, const int32_t *cam) 
                     return bad("pair slots not consecutive", t, q);
                 pair_grp[(size_t)own] = group[(size_t)c];
             }
+            for (int q = 0; q < kTile; ++q)
+                if (M.pair_grp[(size_t)((int64_t)t * kTile + q)] != pair_grp[(size_t)q]) return bad("pair subset", t, q);
             for (int q = 0; q < kTile; ++q) {
                 size_t s = (size_t)((int64_t)t * kTile + q);
                 if (P.slot_obs[s] < 0) continue;
@@ -150,6 +199,8 @@ bool check_multi(const HostPlan &P, const HostMultiPlan &M, const int32_t *cam) 
             }
         }
     }
+    // the two-pass form's subsets, and the count that it is refused by
+    if (multi_tile_outputs(P, M) > M.max_out) return bad("out-pairs of a tile", multi_tile_outputs(P, M), M.max_out);
     for (int64_t i = 0; i < M.n_part; ++i)
         if (part_key[(size_t)i] < 0) return bad("unused out-pair", i);
     for (int64_t k = 0; k < (int64_t)P.np * N; ++k)
@@ -163,8 +214,9 @@ bool check_multi(const HostPlan &P, const HostMultiPlan &M, const int32_t *cam) 
 extern "C" {
 
 // Host-only: plan the layout for host index arrays, check its invariants (and
-// those of the plan of the multidirectional product for each N in Ns), and
-// report sizes: stats[0] tiles, [1] chunks, [2] partial rows, [3] largest chunk
+// those of the plan of the multidirectional product for each N in Ns, and, with
+// max_tiles = 0, of layouts whose chunks take shares of the tiles and of other chunks
+// over the same tiles, as copies of the stream have them), and report sizes: stats[0] tiles, [1] chunks, [2] partial rows, [3] largest chunk
 // slot count, then per N: [4 + 3j] multi chunks, [5 + 3j] out-pairs, [6 + 3j]
 // largest chunk out count.  Returns BA_OK, the planner's error, or
 // BA_ERR_INVALID_ARG with ba_last_error() naming the broken invariant.
@@ -199,6 +251,27 @@ ba_status ba_plan_validate(int32_t n_cams, int32_t n_lms, int64_t n_obs, const i
             stats[4 + 3 * j] = M.n_chunks;
             stats[5 + 3 * j] = M.n_part;
             stats[6 + 3 * j] = M.max_out;
+        }
+    }
+    if (max_tiles == 0) {
+        // a number of chunks to make: one; some; one fewer than the tiles, as many, one more
+        const int T = (int)P.n_tiles;
+        for (int shares : {1, 7, 96, T - 1, T, T + 1}) {
+            if (shares < 1) continue;
+            HostPlan Q;
+            st = build_plan(n_cams, n_lms, n_obs, cam, lm, max_slots ? max_slots : 256, 0, Q, err, nullptr, 0, 0, 0, shares);
+            if (st != BA_OK) {
+                g_check_err = err;
+                return st;
+            }
+            if (!check_plan(Q, cam, lm)) return BA_ERR_INVALID_ARG;
+            for (int slots : {64, 128, 256}) {
+                HostChunks C;
+                build_chunks(Q, slots, 0, 2 * shares, C);
+                if (!check_chunks(Q, C, slots, cam)) return BA_ERR_INVALID_ARG;
+                build_chunks(Q, slots, 1 + shares % 5, 0, C);
+                if (!check_chunks(Q, C, slots, cam)) return BA_ERR_INVALID_ARG;
+            }
         }
     }
     return BA_OK;

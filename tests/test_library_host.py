@@ -67,6 +67,19 @@ def test_plan_invariants_chunk_shapes(L, max_slots, max_tiles):
     assert st[3] <= max_slots
 
 
+@pytest.mark.parametrize("make,max_slots", [
+    (lambda: synth.tiny(n_cams=5, n_lms=9, seed=3, c_hi=4), 0),                                    # one tile
+    (lambda: synth.ring_problem(n_cams=90, n_lms=700, c_lo=2, c_hi=9, seed=4, shuffle=True), 0),
+    (lambda: synth.cap_problem(n_cams=150, n_lms=4000, seed=5), 64),      # chunks that end for want of slots
+    (lambda: synth.cap_problem(n_cams=300, n_lms=6000, seed=6), 440),
+], ids=["one-tile", "shuffled", "64-slots", "440-slots"])
+def test_plan_invariants_shares_and_copies(L, make, max_slots):
+    """With max_tiles = 0 the validator also plans chunks by shares of the tiles (one to more than
+    there are tiles) and other chunks over the same tiles, and checks the camera order's tables."""
+    r, err, st = _validate(L, make(), Ns=(2, 5), max_slots=max_slots)
+    assert r == 0, err
+
+
 def test_plan_rejects_bad_observations(L):
     p = synth.tiny(n_cams=4, n_lms=20, seed=0)
     q = synth.tiny(n_cams=4, n_lms=20, seed=0)
