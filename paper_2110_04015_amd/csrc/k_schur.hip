@@ -357,10 +357,12 @@ __device__ __forceinline__ double wave_rows(const double *__restrict__ rows, int
 // four cameras (the Gram products Q^T P and P^T r of a one-column block, Q = S P).
 // The skip flag, the camera's row range and its entries of v, diag(U) and gr are
 // requested together, before anything waits on one of them (a wavefront past the last
-// camera reads the last camera's and drops them).  With z (PCG) the product's vector is
-// z - beta v, which every chunk formed for its cameras and this kernel, after all of them,
-// stores in v: a launch less per iteration (571 cameras and fewer: 2 us and the gap of one).
-template <int DP, bool HIST = false>
+// camera reads the last camera's and drops them).  PCG: the product's vector is z - beta v,
+// which every chunk formed for its cameras and this kernel, after all of them, stores in v: a
+// launch less per iteration (571 cameras and fewer: 2 us and the gap of one).  (An instance of
+// its own: with d_p = 6 the run-time test took four more registers and 0.3 us, 5.20 against
+// 4.89 us after the BF16 product of 70 cameras.)
+template <int DP, bool HIST = false, bool PCG = false>
 __global__ __launch_bounds__(256) void k_reduce1(int np, const int32_t *__restrict__ ptr,
                                                  const double *__restrict__ partial,
                                                  const double *__restrict__ dU, double *__restrict__ v,
@@ -380,7 +382,7 @@ __global__ __launch_bounds__(256) void k_reduce1(int np, const int32_t *__restri
     const double dn = done ? *done : 0.0;
     const int32_t ra = ptr[cl], rb = ptr[cl + 1];
     double vi = v[i];
-    const double du = dU[i], zi = z ? z[i] : 0.0, be = z ? *beta : 0.0;
+    const double du = dU[i], zi = PCG ? z[i] : 0.0, be = PCG ? *beta : 0.0;
     const double gi = gram ? gr[i] : 0.0;
     double *yo = HIST ? nullptr : y + i;
     if (HIST) {   // the row's place in its problem's next history column
@@ -389,14 +391,14 @@ __global__ __launch_bounds__(256) void k_reduce1(int np, const int32_t *__restri
         yo = hist + P.hbase + (int64_t)dyn[b].hcols * P.n + (i - P.row0);
     }
     if (dn != 0.0) return;
-    if (z) vi = next_direction(zi, be, vi);
+    if (PCG) vi = next_direction(zi, be, vi);
     double qp = 0.0, pr = 0.0;
     if (c < np && !(seg_skip && seg_skip[cam_seg[c]])) {   // uniform per wavefront
         const double t = wave_rows<DP>(partial, ra, rb, sh[w]);
         if (lane < DP) {
             const double yi = du * vi + t;
             *yo = yi;
-            if (z) v[i] = vi;
+            if (PCG) v[i] = vi;
             if (y32) y32[i] = (float)yi;
             if (gram) {
                 qp = yi * vi;
@@ -442,7 +444,10 @@ int schur_gram_blocks(int np) { return (np + 3) / 4; }
 void launch_schur_reduce(const SchurArgs &a, const double *v, double *y, hipStream_t s) {
     const dim3 g((unsigned)schur_gram_blocks(a.np)), b(256);
     double *vw = const_cast<double *>(v);   // written with a.z only (then the caller's own vector)
-    auto kernel = a.dp == 6 ? k_reduce1<6> : a.hist ? k_reduce1<9, true> : k_reduce1<9>;   // batches: d_p = 9
+    auto kernel = a.dp == 6 ? (a.z ? k_reduce1<6, false, true> : k_reduce1<6>)
+                  : a.hist  ? k_reduce1<9, true>   // batches: d_p = 9
+                  : a.z     ? k_reduce1<9, false, true>
+                            : k_reduce1<9>;
     hipLaunchKernelGGL(kernel, g, b, 0, s, a.np, a.cam_part_ptr, a.partial, a.dU, vw, a.z, a.beta, y, a.done, a.cam_seg,
                        a.seg_skip, a.gram, a.gram_r, a.y32, a.prob, a.dyn, a.hist);
 }
