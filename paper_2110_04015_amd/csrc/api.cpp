@@ -331,8 +331,15 @@ void matvec(ba_system *s, const SchurArgs &a, const double *v, double *y) {
     launch_schur_reduce(a, v, y, s->stream);
 }
 
-// slots whose FP64 camera rows (two of 72 bytes each, and 1.5 KB) fit six times in 160 KiB
-constexpr int kSlotsOfSix = 178;
+// FP32 products with nine parameters: a chunk that sees more cameras than this takes the plan's
+// division (571 cameras dense 58.7 us with it, 59.9 with twice as many chunks; 800 cameras 72 and
+// 84, 1,200 cameras 115 and 111; below, with 190 to 420 cameras, no chunk sees so many).
+constexpr int kMaxSlots32 = 178;
+// With six, the partial rows per tile from which eight chunks per compute unit, of more than a
+// tile each, are too many.  Six / eight: walks of 250 (6 rows), 1,000 (2) and 1,900 cameras (1) 30.7 / 30.2, 59.3 / 55.4 and
+// 98.4 / 87.0 us, rings of 333 (4) and 800 (2) 28.4 / 27.5 and 38.0 / 35.7; dense caps of 190
+// cameras (27), 300 (24) and 571 (20) 35.6 / 37.4, 40.2 / 41.8 and 54.7 / 55.6.
+constexpr int kMaxRows32 = 12;
 
 // Chunks of a precision's product, made with its copy of the records where they may be (see
 // build_system for their number); without them the product takes the plan's.  A failure leaves
@@ -343,8 +350,11 @@ ba_status ensure_chunks(ba_system *s, int precision) try {
     const HostPlan &P = s->plan;
     HostChunks h;
     if (precision == 1) {
-        build_chunks(P, s->own_slots > 0 ? s->own_slots : 256, 0, 2 * schur1_few_chunks(), h);
-        if (h.max_used_slots > kSlotsOfSix) return BA_OK;
+        const int slots = s->own_slots > 0 ? s->own_slots : 256, few = schur1_few_chunks();
+        const int shares = s->dp == 6 ? few * 8 / 3 : 2 * few;
+        build_chunks(P, slots, 0, shares, h);
+        if (s->dp == 6 && P.n_tiles > shares && h.n_part > kMaxRows32 * P.n_tiles) build_chunks(P, slots, 0, 2 * few, h);
+        if (s->dp == 9 && h.max_used_slots > kMaxSlots32) return BA_OK;
     } else {
         const int resident = schur1_resident_chunks(s->dp);
         if (resident <= 0) return BA_OK;
@@ -943,8 +953,8 @@ static ba_status build_system(const ba_problem_desc *d, const ba_build_opts *opt
     // can be resident.  Fewer chunks see more cameras each, hence 256 slots where 128 would end
     // them early.  The other precisions stream less per tile and want more wavefronts; the FP64
     // product is the same with and without their copies, so they have chunks of their own:
-    // FP32 twice as many (while the camera rows of six fit a compute unit), BF16 the resident
-    // number, its product being bound by instructions that fewer wavefronts do not overlap
+    // FP32 twice as many (or eight per compute unit with six parameters a camera, whose records
+    // are shorter still; see ensure_chunks), BF16 the resident number, its product being bound by instructions that fewer wavefronts do not overlap
     // (1,936 cameras: 69 us against 80).  So do batches, whose problems stop one by one.  Per
     // product, resident -> now, FP64 / FP32: 1,936 cameras along a walk (82k tiles) 171 / 97 us
     // -> 160 / 94; a ring of 333 (11.5k) 31.7 / 21.0 -> 28.9 / 19.4; a dense cap of 571 (14.4k)

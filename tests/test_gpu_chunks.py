@@ -13,6 +13,8 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 ba = pytest.importorskip("paper_2110_04015_amd")
 
+from test_gpu_parity import assert_within_rounding, stored_product  # noqa: E402
+
 
 def _dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda", dtype=torch.float64)
@@ -53,6 +55,24 @@ def test_products_and_back_substitution(make):
         assert np.abs(dl - rl).max() <= 1e-11 * np.abs(rl).max()
     finally:
         plain.close()
+        g.close()
+
+
+@pytest.mark.parametrize("make", [
+    lambda: synth.walk_problem(n_cams=150, n_lms=26000, seed=4, name="walk150"),   # few camera rows a tile
+    lambda: synth.cap_problem(n_cams=300, n_lms=24000, seed=5, name="cap300"),     # many
+    lambda: synth.ring_problem(n_cams=60, n_lms=9700, c_lo=2, c_hi=18, seed=6, name="ring60"),   # a tile a chunk
+], ids=["walk150", "cap300", "ring60"])
+def test_copies_of_poses_without_intrinsics(make):
+    p = synth.extrinsics_only(make())
+    o = oracle.System(p)
+    v = np.random.default_rng(8).standard_normal(6 * p.n_cams)
+    g = ba.System.from_problem(p, store_fp32=True, store_bf16=True)
+    try:
+        for prec in ("fp32", "bf16"):
+            ref, bound = stored_product(p, o, prec, v)
+            assert_within_rounding(g.matvec(_dev(v), precision=prec).cpu().numpy(), ref, bound, prec)
+    finally:
         g.close()
 
 
