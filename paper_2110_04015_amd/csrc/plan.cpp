@@ -269,9 +269,11 @@ ba_status build_plan(int np, int nl, int64_t m, const int32_t *cam, const int32_
     // Every iteration of a batch runs the multidirectional product of those problems only
     // that fail the tau-test, and lasts as long as one chunk: with many problems the chunks
     // are made shorter, so that the few that run still fill the device.  24 ring problems of
-    // 50 to 200 cameras (101,342 tiles, FP32, N = 16): 50 tiles per chunk 129 us per product
-    // and 37.5 ms per solve, 8 tiles 50 us and 31.1 ms, 4 tiles 31.5 ms.  2 or 6 problems
-    // (19 or 20 tiles): the same to 2 % for 1x to 8x as many chunks.
+    // 50 to 200 cameras (101,342 tiles, FP32, N = 16): 50 tiles per chunk 129 us per product,
+    // 8 tiles 50 us.  Solves of such problems with 1 / 2 / 4 / 8 times as many chunks as can be
+    // resident, ms: 3 problems 10.3 / 10.4 / 10.4 / 10.7, 5 12.6 / 12.4 / 12.5 / 12.7, 8 16.4 /
+    // 15.9 / 15.8 / 16.3, 12 20.5 / 19.2 / 18.8 / 18.9, 16 24.3 / 22.5 / 21.6 / 21.5, 24 34.6 /
+    // 30.4 / 28.7 / 28.0 (FP64, N = 4 and 45 to 90 cameras the same way): a third of the problems.
     if (cam_seg) {
         int problems = 1;
         for (int c = 1; c < np; ++c) problems += cam_seg[c] != cam_seg[c - 1];
