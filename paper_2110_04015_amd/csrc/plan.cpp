@@ -441,7 +441,10 @@ ba_status build_multi_plan(const HostPlan &P, int N, int max_out, HostMultiPlan 
 ba_status build_multi_chunks(const HostPlan &P, int max_out, HostMultiPlan &M, std::string &err) {
     const int np = P.np, N = M.N;
     const int64_t T = P.n_tiles;
-    // chunks over out-pairs (camera, subset), numbered within a chunk as they first appear
+    // chunks over out-pairs (camera, subset), numbered within a chunk tile by tile, a tile's in
+    // (camera, subset) order: the order in which the chunk's rows are written out, close to that
+    // of their places (numbered as the slots name them, products of small subsets took 0.5 to 4 %
+    // longer: 120 cameras, N = 29, BF16 36.4 -> 38.0 us)
     struct Seen {
         int32_t tile, chunk, local;   // the last tile and chunk that held it, its number there
     };
@@ -473,15 +476,16 @@ ba_status build_multi_chunks(const HostPlan &P, int max_out, HostMultiPlan &M, s
             M.chunk_seg.push_back(P.tile_seg[(size_t)t]);
         }
         M.tile_oidx[(size_t)t] = (uint32_t)at;
+        const size_t first_new = part_key.size();
         for (int i = 0; i < n; ++i) {
             Seen &e = seen[(size_t)keys[(size_t)i]];
-            if (e.chunk != chunk) {
-                e.chunk = chunk;
-                e.local = outs++;
-                part_key.push_back(keys[(size_t)i]);
-            }
-            M.oidx[(size_t)at++] = (uint16_t)e.local;
+            if (e.chunk == chunk) continue;
+            e.chunk = chunk;
+            part_key.push_back(keys[(size_t)i]);
         }
+        std::sort(part_key.begin() + (int64_t)first_new, part_key.end());
+        for (size_t k = first_new; k < part_key.size(); ++k) seen[(size_t)part_key[k]].local = outs++;
+        for (int i = 0; i < n; ++i) M.oidx[(size_t)at++] = (uint16_t)seen[(size_t)keys[(size_t)i]].local;
         M.max_out = std::max(M.max_out, outs);
         int off = 0;
         for (int q = 0; q < kTile && M.mmeta[(size_t)(t * kTile + q)] != kPad; ++q) {

@@ -149,6 +149,7 @@ bool check_multi(const HostPlan &P, const HostMultiPlan &M, const int32_t *cam) 
     for (int ch = 0; ch < M.n_chunks; ++ch) {
         int pb = M.chunk_part[(size_t)ch], no = M.chunk_part[(size_t)ch + 1] - pb;
         if (no < 1 || no > M.max_out) return bad("multi chunk out count", ch, no);
+        int known = 0;   // out-pairs of the chunk's tiles so far
         for (int t = M.chunk_tile[(size_t)ch]; t < M.chunk_tile[(size_t)ch + 1]; ++t) {
             // the product loads a tile's first output-row entry with the tile, for every
             // lane, padding lanes included: every tile's list holds at least one entry
@@ -197,6 +198,16 @@ bool check_multi(const HostPlan &P, const HostMultiPlan &M, const int32_t *cam) 
                     pk = key;
                 }
             }
+            // the tile's new out-pairs follow those of the tiles before it, in order
+            int upto = known;
+            while (upto < no && part_key[(size_t)(pb + upto)] >= 0) {
+                if (upto > known && part_key[(size_t)(pb + upto)] <= part_key[(size_t)(pb + upto - 1)])
+                    return bad("order of a tile's out-pairs", t, upto);
+                ++upto;
+            }
+            for (int o = upto; o < no; ++o)
+                if (part_key[(size_t)(pb + o)] >= 0) return bad("out-pair numbering", t, o);
+            known = upto;
         }
     }
     // the two-pass form's subsets, and the count that it is refused by
