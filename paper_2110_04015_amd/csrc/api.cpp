@@ -220,7 +220,7 @@ void free_all(ba_system *s) {
     sfree(s, s->bsr_val);
     if (s->host_pinned) (void)hipHostFree(s->host_pinned);
     s->host_pinned = nullptr;
-    s->host_pinned_dev = nullptr;
+    s->host_tagged = s->host_tagged_dev = nullptr;
     free_multi(s, s->multi);
     for (hipEvent_t e : s->prof_events) (void)hipEventDestroy(e);
     s->prof_events.clear();
@@ -615,36 +615,36 @@ ba_status ensure_tickets(ba_system *s, int64_t count) {
 ba_status ensure_pinned(ba_system *s) {
     if (s->ws_counting) return BA_OK;
     if (!s->host_pinned) {
-        // SC_COUNT scalars and the tag of the kernel-written copy
-        HIPCHK(hipHostMalloc((void **)&s->host_pinned, (SC_COUNT + 1) * sizeof(double), hipHostMallocMapped));
-        s->host_pinned[SC_COUNT] = 0.0;
-        HIPCHK(hipHostGetDevicePointer((void **)&s->host_pinned_dev, s->host_pinned, 0));
+        // SC_COUNT scalars, and as many with tags, written by kernels
+        static_assert(SC_COUNT % 2 == 0, "the tagged scalars are 16-byte aligned");
+        HIPCHK(hipHostMalloc((void **)&s->host_pinned, SC_COUNT * (sizeof(double) + sizeof(Tagged)), hipHostMallocMapped));
+        s->host_tagged = reinterpret_cast<Tagged *>(s->host_pinned + SC_COUNT);
+        for (int i = 0; i < SC_COUNT; ++i) s->host_tagged[i] = Tagged{0.0, 0.0};
+        HIPCHK(hipHostGetDevicePointer((void **)&s->host_tagged_dev, s->host_pinned, 0));
+        s->host_tagged_dev = reinterpret_cast<Tagged *>(reinterpret_cast<double *>(s->host_tagged_dev) + SC_COUNT);
     }
     return BA_OK;
 }
 
-// Waits for the scalars a kernel wrote to host_pinned with the tag `tag` (written after
-// the values, which the kernel released at system scope first): the host polls the tag,
-// with no event between the kernels.  Only when the tag is late (10 ms) does it ask the
-// stream, every 10 ms, whether it failed or drained without the tag (an error either
+// Waits for the scalars a kernel wrote to host_tagged with the tag `tag`: the host polls
+// them, with no event between the kernels.  Only when they are late (10 ms) does it ask the
+// stream, every 10 ms, whether it failed or drained without them (an error either
 // way): a stream query can itself put work on the device's queue.
 static ba_status scalars_wait_tag(ba_system *s, double tag, double *out) {
-    volatile double *t = s->host_pinned + SC_COUNT;
+    const volatile Tagged *v = s->host_tagged;
     const auto t0 = std::chrono::steady_clock::now();
     auto next = t0 + std::chrono::milliseconds(10);
-    for (int64_t spin = 1; *t != tag; ++spin) {
+    for (int64_t spin = 1; !tagged_read(v, SC_COUNT, tag, out); ++spin) {
         if ((spin & 255) == 0 && std::chrono::steady_clock::now() >= next) {
             next += std::chrono::milliseconds(10);
             const hipError_t e = hipStreamQuery(s->stream);
             if (e != hipSuccess && e != hipErrorNotReady)
                 return fail(BA_ERR_HIP, std::string("waiting for the MCG scalars: ") + hipGetErrorString(e));
-            if (e == hipSuccess && *t != tag) return fail(BA_ERR_HIP, "the MCG scalars were not written");
+            if (e == hipSuccess && !tagged_read(v, SC_COUNT, tag, out)) return fail(BA_ERR_HIP, "the MCG scalars were not written");
             if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(60))
                 return fail(BA_ERR_HIP, "timed out waiting for the MCG scalars");
         }
     }
-    std::atomic_thread_fence(std::memory_order_acquire);
-    memcpy(out, s->host_pinned, SC_COUNT * sizeof(double));
     return BA_OK;
 }
 
@@ -1583,7 +1583,7 @@ static ba_status mcg_core(ba_system *s, const double *bt, bool report_true, int 
             // term, rho = r^T M^-1 r and Z = D^-1 r + U (U^T r), the last by the next kernel)
             s->sc_tag += 1.0;
             launch_mcg_xrz(s->np, k, Ph + (int64_t)off * n, Qh + (int64_t)off * n, alpha, x, r, s->Dchol, z, red,
-                           s->tickets, gamma, sc, s->host_pinned_dev, s->sc_tag, N, tau, opts.eps, q, s->dp, g1, lr);
+                           s->tickets, gamma, sc, s->host_tagged_dev, s->sc_tag, N, tau, opts.eps, q, s->dp, g1, lr);
             if (lowrank) launch_lr_zadd(n, s->Ulr, lr.w, z, q);
             // Everything up to the next iteration's Gram products that a one-column block
             // needs goes ahead of the read-back, so the device stays busy while the host

@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "../../include/ba.h"
+#include "tagged.h"
 
 namespace ba {
 
@@ -251,8 +252,8 @@ struct ba_system {
     double *lr_proj = nullptr;      // kRedBlocks x 8 projections U^T r
     size_t small_cap = 0;
     double *host_pinned = nullptr;  // pinned host scalars
-    double *host_pinned_dev = nullptr;  // the same memory as kernels address it
-    double sc_tag = 0.0;            // tag of the last scalars a kernel wrote to host_pinned[SC_COUNT]
+    ba::Tagged *host_tagged = nullptr, *host_tagged_dev = nullptr;   // those a kernel writes; as it addresses them
+    double sc_tag = 0.0;            // tag of the last of them
     ba::DevMulti multi;
     int64_t multi_serial = 0;       // layouts made so far
     // batches: problem of every camera and of every chunk of the S product (device)

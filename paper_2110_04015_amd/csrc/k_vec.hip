@@ -687,7 +687,7 @@ __global__ __launch_bounds__(kNT) void k_mcg_xrz(int np, int k, const double *__
                                                  const double *__restrict__ Dchol, double *__restrict__ z,
                                                  double *__restrict__ partials, uint32_t *__restrict__ ticket,
                                                  double *gamma, double *__restrict__ sc,
-                                                 double *__restrict__ host_sc, double tag, int N, double tau,
+                                                 Tagged *__restrict__ host_sc, double tag, int N, double tau,
                                                  double eps, XrzGram g1, XrzLowrank lr) {
     constexpr int CB = kNT / DP;
     constexpr int NL = DP * (DP + 1) / 2;
@@ -859,15 +859,14 @@ __global__ __launch_bounds__(kNT) void k_mcg_xrz(int np, int k, const double *__
         mcg_scalars_put(v, sc);
         __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (host_sc) {   // all the scalars, for the host's read-back: lane i writes scalar i
+    if (host_sc) {   // all the scalars, for the host's read-back: lane i writes scalar i and the tag
         const double b_rr = __shfl(v.rr, 0, 64), b_rho = __shfl(v.rho, 0, 64), b_t = __shfl(v.t, 0, 64);
         const double b_sm = __shfl(v.skipm, 0, 64), b_kn = __shfl(v.kn, 0, 64), b_ss = __shfl(v.skips, 0, 64);
         double mine = t == SC_RANK ? rank_sh : scv;
         mine = t == SC_RR ? b_rr : t == SC_RHO ? b_rho : t == SC_T ? b_t : mine;
         mine = t == SC_SKIPM ? b_sm : t == SC_KN ? b_kn : t == SC_SKIPS ? b_ss : mine;
-        if (t < SC_COUNT) host_sc[t] = mine;
-        __threadfence_system();   // the values reach the host before the tag
-        if (t == 0) host_sc[SC_COUNT] = tag;
+        typedef double dbl2_t __attribute__((ext_vector_type(2)));   // one 16-byte store
+        if (t < SC_COUNT) reinterpret_cast<dbl2_t *>(host_sc)[t] = dbl2_t{mine, tag};
     }
 }
 
@@ -875,7 +874,7 @@ int mcg_xrz_blocks(int np, int dp) { return (np + kNT / dp - 1) / (kNT / dp); }
 
 void launch_mcg_xrz(int np, int k, const double *P, const double *Q, double *alpha, double *x, double *r,
                     const double *Dchol, double *z, double *partials, uint32_t *ticket, double *gamma,
-                    double *sc, double *host_sc, double tag, int N, double tau, double eps, hipStream_t s, int dp,
+                    double *sc, Tagged *host_sc, double tag, int N, double tau, double eps, hipStream_t s, int dp,
                     XrzGram g1, XrzLowrank lr) {
     const unsigned nb = (unsigned)mcg_xrz_blocks(np, dp);
     if (dp == 6)

@@ -6,6 +6,8 @@
 
 #include <algorithm>
 
+#include "tagged.h"
+
 namespace ba {
 
 // slots of the device scalar array of the solvers
@@ -286,9 +288,8 @@ void launch_pinv_alpha(int k, const double *partials, int nblocks, double *Dp, d
 // Alg. 2's stop and tau tests (sc[SC_RR], [SC_RHO], [SC_T], and the next block's width in
 // sc[SC_SKIPM], [SC_KN], [SC_SKIPS]), from
 // mcg_xrz_blocks(np, dp) blocks' partials (2 per block) added by the last block to arrive
-// (ticket: a zero counter, left zero); that block also copies sc[0, SC_COUNT) to host_sc
-// (nullable: mapped host memory of SC_COUNT + 1 doubles) and, once those values are
-// released at system scope, writes tag to host_sc[SC_COUNT]
+// (ticket: a zero counter, left zero); that block also copies sc[0, SC_COUNT), each with the
+// tag, to host_sc (nullable: mapped host memory, see tagged.h)
 // For a one-column block (g1.part set) the kernel also takes the place of the Gram and
 // pseudo-inverse kernels: Delta and gamma from the camera reduction's partials (nb blocks,
 // schur_gram_blocks), then Delta^+ into g1.Dp, gamma, alpha, sc[SC_RANK] and the block entry.
@@ -311,7 +312,7 @@ struct XrzLowrank {
 int mcg_xrz_blocks(int np, int dp);
 void launch_mcg_xrz(int np, int k, const double *P, const double *Q, double *alpha, double *x, double *r,
                     const double *Dchol, double *z, double *partials, uint32_t *ticket, double *gamma,
-                    double *sc, double *host_sc, double tag, int N, double tau, double eps, hipStream_t s,
+                    double *sc, Tagged *host_sc, double tag, int N, double tau, double eps, hipStream_t s,
                     int dp = 9, XrzGram g1 = XrzGram(), XrzLowrank lr = XrzLowrank());
 // z += U w (n x 8 row-major U, w of 8 doubles)
 void launch_lr_zadd(int64_t n, const double *U, const double *w, double *z, hipStream_t s);
