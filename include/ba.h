@@ -79,8 +79,8 @@ typedef struct {
     int32_t store_fp32;      /* also keep an FP32 copy of the Jacobian stream (precision FP32) */
     int32_t store_bf16;      /* also keep a BF16 copy with per-camera column scales (precision BF16) */
     int32_t max_slots;       /* cameras per landmark chunk (0 = automatic, at most 256; 64..440) */
-    int32_t max_tiles;       /* 64-observation tiles per chunk of the S product; 0: chosen from the device,
-                                the problem's size and the copies kept */
+    int32_t max_tiles;       /* 64-observation tiles per chunk of the S product; 0: chosen from the device and
+                                the problem's size, for each precision */
     int32_t explicit_schur;  /* also form S explicitly in 9x9 block-sparse rows (the paper's representation,
                                 Sec. 3.2 and 4.1); FP64 S products then read it instead of the Jacobians.
                                 BA_ERR_UNSUPPORTED when a row has more than 40,797 blocks */

@@ -408,7 +408,8 @@ ba_status ensure_precision(ba_system *s, int precision) {
 // records twice whatever their number.  Measured, one pass / two passes (us, FP64): walk of
 // 300 cameras, 1.8 rows 48 / 73, 3.5 rows 75 / 89; ring of 50 cameras, 4.2 rows 31 / 33, 10.5
 // rows 56 / 35; cap of 571 cameras, 2.0 rows 103 / 125, 3.7 rows 155 / 130, 5.8 rows 272 / 140,
-// 10.0 rows 1035 / 175; cap of 80, 6.2 rows 63 / 39.
+// 10.0 rows 1035 / 175; cap of 80, 6.2 rows 63 / 39.  Just above the line, a ring of 120 cameras
+// with 5.2 rows: FP64 52.7 / 54.2, FP32 50.8 / 46.0.
 constexpr double kTwoPassRows = 5.0;
 
 // The two-pass product's camera-major records in a precision (the tile stream of that

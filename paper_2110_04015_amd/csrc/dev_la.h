@@ -11,6 +11,11 @@ constexpr int kMaxK = 64;   // widest direction block (Delta_i is at most 64 x 6
 
 constexpr int kNT = 256;   // threads of the reduction blocks
 
+// Two doubles, eight-byte aligned (the caller's arrays need no more)
+struct alignas(8) Dbl2 {
+    double x, y;
+};
+
 // Cross-lane move of a double by a DPP control (lanes whose source lies outside the
 // control's reach, or outside row_mask, read 0).
 template <int CTRL, int ROW_MASK = 0xf>

@@ -9,11 +9,6 @@ namespace ba {
 
 // ---------------------------------------------------------------- validation
 
-// Two doubles, eight-byte aligned (the caller's arrays need no more)
-struct alignas(8) Dbl2 {
-    double x, y;
-};
-
 // Sets the flag when a value of a (count0), b (count1) or c (count2, all even) is not finite:
 // its exponent bits are all set.  Sixteen-byte loads, eight of a contiguous 32 KiB in flight
 // (1.06 GB just written by k_project: 221 us; with the eight a grid's width apart 251).

@@ -17,11 +17,6 @@ namespace ba {
 
 constexpr int kLmThreads = 256;
 
-// Two doubles, eight-byte aligned (the caller's arrays need no more)
-struct alignas(8) Dbl2 {
-    double x, y;
-};
-
 // Copies the wavefront's 64 rows of W 16-byte words from LDS (row after row) to rows of the
 // caller's array, consecutive lanes to consecutive words; rows past cnt stay out.
 template <int W>

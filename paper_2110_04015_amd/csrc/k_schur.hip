@@ -560,8 +560,11 @@ __device__ __forceinline__ PairVals<T> pair_tile(const T (&J)[2 * DP + 6], const
         double gs[3];   // the pair's total, in its last lane (the only one that uses it)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            // TWO: contracted as the compiler contracts the one-pass kernel's short chunks (the
-            // dense problems the two-pass form takes), so that both give the same term
+            // TWO: contracted as this compiler contracts the one-pass kernel's short chunks (the
+            // dense problems the two-pass form takes), so that both give the same term.  Another
+            // compiler may choose otherwise in the one-pass kernel: then the two forms part by
+            // one FP32 rounding of a term, as that kernel's two copies of this code do already
+            // (written out for both, its results move by as much against what they were)
             T t;
             if constexpr (!TWO) t = J[L0 + k] * e0 + J[L1 + k] * e1;
             else if constexpr (PREC == 2 && DP == 6) t = fmaf(J[L0 + k], e0, J[L1 + k] * e1);

@@ -223,9 +223,10 @@ void launch_pcg_update_xr(int64_t n, const double *partials_dq, int n_dq, double
 // r -= alpha Q, Z = D^-1 r, and the partial sums of |r|^2 and Phi = Q^T Z.  Block b owns
 // the poses [b CB, (b + 1) CB) (CB = kNT / DP), whose rows it updates and whose D^-1
 // solves it takes.  The block that arrives last (an agent-scope counter, left zero) adds
-// the partials in block order and takes the step-end decisions of k_pcg_step_end (on a
-// breakdown flag, the stop test, the iteration cap), then beta = Phi / Delta into the
-// scalars for k_pcg_update_p.  As in k_mcg_xrz, the loads that need nothing formed here
+// the partials in block order and takes the step-end decisions of k_pcg_step_end (breakdown
+// where Delta, which every block forms, is not positive; the stop test, the iteration cap),
+// then beta = Phi / Delta into the scalars for whoever forms P_{i+1} (the next product or
+// k_pcg_update_p).  As in k_mcg_xrz, the loads that need nothing formed here
 // (x, r, P, Q and the Cholesky factor of the thread's camera; threads without a row or a
 // camera read the block's first and ignore them) go before the reduction of the partials,
 // which are read as pairs with eight loads in flight.
