@@ -250,9 +250,12 @@ void launch_cam_slots(int64_t m, const int64_t *cam_obs, const int64_t *obs_slot
 // The work-groups run in the order of their first slot, consecutive ones on one XCD, so that
 // the cameras that share tiles read them from its L2 at about the same time.  r0 = 0 when
 // only the lambda-dependent sums are asked for: the others' accumulators do not see it.
-// Lane layouts as in the Gram kernel of the solvers.  Bound by the scattered 16-byte loads
-// (twenty per observation keep the address units busy for three quarters of the time; of the
-// lines read, 1.9 GB come from HBM for 1.0 GB of records).  5.08M observations of 1,936
+// Lane layouts as in the Gram kernel of the solvers.  No unit is full: the address units (twenty
+// scattered 16-byte loads per observation) are busy for 70 % of the time, vector issue for 30 %,
+// the matrix cores for 14 %, and a wavefront waits for memory for 42 % of its own.  Loads,
+// barrier and products of a work-group follow each other, and 53 KB of LDS leave three of them
+// to a compute unit to overlap.  Fewer address cycles alone gain nothing (camera rows read from
+// the caller's Jacobians by lanes in turn: 508 against 517 us).  5.08M observations of 1,936
 // cameras: 506 us, against 354 (U, b_p) + 1,389 us (E, w) with a wavefront per camera and the
 // sums on the vector units; ba_set_lambda 1,420 -> 500 us.  571 cameras of very uneven
 // popularity, 897k observations: an update 6.1 -> 0.45 ms.
