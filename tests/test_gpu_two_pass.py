@@ -91,6 +91,24 @@ def test_batch_skips_and_layout_change():
     b.close()
 
 
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_batch_skips_in_reduced_precision(prec):
+    """Problems of a batch on either branch of an iteration: each ends with the bits of a batch of its
+    own.  (Every chunk is one tile and every sum of a problem runs over that problem alone, in an
+    order that does not depend on the others.)"""
+    probs = [synth.cap_problem(n_cams=n, n_lms=40 * n, seed=n, name=f"cap{n}") for n in (24, 40, 33)]
+    kw = dict(eps=1e-13, max_iter=8, precision=prec, max_outer=1, max_inner=8, inner_eps=1e-13)
+    b = ba.Batch(probs)
+    x, stats, _, _ = b.mcg(20, 10.0, **kw)
+    assert all(0 < s.multi_steps < s.iterations for s in stats)
+    for p, xi, s in zip(probs, b.split(x), stats):
+        alone = ba.Batch([p])
+        y, so, _, _ = alone.mcg(20, 10.0, **kw)
+        assert so[0].multi_steps == s.multi_steps and torch.equal(xi, y), p.name
+        alone.close()
+    b.close()
+
+
 @pytest.mark.parametrize("name,N", [("cap70", 17), ("ring64", 64), ("dp6", 47)])
 def test_without_room_for_records(name, N):
     """The product reads the tile stream then, to the same bits: after a solve whose history fits no
